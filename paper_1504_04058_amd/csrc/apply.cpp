@@ -205,7 +205,6 @@ asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int n
         L.act = act;
         L.nact = nact;
         L.in_mode = IN_GRID;
-        L.out_mode = OUT_GRID_STORE;
         L.r = r;
         L.out = (m == 1) ? z : P->d_U;
         solve_cost(P, 0, m, nact, 2.0, &by, &fl);
@@ -241,9 +240,7 @@ asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int n
             L.act = act;
             L.nact = nact;
             L.in_mode = IN_BOUNDARY;
-            L.out_mode = OUT_GRID_STORE;
             L.out = z;
-            L.out_mode_L = OUT_GRID_STORE;
             L.out_L = P->d_stage;
             L.W = P->d_W;
             L.w_rhs = w_rhs;
@@ -289,9 +286,7 @@ asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int n
         L.act = act;
         L.nact = nact;
         L.in_mode = IN_BOUNDARY;
-        L.out_mode = OUT_GRID_STORE;
         L.out = z;
-        L.out_mode_L = OUT_GRID_STORE;
         L.out_L = P->d_stage;
         L.W = P->d_W;
         L.w_rhs = w_rhs;
@@ -340,32 +335,44 @@ static asp_status compute_transfer(asp_plan* P) {
         ASP_HIP(P, launch_rgf2d(P, P->idx_R(2), P->idx_L(2), nj, P->stream));
         t.end();
     }
+    double fb = 0, L2 = 0;
+    int maxL = 0;
     for (int side = 0; side < 2; ++side) {
         const int first = side == 0 ? P->idx_R(2) : P->idx_L(2);
-        double fb = 0, L2 = 0;
         for (int s = first; s < first + nj; ++s) {
             const SubDesc& d = P->subs[s];
             fb += factor_bytes_of(P, d);
             L2 += (double)d.L * d.L;
+            maxL = std::max(maxL, d.L);
         }
-        for (int kind = 0; kind < 2; ++kind) {
-            SolveLaunch L;
-            L.job0 = first;
-            L.njobs = nj;
-            L.rl = true;
-            L.nact = P->n;
-            L.in_mode = IN_TWIST;
-            L.out_mode = OUT_LINE;
-            L.twist_kind = kind;
-            // about n^2 / 2 block steps of L^2 complex MACs per problem and kind;
-            // the factor read once per chunk over half the blocks on average
-            const double chunks = (P->n + solve_rhs_per_block(P->LR_RL) - 1) / solve_rhs_per_block(P->LR_RL);
-            const double by = 0.5 * chunks * fb + 0.5 * (double)nj * P->n * P->n * esz;
-            const double flk = 0.5 * (double)P->n * P->n * L2 * 8.0;
-            KTimer t(P, ASP_K_TRANSFER, by, flk);
-            ASP_HIP(P, launch_solve2d(P, L, P->stream));
-            t.end();
-        }
+    }
+    SolveLaunch L;
+    L.job0 = P->idx_R(2);
+    L.job1 = P->idx_L(2);
+    L.njobs0 = nj;
+    L.njobs = 2 * nj;
+    L.rl = true;
+    L.nact = P->n;
+    L.in_mode = IN_TWIST;
+    const double nn = (double)P->n * P->n;
+    {
+        // n^2 / 2 block steps of L^2 complex MACs per problem in all; the factor
+        // read once per chunk of columns and triangle over half of a half's blocks
+        KTimer t(P, ASP_K_TRANSFER, 0.5 * (P->n / 32.0 + 1) * fb + 0.5 * 2 * nj * nn * esz, 0.5 * nn * L2 * 8.0);
+        ASP_HIP(P, launch_solve2d(P, L, P->stream));
+        t.end();
+    }
+    {
+        L.twist_kind = 2;
+        L.nact = maxL;
+        KTimer t(P, ASP_K_TRANSFER, fb, (double)P->n * maxL * L2 * 8.0);
+        ASP_HIP(P, launch_solve2d(P, L, P->stream));
+        t.end();
+    }
+    {
+        KTimer t(P, ASP_K_TRANSFER, 0.5 * 2 * nj * nn * esz, 0.5 * 2 * nj * nn * maxL * 8.0);
+        ASP_HIP(P, launch_map_cross(P, L, P->stream));
+        t.end();
     }
     return ASP_OK;
 }
@@ -464,7 +471,6 @@ extern "C" asp_status asp_subsolve(asp_plan* P, int kind, int p, const void* in,
     L.njobs = 1;
     L.rl = kind != ASP_SUB_M;
     L.nact = nrhs;
-    L.out_mode = OUT_GRID_STORE;
     L.out = P->d_stage;
     if (kind == ASP_SUB_M) {
         // y on X_p into a grid-shaped copy of the input

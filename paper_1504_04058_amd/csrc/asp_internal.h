@@ -156,6 +156,10 @@ inline long long sub_table_len(int L) { return 3LL * L + 1; }
 //   sh[k]      s at t = k + 1/2, k = 0..n
 //   inv_sh2[i] 1 / (s(i+1) h^2), i = 0..n-1
 //   inv_s[i]   1 / s(i+1)
+// the middle block of the twisted 2D factorization (1-based): the recurrence
+// runs from block 1 up and from block n down to it
+__host__ __device__ constexpr int mid_block(int n) { return (n + 1) / 2; }
+
 struct AxisTables {
     const zd* sh;
     const zd* inv_sh2;
@@ -335,32 +339,32 @@ hipError_t launch_residual(const asp_plan* P, const zd* b, const zd* x, zd* out,
 hipError_t launch_factor2d(const asp_plan* P, hipStream_t st);
 
 // batched layer solves for the jobs d_jobs[job0 .. job0+njobs) (all M, or all
-// R/L: rl) and the right-hand sides act[0..nact) (NULL: 0..nact-1).
+// R/L: rl) and the right-hand sides act[0..nact) (NULL: 0..nact-1): out = v on X_p.
 //   in_mode   IN_GRID: data = r on X_p;  IN_BOUNDARY: boundary data from the
-//             W rows of the problems;  IN_TWIST: the boundary-map solutions
-//             (nact = n virtual right-hand sides, act ignored)
-//   out_mode  OUT_GRID_STORE: out = v on X_p (IN_GRID, IN_BOUNDARY);
-//             OUT_LINE: the outgoing boundary line into the problem's
-//             boundary map (IN_TWIST); other modes are refused
+//             W rows of the problems;  IN_TWIST: the chains of the boundary
+//             maps of the jobs d_jobs[job0 .. job0+njobs0) and, in the same
+//             launch, d_jobs[job1 ..) (njobs in all)
 struct SolveLaunch {
     int job0 = 0, njobs = 0;
+    int job1 = 0, njobs0 = 0;
     bool rl = false;
     const int* act = nullptr;
     int nact = 0;
-    int in_mode = IN_GRID, out_mode = OUT_GRID_STORE;
+    int in_mode = IN_GRID;
     const zd* r = nullptr;
     const zd* W = nullptr;
     int w_rhs = 0;
     zd* out = nullptr;
     // a launch over R and L problems: the L problems write here instead (NULL: out)
-    int out_mode_L = OUT_GRID_STORE;
     zd* out_L = nullptr;
-    // IN_TWIST: 0 = solutions for unit data at column slot (map columns on and
-    // above the diagonal), 1 = for unit data on the map's output line at row
-    // slot (the entries below the diagonal, by the symmetry of H)
+    // IN_TWIST: 0 = the map entries between blocks of the same half, 2 = rows
+    // grow and jout of the propagators from the middle block (nact = the rows
+    // of the middle block), over the columns of the diagonal blocks
     int twist_kind = 0;
 };
 hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t st);
+// the map entries between blocks of different halves (after the kind-2 chains)
+hipError_t launch_map_cross(const asp_plan* P, const SolveLaunch& L, hipStream_t st);
 // columns grow and jout of the diagonal blocks of H^-1 of the map problems
 // jobs[job0 .. job0 + njobs) and, if job1 >= 0, jobs[job1 .. job1 + njobs)
 // in the same launch (R_p or L_p with 1 < p < m, after asp_factor)

@@ -21,7 +21,6 @@
 namespace {
 
 constexpr int WAVE = 64;
-constexpr int MAXL = 64;   // the most sweep lines of a 2D auxiliary problem
 static_assert(WAVE * 16 <= SINK_ELEMS, "sixteen discard entries per lane");
 
 // raw buffer stores: dword 3 of the resource (32-bit data format) and an
@@ -30,67 +29,232 @@ constexpr int BUF_DW3 = 0x00020000;
 constexpr unsigned BUF_OOB = 0x80000000u;
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off, zd v) {
+// off past the range drops the write, soff (uniform, < 2^31) is added to it.
+// A 16-byte store adds soff to the lane's offset and gives the instruction none:
+// the compiler separates a store of more than 8 bytes from a following write of
+// its data registers only when the instruction has no scalar offset, and with
+// one the last lanes' data were overwritten before the store had read them
+// (measured: low-order bits of FP64 forward results, lanes 60 - 63).
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff, zd v) {
     u32x4 d;
     __builtin_memcpy(&d, &v, sizeof(d));
-    __builtin_amdgcn_raw_buffer_store_b128(d, r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(d, r, off + soff, 0, 0);
 }
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off, zf v) {
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff, zf v) {
     u32x2 d;
     __builtin_memcpy(&d, &v, sizeof(d));
-    __builtin_amdgcn_raw_buffer_store_b64(d, r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(d, r, off, soff, 0);
 }
 
 // ----------------------------------------------------------------------------
-// factorization: one 256-thread workgroup per auxiliary problem.  With LR
-// columns, thread (j, g) holds rows g RPL .. g RPL + RPL - 1 of column j of the
-// current block in registers (LR = 64: 4 row groups of 16; LR = 32: 8 of 4;
-// LR = 16: 16 of 1);
-// S_k is formed from S_{k-1}^-1 in place and inverted by Gauss-Jordan
-// elimination without pivoting (at a few points per wavelength the blocks are
-// close to diagonally dominant; a zero or non-finite pivot is reported as a
-// breakdown).  The pivot row and column pass through LDS, double-buffered by
-// pivot parity: one barrier per pivot.  Arithmetic in double; the stored
-// factor is rounded to TS.
+// Twisted order of the blocks: the block recurrence runs from both ends towards
+// the middle block p = mid_block(n),
+//   S_k = D_k - E_{k-1} S_{k-1}^-1 E_{k-1}   for k = 1 .. p-1,
+//   R_k = D_k - E_k R_{k+1}^-1 E_k           for k = n .. p+1,
+//   M_p = D_p - E_{p-1} S_{p-1}^-1 E_{p-1} - E_p R_{p+1}^-1 E_p,
+// so that every chain of dependent blocks (the factorization, each pass of a
+// solve, the boundary maps) is half as long as with one direction and the two
+// halves run at the same time.  Half `dir` (0: blocks 1 .. p-1, 1: blocks n ..
+// p+1) counts its blocks s = 1 .. np from its end; s = np + 1 is block p.
 // ----------------------------------------------------------------------------
-constexpr int FB = 256;   // threads per factor workgroup
+struct Half {
+    int n, dir, np;
+    __device__ __forceinline__ Half(int n_, int dir_)
+        : n(n_), dir(dir_), np(dir_ ? n_ - mid_block(n_) : mid_block(n_) - 1) {}
+    __device__ __forceinline__ int blk(int s) const { return dir ? n + 1 - s : s; }
+    // the half line between blocks s and s + 1 of this half (index into AxisTables::sh)
+    __device__ __forceinline__ int half_line(int s) const { return dir ? n - s : s; }
+};
 
-template <typename TS, int LR, int ML>
-__device__ __forceinline__ void factor2d_body(const SubDesc& d, AxisTables ax,
+// orders the LDS accesses of one wavefront among its lanes (LDS operations of
+// a wavefront complete in order; this keeps the compiler from moving them)
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// ----------------------------------------------------------------------------
+// factorization: each half of a problem is a chain of np blocks, one 16-row
+// strip of the current block per wavefront, held in the accumulator layout of
+// the FP64 matrix instructions (lane l: column l % 16 of each 16-wide tile,
+// rows l / 16 + 4 v).  S_k is formed from S_{k-1}^-1 in place and inverted by
+// Gauss-Jordan elimination without pivoting, two pivots at a time: the two
+// pivot rows pass through LDS (one exchange per pair), every wavefront inverts
+// the 2 x 2 pivot block itself, and the rank-2 complex update of a tile is one
+// FP64 matrix instruction for the real and one for the imaginary plane (K = 4:
+// re and im of both pivots).  S_k is complex symmetric, and an in-place
+// elimination keeps A[i][k] = -A[k][i] between eliminated and remaining rows
+// and A[i][k] = A[k][i] otherwise, so the pivot columns are read from the pivot
+// rows.  A zero or non-finite pivot is reported as a breakdown.  Arithmetic in
+// double; the stored factor is rounded to TS.
+// What bounds it: the chain pivot row -> LDS -> 2 x 2 inverse (two FP64
+// divisions) -> update, once per pair and block; hence two pivots per exchange
+// and both halves at once.
+// ----------------------------------------------------------------------------
+template <typename TS, int LR>
+__device__ __forceinline__ void factor2d_body(const SubDesc& d, bool live, int npair, int wl, AxisTables ax,
                                               const zd* __restrict__ subtab,
                                               const double* __restrict__ ksq, int n,
                                               cplx<TS>* __restrict__ fac, int* __restrict__ flag,
-                                              zd (&rowbuf)[2][ML + 1], zd (&colbuf)[2][ML],
-                                              zd (&srow)[ML]) {
-    constexpr int G = FB / LR, RPL = LR / G;
+                                              zd* __restrict__ rowbuf_, zd* __restrict__ xch) {
+    constexpr int NW = LR / 16, CT = LR / 16;   // strips per half, tiles per strip
+    using D = Mfma<double>;
+    const Half H(n, wl / NW);
+    const int rt = wl % NW;
     const int L = d.L;
-    const int t = threadIdx.x;
-    const int j = t % LR, g = t / LR;
-    const bool cj = j < L;
+    const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+    zd* rowbuf = rowbuf_ + H.dir * 4 * LR;      // [parity][2][LR]
     const zd* tab = subtab + d.tab_off;
     const zd* ssh = tab;                // s at half lines lo-1/2 .. hi+1/2
     const zd* sinv2 = tab + L + 1;      // 1/(s h^2) on lines lo..hi
     const zd* sinv = tab + 2 * L + 1;   // 1/s on lines lo..hi
-    const int jc = min(j, L - 1);
-    // tables that do not change along axis 1: 1/(s h^2) per row (LDS, zero
-    // past L) and, for this thread's column j, the couplings to rows j -+ 1
-    if (g == 0) srow[j] = csel(cj, sinv2[jc], mk(0.0, 0.0));
-    const zd sj = csel(cj, sinv2[jc], mk(0.0, 0.0));
-    const zd c_lo = ssh[jc], c_hi = ssh[jc + 1], sinvj = sinv[jc];
+    const zd zero = mk(0.0, 0.0);
+    zd srow[4], scol[CT];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int i = 16 * rt + lk + 4 * v;
+        srow[v] = csel(i < L, sinv2[min(i, L - 1)], zero);
+    }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) scol[ct] = csel(16 * ct + li < L, sinv2[min(16 * ct + li, L - 1)], zero);
+    // D_k: this lane holds at most one entry of the tridiagonal in its diagonal
+    // tile (column jd, row jd + od), of value kq is1 cd + (s1 terms) cs + cn / (s1 h^2);
+    // tiles next to the diagonal one hold one corner entry each, cn / (s1 h^2)
+    const int jd = 16 * rt + li, jc = min(jd, L - 1);
+    const int od = ((lk - li + 1) & 3) - 1;                 // -1, 0, 1 (2: none)
+    const int vd = (li + od - lk) >> 2;                     // its register, 0..3 if inside
+    const bool has = od < 2 && li + od >= 0 && li + od < 16 && jd < L && jd + od < L;
+    const bool ond = has && od == 0;
+    const zd cd_ = csel(ond, sinv[jc], zero);
+    const zd cs_ = csel(ond, -sinv2[jc], zero);
+    const zd cn_ = csel(ond, -(ssh[jc + 1] + ssh[jc]), csel(has, ssh[max(jc, min(jd + od, L))], zero));
+    const bool padd = od == 0 && li + od >= 0 && jd >= L;   // identity padding
+    // corner of tile rt - 1 (row 16 rt, column 16 rt - 1) and rt + 1
+    const bool clo = lk == 0 && li == 15 && rt > 0 && 16 * rt < L;
+    const bool chi = lk == 3 && li == 0 && 16 * rt + 16 < L;
+    const zd cnlo = csel(clo, ssh[min(16 * rt, L)], zero);
+    const zd cnhi = csel(chi, ssh[min(16 * rt + 16, L)], zero);
     const double* ksq_j = ksq + (long long)n * (d.lo + jc - 1);
-    // S_k^-1 column-major with leading dimension LR through a buffer resource:
-    // columns past L give an offset past the range (dropped writes)
+    // S_k^-1 column-major with leading dimension LR through a buffer resource,
+    // stored as its transpose (it is symmetric): 16 lanes write one line
     const __amdgpu_buffer_rsrc_t rf =
         __builtin_amdgcn_make_buffer_rsrc(fac + d.fac_off, 0, 0x7fffffff, BUF_DW3);
-    const unsigned foff = cj ? (unsigned)((j * LR + g * RPL) * sizeof(cplx<TS>)) : BUF_OOB;
+    unsigned foff[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int i = 16 * rt + lk + 4 * v;
+        foff[v] = live && i < L ? (unsigned)((i * LR + li) * sizeof(cplx<TS>)) : BUF_OOB;
+    }
     const unsigned fstep = (unsigned)(L * LR * sizeof(cplx<TS>));
     bool bad = false;
-    zd v[RPL];
+    f64x4 re[CT], im[CT];
 #pragma unroll
-    for (int q = 0; q < RPL; ++q) v[q] = mk(0.0, 0.0);
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) re[ct][v] = im[ct][v] = 0.0;
 
-    // the tables of block k (couplings s1 at k -+ 1/2, 1/(s1 h^2), 1/s1 and
-    // omega^2/c^2 on this thread's diagonal point), fetched one block ahead
+    // V <- D_k - c1 V c1 (c1 the couplings to the previous block), from the
+    // tables of block k; sm + sp: s1 at the half lines around it
+    auto form = [&](zd c1, zd ssum, zd is2, zd is, double kq) {
+        const zd addd = (kq * is) * cd_ + ssum * cs_ + is2 * cn_;
+        const zd alo = is2 * cnlo, ahi = is2 * cnhi;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            const zd cc = c1 * scol[ct];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                zd x = -((c1 * srow[v]) * mk(re[ct][v], im[ct][v]) * cc);
+                if (ct == rt) {
+                    x = x + csel(v == vd && has, addd, zero);
+                    if (v == vd && padd) x = mk(1.0, 0.0);
+                }
+                if (ct + 1 == rt && v == 0) x = x + alo;
+                if (ct == rt + 1 && v == 3) x = x + ahi;
+                re[ct][v] = x.x;
+                im[ct][v] = x.y;
+            }
+        }
+    };
+    int par = 0;
+    auto invert = [&]() {
+        for (int tb = 0; tb < CT; ++tb) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (8 * tb + q >= npair) break;
+                const int kk = 16 * tb + 2 * q;
+                const int vk = q >> 1;
+                zd* R0 = rowbuf + par * 2 * LR;
+                const zd* R1 = R0 + LR;
+                par ^= 1;
+                const bool mine = rt == tb && (lk >> 1) == (q & 1);   // lanes holding the pivot rows
+                if (mine)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) R0[(lk & 1) * LR + 16 * ct + li] = mk(re[ct][vk], im[ct][vk]);
+                if constexpr (NW == 1)
+                    wave_lds_fence();
+                else
+                    __syncthreads();
+                const zd a = R0[kk], b = R0[kk + 1], c = R1[kk], dd = R1[kk + 1];
+                zd r0[CT], r1[CT];
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    r0[ct] = R0[16 * ct + li];
+                    r1[ct] = R1[16 * ct + li];
+                }
+                // -A[i][kk], -A[i][kk+1] of row i = 16 rt + li, as the lane's K entry
+                const zd ci = R0[(lk >> 1) * LR + 16 * rt + li];
+                const double sg = 16 * rt + li < kk ? 1.0 : -1.0;
+                const bool odd = lk & 1;
+                const double are = sg * (odd ? -ci.y : ci.x);
+                const double aim = sg * (odd ? ci.x : ci.y);
+                // the 2 x 2 pivot block [a b; c d], eliminated in order
+                const double pa = abs2(a);
+                const zd i1 = cinv(a);
+                const zd m = c * i1;
+                const zd p2 = dd - m * b;
+                const double pb = abs2(p2);
+                const zd i2 = cinv(p2);
+                if (!(pa > 1e-300) || !(pb > 1e-300) || !isfinite(pa) || !isfinite(pb)) bad = true;
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    // the pivot columns take the columns of the inverse
+                    const bool e0 = ct == tb && li == 2 * q, e1 = ct == tb && li == 2 * q + 1;
+                    const zd x0 = csel(e0, mk(1.0, 0.0), csel(e1, zero, r0[ct]));
+                    const zd x1 = csel(e1, mk(1.0, 0.0), csel(e0, zero, r1[ct]));
+                    const zd w1 = i2 * (x1 - m * x0);
+                    const zd w0 = i1 * (x0 - b * w1);
+                    if (ct == tb) {
+                        const bool ep = e0 || e1;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            re[ct][v] = ep ? 0.0 : re[ct][v];
+                            im[ct][v] = ep ? 0.0 : im[ct][v];
+                        }
+                    }
+                    const zd wk = csel(lk < 2, w0, w1);
+                    const double bk = odd ? wk.y : wk.x;
+                    re[ct] = D::mac(are, bk, re[ct]);
+                    im[ct] = D::mac(aim, bk, im[ct]);
+                    // the pivot rows
+                    const zd wr = csel(odd, w1, w0);
+                    re[ct][vk] = mine ? wr.x : re[ct][vk];
+                    im[ct][vk] = mine ? wr.y : im[ct][vk];
+                }
+            }
+        }
+    };
+    auto store = [&](int k, bool on) {
+        const unsigned base = (unsigned)(k - 1) * fstep;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const zd x = csel(16 * ct + li < L, mk(re[ct][v], im[ct][v]), zero);
+                buf_store(rf, on ? foff[v] + (unsigned)(16 * ct * sizeof(cplx<TS>)) : BUF_OOB, base, ccast<TS>(x));
+            }
+    };
+    // the tables of block k: couplings s1 at k -+ 1/2, 1/(s1 h^2), 1/s1 and
+    // omega^2/c^2 on this lane's column, fetched one block ahead
     struct Step {
         zd sh_m, sh_p, is2, is;
         double kq;
@@ -102,118 +266,118 @@ __device__ __forceinline__ void factor2d_body(const SubDesc& d, AxisTables ax,
         S.is = ax.inv_s[k - 1];
         S.kq = ksq_j[k - 1];
     };
+    // both halves take smax steps together (shared barriers): the shorter one
+    // starts late, on its first block, which it forms and inverts once unstored
+    const int p = mid_block(n);
+    const int smax = max(p - 1, n - p);
     Step cur, nxt;
-    fetch(cur, 1);
-    // nothing outstanding on entry: the waits in the loop count its own operations
+    fetch(cur, H.blk(1));
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    int pc = 0;   // pivots so far: their parity picks the LDS buffer
-    for (int k = 1; k <= n; ++k) {
-        fetch(nxt, min(k + 1, n));
-        // S_k = D_k - E_{k-1} S_{k-1}^-1 E_{k-1} over S_{k-1}^-1; identity padding
-        const zd ej = cur.sh_m * sj;
-        const zd diag = (cur.kq * cur.is) * sinvj - (cur.sh_p + cur.sh_m) * sj -
-                        (c_hi + c_lo) * cur.is2;
-        const zd off_lo = c_lo * cur.is2;   // row j - 1
-        const zd off_hi = c_hi * cur.is2;   // row j + 1
-#pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-            const int i = g * RPL + q;
-            zd val = csel(k > 1, -((cur.sh_m * srow[i]) * v[q] * ej), mk(0.0, 0.0));
-            const zd add = csel(i == j, diag,
-                                csel(i == j - 1, off_lo, csel(i == j + 1, off_hi, mk(0.0, 0.0))));
-            val = val + add;
-            const bool inside = i < L && cj;
-            v[q] = csel(inside, val, mk(i == j ? 1.0 : 0.0, 0.0));
-        }
-        // in-place inverse; the pivots run in groups of RPL with the pivot's
-        // register index fixed at compile time
-        for (int kb = 0; kb < L; kb += RPL) {
-            const int gb = kb / RPL;
-#pragma unroll
-            for (int pq = 0; pq < RPL; ++pq) {
-                const int kk = kb + pq;
-                if (kk >= L) continue;
-                const int b = pc & 1;
-                ++pc;
-                const bool jp = j == kk, gp = g == gb;
-                if (gp) rowbuf[b][j] = v[pq];
-                if (jp)
-#pragma unroll
-                    for (int q = 0; q < RPL; ++q) colbuf[b][g * RPL + q] = v[q];
-                // the pivot's owner checks it and publishes 1 / p
-                if (jp && gp) {
-                    const zd p = v[pq];
-                    const double pa = abs2(p);
-                    if (!(pa > 1e-300) || !isfinite(pa)) bad = true;
-                    rowbuf[b][ML] = cinv(p);
-                }
-                __syncthreads();
-                const zd pinv = rowbuf[b][ML];
-                // A[kk][j] / p; the pivot column is scaled by 1 / p instead
-                const zd rp = csel(jp, pinv, rowbuf[b][j] * pinv);
-                // A[i][j] - A[i][kk] A[kk][j] / p off the pivot row and column,
-                // -A[i][kk] / p on the pivot column, A[kk][j] / p on the pivot
-                // row and 1 / p at the pivot
-#pragma unroll
-                for (int q = 0; q < RPL; ++q) {
-                    const zd ci = colbuf[b][g * RPL + q];     // A[i][kk]
-                    zd x = csel(jp, mk(0.0, 0.0), v[q]) - ci * rp;
-                    if (q == pq) x = csel(gp, rp, x);
-                    v[q] = x;
-                }
-            }
-        }
-        // store S_k^-1 (rows past L zero)
-#pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-            const int i = g * RPL + q;
-            buf_store(rf, foff + (unsigned)(k - 1) * fstep + (unsigned)(q * sizeof(cplx<TS>)),
-                      ccast<TS>(csel(i < L, v[q], mk(0.0, 0.0))));
-        }
+    for (int it = 1; it <= smax; ++it) {
+        const int s = it - (smax - H.np);
+        fetch(nxt, H.blk(min(max(s, 0), H.np) + 1));
+        // s <= 1: no previous block (the state is finite, the coupling zero)
+        const zd c1 = csel(s > 1, H.dir ? cur.sh_p : cur.sh_m, zero);
+        form(c1, cur.sh_m + cur.sh_p, cur.is2, cur.is, cur.kq);
+        invert();
+        store(H.blk(max(s, 1)), s >= 1);
         cur = nxt;
     }
-    if (bad) *flag = 1;
+    // the middle block: half 1 hands R_{p+1}^-1 over in the accumulator layout
+    if (H.dir == 1)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) xch[((rt * CT + ct) * 4 + v) * 64 + l] = mk(re[ct][v], im[ct][v]);
+    __syncthreads();
+    const bool bad_halves = bad;
+    if (H.dir == 0) {
+        fetch(cur, p);
+        f64x4 xr[CT], xi[CT];
+        const zd cp = csel(n > p, cur.sh_p, zero);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const zd x = xch[((rt * CT + ct) * 4 + v) * 64 + l];
+                const zd t = (cp * srow[v]) * x * (cp * scol[ct]);
+                xr[ct][v] = t.x;
+                xi[ct][v] = t.y;
+            }
+        form(csel(p > 1, cur.sh_m, zero), cur.sh_m + cur.sh_p, cur.is2, cur.is, cur.kq);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                re[ct][v] -= xr[ct][v];
+                im[ct][v] -= xi[ct][v];
+            }
+    }
+    invert();
+    if (H.dir == 1) bad = bad_halves;
+    store(p, H.dir == 0);
+    if (bad && live) *flag = 1;
 }
 
-// ML: the largest LR of the launch (32, or 64 when a problem has more than 32
-// lines: that body's registers would halve the occupancy of the others)
-template <typename TS, int ML>
-__global__ __launch_bounds__(FB) void factor2d_kernel(const SubDesc* __restrict__ desc,
-                                                     AxisTables ax,
-                                                     const zd* __restrict__ subtab,
-                                                     const double* __restrict__ ksq, int n,
-                                                     cplx<TS>* __restrict__ fac,
-                                                     int* __restrict__ flag) {
-    static_assert(ML == 32 || ML == MAXL, "row counts");
-    __shared__ zd rowbuf[2][ML + 1];   // pivot row; [ML]: the pivot's reciprocal
-    __shared__ zd colbuf[2][ML];
-    __shared__ zd srow[ML];
-    const SubDesc d = desc[blockIdx.x];
-    if (d.LR == 16)
-        factor2d_body<TS, 16, ML>(d, ax, subtab, ksq, n, fac, flag, rowbuf, colbuf, srow);
-    else if (ML == 32 || d.LR == 32)
-        factor2d_body<TS, 32, ML>(d, ax, subtab, ksq, n, fac, flag, rowbuf, colbuf, srow);
+// Workgroups of 2 LX / 16 wavefronts, LX the larger row count of the plan: a
+// problem of LR rows takes 2 LR / 16 of them (one strip per wavefront and
+// half), so LX / LR problems share a workgroup.  The M problems come first,
+// then the R and L problems.
+struct FactorClass {
+    int first, count, LR, npair;   // problems desc[first ..), pivot pairs (the widest problem's)
+    int blocks;
+};
+template <typename TS, int LX>
+__global__ __launch_bounds__(8 * LX) void factor2d_kernel(const SubDesc* __restrict__ desc,
+                                                         FactorClass cm, FactorClass cr, AxisTables ax,
+                                                         const zd* __restrict__ subtab,
+                                                         const double* __restrict__ ksq, int n,
+                                                         cplx<TS>* __restrict__ fac,
+                                                         int* __restrict__ flag) {
+    __shared__ zd rows[8 * LX];      // pivot rows [problem][half][parity][2][LR]
+    __shared__ zd xch[LX * LX];      // R_{p+1}^-1 of every problem
+    const bool ism = (int)blockIdx.x < cm.blocks;
+    const FactorClass c = ism ? cm : cr;
+    const int g = ism ? blockIdx.x : blockIdx.x - cm.blocks;
+    const int w = threadIdx.x >> 6;
+    const int per = LX / c.LR, wpp = c.LR / 8;
+    const int slot = w / wpp;
+    const int idx = g * per + slot;
+    const bool live = idx < c.count;
+    const SubDesc d = desc[c.first + min(idx, c.count - 1)];
+    zd* rb = rows + slot * 8 * c.LR;
+    zd* xc = xch + slot * c.LR * c.LR;
+    const int wl = w % wpp;
+    if (LX == 16 || c.LR == 16)
+        factor2d_body<TS, 16>(d, live, c.npair, wl, ax, subtab, ksq, n, fac, flag, rb, xc);
+    else if (LX == 32 || c.LR == 32)
+        factor2d_body<TS, (LX < 32 ? 16 : 32)>(d, live, c.npair, wl, ax, subtab, ksq, n, fac, flag, rb, xc);
     else
-        factor2d_body<TS, ML, ML>(d, ax, subtab, ksq, n, fac, flag, rowbuf, colbuf, srow);
+        factor2d_body<TS, LX>(d, live, c.npair, wl, ax, subtab, ksq, n, fac, flag, rb, xc);
 }
 
 // ----------------------------------------------------------------------------
 // The diagonal blocks G_k of H^-1 of a map problem (R_p or L_p, 1 < p < m),
-// from the stored S_k^-1: G_n = S_n^-1 and, towards block 1,
-//   G_k = S_k^-1 + S_k^-1 E_k G_{k+1} E_k S_k^-1,
-// E_k the diagonal coupling of blocks k and k+1 (H, S_k^-1 and G_k are complex
+// from the stored inverses: G = M_p^-1 at the middle block and, outwards in
+// each half (S_k^-1 standing for R_k^-1 in the second, s counted from its end),
+//   G_s = S_s^-1 + S_s^-1 E_s G_{s+1} E_s S_s^-1,
+// E_s the diagonal coupling of blocks s and s + 1 (H, S_k^-1 and G_k are complex
 // symmetric).  The boundary maps then start from two columns of every G_k
-// (IN_TWIST solves).  One 256-thread workgroup per problem, k from n down to 1;
-// thread (j, g) holds rows g RPL .. of column j of G in double, the two
-// products of a step go through LDS.  Columns grow and jout of each G_k are
-// stored (type TS) at the problem's g_off in the map buffer, [k][2][LR].
+// (IN_TWIST solves).  One 256-thread workgroup per problem and half; thread
+// (j, g) holds rows g RPL .. of column j of G in double, the two products of a
+// step go through LDS.  Columns grow and jout of each G_k are stored (type TS)
+// at the problem's g_off in the map buffer, [k][2][LR].  Bound by the latency
+// of the step chain.
 // ----------------------------------------------------------------------------
+constexpr int FB = 256;   // threads per workgroup
+
 template <typename TS, int LR>
 __device__ __forceinline__ void rgf2d_body(const SubDesc& d, AxisTables ax, const zd* __restrict__ subtab,
-                                           int n, const cplx<TS>* __restrict__ fac, cplx<TS>* __restrict__ tbuf,
-                                           zd (*A)[LR + 1], zd (*Bm)[LR + 1]) {
+                                           int n, int dir, const cplx<TS>* __restrict__ fac,
+                                           cplx<TS>* __restrict__ tbuf, zd (*A)[LR + 1], zd (*Bm)[LR + 1]) {
     constexpr int G = FB / LR, RPL = LR / G;
+    const Half H(n, dir);
     const int L = d.L;
     const int t = threadIdx.x, j = t % LR, g = t / LR;
     const zd* sinv2 = subtab + d.tab_off + L + 1;        // 1/(s h^2) on lines lo..hi
@@ -229,7 +393,8 @@ __device__ __forceinline__ void rgf2d_body(const SubDesc& d, AxisTables ax, cons
     const cplx<TS>* F = fac + d.fac_off;
     cplx<TS>* Gout = tbuf + d.g_off;
     zd Gv[RPL], sv[RPL];
-    for (int k = n; k >= 1; --k) {
+    for (int s = H.np + 1; s >= 1; --s) {
+        const int k = H.blk(s);
         // S_k^-1 (block k - 1, column-major, rows past L zero): column j
 #pragma unroll
         for (int q = 0; q < RPL; ++q) {
@@ -237,12 +402,12 @@ __device__ __forceinline__ void rgf2d_body(const SubDesc& d, AxisTables ax, cons
             sv[q] = (j < L && r < L) ? ccast<double>(F[(long long)(k - 1) * L * LR + (long long)j * LR + r])
                                      : mk(0.0, 0.0);
         }
-        if (k == n) {
+        if (s == H.np + 1) {
 #pragma unroll
             for (int q = 0; q < RPL; ++q) Gv[q] = sv[q];
         } else {
-            const zd sh = ax.sh[k];                            // s at the half line k + 1/2
-            // A = G_{k+1} E_k, Bm = S_k^-1
+            const zd sh = ax.sh[H.half_line(s)];               // s1 between blocks s and s + 1
+            // A = G_{s+1} E_s, Bm = S_s^-1
 #pragma unroll
             for (int q = 0; q < RPL; ++q) {
                 const int r = g * RPL + q;
@@ -250,7 +415,7 @@ __device__ __forceinline__ void rgf2d_body(const SubDesc& d, AxisTables ax, cons
                 Bm[r][j] = sv[q];
             }
             __syncthreads();
-            // X = E_k (A Bm) = E_k G_{k+1} E_k S_k^-1
+            // X = E_s (A Bm) = E_s G_{s+1} E_s S_s^-1
             zd xv[RPL];
 #pragma unroll
             for (int q = 0; q < RPL; ++q) {
@@ -263,7 +428,7 @@ __device__ __forceinline__ void rgf2d_body(const SubDesc& d, AxisTables ax, cons
 #pragma unroll
             for (int q = 0; q < RPL; ++q) A[g * RPL + q][j] = xv[q];
             __syncthreads();
-            // G_k = S_k^-1 + S_k^-1 X, with (S_k^-1)[r][l] = Bm[l][r] (symmetric)
+            // G_s = S_s^-1 + S_s^-1 X, with (S_s^-1)[r][l] = Bm[l][r] (symmetric)
 #pragma unroll
             for (int q = 0; q < RPL; ++q) {
                 const int r = g * RPL + q;
@@ -273,6 +438,7 @@ __device__ __forceinline__ void rgf2d_body(const SubDesc& d, AxisTables ax, cons
             }
             __syncthreads();   // A and Bm are written again at the next step
         }
+        if (s == H.np + 1 && dir) continue;   // the middle block is written by half 0
 #pragma unroll
         for (int q = 0; q < RPL; ++q) {
             const int r = g * RPL + q;
@@ -291,19 +457,31 @@ __global__ __launch_bounds__(FB) void rgf2d_kernel(const SubDesc* __restrict__ d
                                                   cplx<TS>* __restrict__ tbuf) {
     __shared__ zd A[LR][LR + 1];
     __shared__ zd Bm[LR][LR + 1];
-    // blockIdx.y picks one of two job lists (the map problems of the two sweeps)
+    // blockIdx.y picks one of two job lists (the map problems of the two sweeps), z the half
     const SubDesc d = desc[(blockIdx.y ? jobs1 : jobs0)[blockIdx.x]];
-    rgf2d_body<TS, LR>(d, ax, subtab, n, fac, tbuf, A, Bm);
+    rgf2d_body<TS, LR>(d, ax, subtab, n, blockIdx.z, fac, tbuf, A, Bm);
 }
 
 // ----------------------------------------------------------------------------
-// batched solves on the matrix cores: one 256-thread workgroup per (auxiliary
-// problem, chunk of 1024 / LR right-hand sides).  A block step is the product
-// of S_k^-1 (L x L, staged in an LDS ring; the next block's load overlaps the
-// step) with the chunk's step vectors (LDS), as four 16 x 16 tiles, one per
-// wavefront.  Each lane owns the four (row, rhs) entries of its tile: it forms
-// their next step inputs in registers and writes them back to LDS, so a step
-// needs one barrier.  Forward results go to scratch for the backward pass.
+// batched solves on the matrix cores: one workgroup of LR / 16 wavefronts per
+// (auxiliary problem, chunk of 16 right-hand sides, half), one 16-row tile of
+// the step vectors per wavefront.  The forward kernel runs both halves towards
+// the middle block and keeps its results in scratch; the backward kernel
+// solves the middle block (each half for itself) and runs outwards.  A block
+// step is the product of S_k^-1 with the chunk's step vectors.  The wavefront's
+// rows of S_k^-1 come straight from memory into the matrix-core operand layout,
+// NSLOT steps ahead into fixed register slots (the step loops are unrolled by
+// NSLOT); columns past L lie past the buffer resource's range and read zero.
+// With 16 rows a wavefront holds the whole step vector: the columns of the
+// product run in the order in which the result tile holds its rows, so a
+// step's result is the next step's operand without leaving its lanes (no LDS,
+// no barrier).  With more rows the step vectors pass through LDS, one barrier
+// per step.
+// What bounds it: few right-hand sides, the latency of a step (the matrix
+// instructions of one tile in sequence, the exchange, the scaling); many, the
+// traffic of the forward results and the matrix cores.  Two halves at once and
+// 16 right-hand sides per workgroup give twice the chains of half the length
+// and no work for absent right-hand sides beyond 16.
 // ----------------------------------------------------------------------------
 // complex 16 x 16 FP32 accumulator of the three-product (Gauss) form:
 // p1 = (a_r + a_i) b_r, p2 = a_r (b_i - b_r), p3 = a_i (b_r + b_i);
@@ -324,142 +502,117 @@ __device__ __forceinline__ void kmac3(KTile3& c, zf a, zf b) {
 struct SolveArgs {
     const SubDesc* desc;
     const int* jobs;
-    int njobs;
+    int njobs, njobs0, jobs1;   // jobs[0 .. njobs0) and jobs[jobs1 .. ): njobs in all
     const int* act;      // right-hand-side ids (NULL: 0..nact-1)
     int nact;
-    int in_mode, out_mode;
-    int out_mode_L;      // L problems of a launch with both kinds: their own output
-    zd* out_L;
+    zd* out_L;           // L problems of a launch with both kinds: their own output
     const void* fac;
     AxisTables ax;
     const zd* subtab;
     const zd* r;         // IN_GRID: grid vectors
     const zd* W;         // IN_BOUNDARY: boundary data per (problem, rhs)
     int w_rhs;           // right-hand-side stride of W (in n-vectors)
-    zd* out;             // OUT_GRID_STORE: grid vectors
-    void* Tout;          // OUT_LINE: boundary-to-boundary maps
-    void* y;
-    long long y_per_wave;   // scratch entries per workgroup
-    zd* sink;               // discard buffer: four entries per thread
-    int buf_ok;             // output byte offsets fit the 31-bit buffer range
-    int twist_kind;         // IN_TWIST: 0 map columns on and above the diagonal, 1 below
+    zd* out;             // grid vectors
+    void* Tout;          // IN_TWIST: boundary-to-boundary maps
+    void* y;             // forward results [problem][chunk][block][LR][16]
+    zd* sink;            // discard buffer: four entries per thread
+    int buf_ok;          // output byte offsets fit the 31-bit buffer range
+    int twist_kind;      // IN_TWIST: 0 both triangles of each half, 2 the propagators
+    int srow;            // staged output lines per workgroup
     int n;
     long long N;
 };
 
-constexpr int SB = 256;        // threads per solve workgroup: four wavefronts, one tile each
+constexpr int RC = 16;         // right-hand sides per workgroup: one matrix-core tile
+constexpr int KO = 8;          // output steps per flush: whole 128-byte lines of complex128
+constexpr int STG_MAX = 8;     // most staged output lines
 
-// SPL (ASP_PREC_BF16X3, T = float): every block product as real-split bf16
-// products with FP32 accumulation (cmac_split), 16x16x32 steps over the block
-template <typename T, int LR, int INM, bool SPL = false>
-__global__ __launch_bounds__(SB) void solve2d_kernel(SolveArgs a) {
-    static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
-    static_assert(INM == IN_GRID || INM == IN_BOUNDARY || INM == IN_TWIST, "input mode");
-    constexpr bool NOSTAGE = INM == IN_TWIST;   // map outputs: no staging
-    constexpr int SRB = 1024 / LR;          // right-hand sides per workgroup
-    constexpr int NCT = SRB / 16;           // right-hand-side tiles
-    static_assert((LR / 16) * NCT == 4, "four 16 x 16 tiles, one per wavefront");
-    static_assert(SB * 4 <= SINK_ELEMS, "four discard entries per thread");
-    constexpr int FMAX = max_lines_2d<T>(LR) * LR;   // largest block
-    constexpr int FPT = FMAX / SB;
-    constexpr int TBS = SRB + 1;            // padded row stride of the step vectors
-    __shared__ cplx<T> Fs[2][FMAX];
-    __shared__ cplx<T> tb[2][LR][TBS];      // step vectors [row][rhs]
-    // grid outputs of the first SROW lines of X for KO steps, by group parity
-    constexpr int KO = sizeof(T) == 4 ? 8 : 2;
-    constexpr int SROW = 4;
-    __shared__ cplx<T> stg[NOSTAGE ? 1 : 2 * KO * SROW * SRB];
-
-    const int nchunk = (a.nact + SRB - 1) / SRB;
-    const int B = a.njobs * nchunk;
-    int w, jl, ch;
-    if constexpr (INM == IN_TWIST) {
-        // chunk ch of a map problem is a chain of min((ch + 1) SRB, n) steps:
-        // the longest chains of every problem first, in dispatch order (and so
-        // spread over the XCDs), so that no long chain starts near the end
-        w = (int)blockIdx.x;
-        if (w >= B) return;
-        ch = nchunk - 1 - w / a.njobs;
-        jl = w % a.njobs;
+// 8 or 16 bytes through a buffer resource, zero past its range
+template <typename T>
+__device__ __forceinline__ cplx<T> buf_load(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
+    cplx<T> v;
+    if constexpr (sizeof(T) == 4) {
+        const u32x2 d = __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
+        __builtin_memcpy(&v, &d, sizeof(v));
     } else {
-        // XCD-aware order: the chunks of one problem are consecutive work items
-        const int per = (B + 7) / 8;
-        w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-        if (w >= B) return;
-        jl = w / nchunk;
-        ch = w % nchunk;
+        const u32x4 d = __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0);
+        __builtin_memcpy(&v, &d, sizeof(v));
     }
-    const SubDesc d = a.desc[a.jobs[jl]];
-    const int L = d.L, n = a.n;
-    const long long N = a.N;
-    const int tid = threadIdx.x;
-    const int l = tid & 63, wv = tid >> 6;
-    const int li = l & 15, lk = l >> 4;
-    const int rt = wv / NCT, ct = wv % NCT;   // this wavefront's tile
-    const int rloc = 16 * ct + li;            // this lane's right-hand side in the chunk
-    const cplx<T>* F = reinterpret_cast<const cplx<T>*>(a.fac) + d.fac_off;
-    const int FS = L * LR;                  // entries of one block
-    const zd* tab = a.subtab + d.tab_off;
-    cplx<T>* Y = reinterpret_cast<cplx<T>*>(a.y) + (long long)w * a.y_per_wave;
+    return v;
+}
 
-    const int slot = ch * SRB + rloc;
-    const bool valid = slot < a.nact;
-    const int rid = valid ? (a.act ? a.act[slot] : slot) : 0;
-    const int grow = (d.kind == ASP_SUB_R) ? 0 : L - 1;          // row carrying boundary data
-    const zd coupl = (d.kind == ASP_SUB_R) ? tab[0] : tab[L];    // s at lo-1/2 or hi+1/2
-    int row[4], lcl[4];
-    bool rowv[4], inX[4];
-    cplx<T> sinv2[4];
+// one wavefront's 16-row tile of a block step
+template <typename T, int LR, bool SPL>
+struct BlockTile {
+    static constexpr int NW = LR / 16;
+    static constexpr int KS = (sizeof(T) == 8 && LR == 64) ? 12 : LR / 4;   // operand entries per lane
+    static constexpr int TBS = RC + 1;   // padded row stride of the step vectors in LDS
+    int l, li, lk, rt, L;
+    unsigned aoff[KS];           // byte offsets of this lane's operand entries, past the range if unused
+    __amdgpu_buffer_rsrc_t rf;
+    unsigned fstep;
+
+    // the column of S^-1 that operand entry j of this lane holds
+    __device__ __forceinline__ int col(int j) const {
+        if constexpr (SPL) return NW == 1 ? 4 * lk + j : 32 * (j >> 3) + 8 * lk + (j & 7);
+        if constexpr (NW == 1) return Mfma<T>::row(l, j);
+        return 4 * j + lk;
+    }
+    __device__ __forceinline__ void init(const SubDesc& d, const cplx<T>* F) {
+        l = threadIdx.x & 63;
+        li = l & 15;
+        lk = l >> 4;
+        rt = threadIdx.x >> 6;
+        L = d.L;
+        rf = __builtin_amdgcn_make_buffer_rsrc(const_cast<cplx<T>*>(F), 0, 0x7fffffff, BUF_DW3);
+        fstep = (unsigned)(L * LR * sizeof(cplx<T>));
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        row[v] = 16 * rt + Mfma<T>::row(l, v);
-        rowv[v] = row[v] < L;
-        const int line = d.lo + row[v];
-        lcl[v] = min(line, n);
-        inX[v] = rowv[v] && line >= d.xs && line <= d.xe;
-        sinv2[v] = rowv[v] ? ccast<T>(tab[L + 1 + row[v]]) : mk<T>(0, 0);
+        for (int j = 0; j < KS; ++j) {
+            const int c = col(j);
+            aoff[j] = c < L ? (unsigned)((c * LR + 16 * rt + li) * sizeof(cplx<T>)) : BUF_OOB;
+        }
     }
-
-    // rows and columns past L stay zero in both rings
-    for (int e = tid; e < 2 * LR * TBS; e += SB) (&tb[0][0][0])[e] = mk<T>(0, 0);
-    for (int e = tid; e < 2 * FMAX; e += SB) (&Fs[0][0])[e] = mk<T>(0, 0);
-    __syncthreads();
-    const int LP = (L + 3) & ~3;
-    // loads below are unconditional (from clamped, always valid addresses) and
-    // their values selected where used: a load under a divergent branch makes
-    // the compiler wait for every earlier load at the branch join
-    // this wavefront's tile of S^-1 (ring slot fb) times the step vectors tb[buf]
-    auto product = [&](int fb, int buf) {
+    __device__ __forceinline__ void load(cplx<T> (&a)[KS], int blk) const {
+#pragma unroll
+        for (int j = 0; j < KS; ++j) a[j] = buf_load<T>(rf, aoff[j], (unsigned)(blk - 1) * fstep);
+    }
+    // S^-1 (operand a) times the step vectors: the lane's own values u (one
+    // tile) or the LDS copy tb
+    __device__ __forceinline__ CTile<T> product(const cplx<T> (&a)[KS], const cplx<T> (&u)[4],
+                                                const cplx<T> (*tb)[TBS]) const {
         CTile<T> acc;
-        if constexpr (SPL) {
-            // lane l takes k = kh + 8 (l / 16) .. + 7 of each 32-wide k range;
-            // columns past L are zero in the factor ring, rows past LR of the
-            // step vectors are masked
-            acc.zero();
-            const int lq = l >> 4;
+        cplx<T> b[KS];
 #pragma unroll
-            for (int kh = 0; kh < FMAX / LR; kh += 32) {
+        for (int j = 0; j < KS; ++j) {
+            if constexpr (NW == 1)
+                b[j] = u[j];
+            else
+                b[j] = tb[col(j)][li];
+        }
+        const int ksn = (L + 3) >> 2;   // 4-column steps in use
+        if constexpr (SPL) {
+            acc.zero();
+#pragma unroll
+            for (int h = 0; h < (KS + 7) / 8; ++h) {
                 float ar[8], ai[8], br[8], bi[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const int c = kh + 8 * lq + j;
-                    const cplx<T> av = Fs[fb][c * LR + 16 * rt + li];
-                    const cplx<T> bv = tb[buf][min(c, LR - 1)][rloc];
-                    const bool in = c < LR;
+                    const bool in = 8 * h + j < KS;
+                    const cplx<T> av = in ? a[(8 * h + j) % KS] : mk<T>(T(0), T(0));
+                    const cplx<T> bv = in ? b[(8 * h + j) % KS] : mk<T>(T(0), T(0));
                     ar[j] = av.x;
                     ai[j] = av.y;
-                    br[j] = in ? bv.x : 0.f;
-                    bi[j] = in ? bv.y : 0.f;
+                    br[j] = bv.x;
+                    bi[j] = bv.y;
                 }
                 cmac_split(acc, ar, ai, br, bi);
             }
         } else if constexpr (std::is_same<T, float>::value) {
             KTile3 k3;
             k3.zero();
-            for (int c0 = 0; c0 < LP; c0 += 4) {
-                const int c = c0 + lk;
-                kmac3(k3, Fs[fb][c * LR + 16 * rt + li], tb[buf][c][rloc]);
-            }
+#pragma unroll
+            for (int j = 0; j < KS; ++j)
+                if (NW == 1 || j <= KS / 2 || j < ksn) kmac3(k3, a[j], b[j]);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 acc.re[v] = k3.p1[v] - k3.p3[v];
@@ -467,350 +620,532 @@ __global__ __launch_bounds__(SB) void solve2d_kernel(SolveArgs a) {
             }
         } else {
             acc.zero();
-            for (int c0 = 0; c0 < LP; c0 += 4) {
-                const int c = c0 + lk;
-                cmac(acc, Fs[fb][c * LR + 16 * rt + li], tb[buf][c][rloc]);
-            }
+#pragma unroll
+            for (int j = 0; j < KS; ++j)
+                if (NW == 1 || j <= KS / 2 || j < ksn) cmac(acc, a[j], b[j]);
         }
         return acc;
-    };
+    }
+};
 
-    // Every memory operation of the step loops is issued by every lane, from a
-    // valid address (loads clamp their index; a store a lane does not keep
-    // goes to the discard buffer), and the loops have no branch inside: the
-    // wait for a load issued two steps ahead then counts exactly the
-    // operations issued after it.  (The vector memory counter also counts
-    // stores, and a branch makes the compiler assume the shorter path.)
-    zd* const sink = a.sink + tid * 4;
-    cplx<T>* const sinkT = reinterpret_cast<cplx<T>*>(sink);
+// the work item of a workgroup: the chunks of one (problem, half) are
+// consecutive items of one XCD (they share its factor in the L2 cache)
+struct SolveItem {
+    int jl, ch, dir;
+    bool ok;
+    __device__ __forceinline__ SolveItem(int njobs, int nchunk) {
+        const int B = njobs * nchunk * 2;
+        const int per = (B + 7) / 8;
+        const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+        ok = w < B && (int)(blockIdx.x >> 3) < per;
+        ch = w % nchunk;
+        dir = (w / nchunk) & 1;
+        jl = w / (2 * nchunk);
+    }
+};
 
-    // step data of this lane's rows (complex128): grid data (IN_GRID) or the
-    // boundary data of its right-hand side (IN_BOUNDARY)
-    // Rows whose data the step ignores read a fixed table entry instead (stride
-    // 0), so that they cost no memory traffic.
-    const zd* inp[4];
-    int ink[4];
-    const long long bbase = ((long long)d.wrow * a.w_rhs + rid) * n;
+template <typename T>
+constexpr int nslot() { return sizeof(T) == 4 ? 3 : 2; }
+
+// forward pass of one half: y_s = S^-1 t_s, t_s = g_s - E y_{s-1}.  Every
+// memory operation of the step loop is issued by every lane, from a valid
+// address or one past the resource's range (no traffic), and the loop has no
+// branch around one: the wait for a load issued some steps ahead then counts
+// exactly the operations issued after it.
+template <typename T, int LR, int INM, bool SPL>
+__global__ __launch_bounds__(4 * LR) void solve2d_fwd_kernel(SolveArgs a) {
+    static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
+    using Tile = BlockTile<T, LR, SPL>;
+    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T>();
+    __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
+    const int nchunk = (a.nact + RC - 1) / RC;
+    const SolveItem it(a.njobs, nchunk);
+    if (!it.ok) return;
+    const SubDesc d = a.desc[a.jobs[it.jl]];
+    const int n = a.n, L = d.L;
+    const Half H(n, it.dir);
+    if (H.np == 0) return;
+    Tile M;
+    M.init(d, reinterpret_cast<const cplx<T>*>(a.fac) + d.fac_off);
+    const int li = M.li;
+    const zd* tab = a.subtab + d.tab_off;
+    const int slot = it.ch * RC + li;
+    const bool valid = slot < a.nact;
+    const int rid = valid ? (a.act ? a.act[slot] : slot) : 0;
+    const int grow = (d.kind == ASP_SUB_R) ? 0 : L - 1;          // row carrying boundary data
+    const zd coupl = (d.kind == ASP_SUB_R) ? tab[0] : tab[L];    // s at lo-1/2 or hi+1/2
+    // forward results through a buffer resource: rows past L are dropped
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<cplx<T>*>(a.y) + ((long long)it.jl * nchunk + it.ch) * n * LR * RC, 0, 0x7fffffff,
+        BUF_DW3);
+    constexpr unsigned ystep = LR * RC * sizeof(cplx<T>);
+    unsigned yoff[4];
+    cplx<T> sinv2[4];
+    // step data: grid data of the rows of X (IN_GRID), or the boundary data on
+    // the carrying row (IN_BOUNDARY, one entry per lane at most); other lanes
+    // read a fixed table entry
+    constexpr int NG = INM == IN_GRID ? 4 : 1;
+    const zd* inp[NG];
+    int ink[NG];
+    bool use[4];
+    int vrow = -1;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const bool used = (INM == IN_GRID) ? inX[v]
-                          : (INM == IN_BOUNDARY) ? (rowv[v] && row[v] == grow)
-                                                       : false;
-        inp[v] = !used                      ? a.subtab
-                 : (INM == IN_GRID) ? a.r + (long long)rid * N + (long long)n * (lcl[v] - 1)
-                                          : a.W + bbase;
-        ink[v] = used ? 1 : 0;
+        const int row = 16 * M.rt + Mfma<T>::row(M.l, v);
+        const int line = d.lo + row;
+        const bool rowv = row < L;
+        yoff[v] = rowv ? (unsigned)((row * RC + li) * sizeof(cplx<T>)) : BUF_OOB;
+        sinv2[v] = rowv ? ccast<T>(tab[L + 1 + row]) : mk<T>(0, 0);
+        if (INM == IN_GRID) {
+            use[v] = rowv && line >= d.xs && line <= d.xe;
+            inp[v % NG] = use[v] ? a.r + (long long)rid * a.N + (long long)n * (line - 1) : a.subtab;
+            ink[v % NG] = use[v] ? 1 : 0;
+        } else {
+            use[v] = rowv && row == grow;
+            if (use[v]) vrow = v;
+        }
     }
-    auto load_in = [&](int k, zd (&g)[4]) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) g[v] = inp[v][(long long)(k - 1) * ink[v]];
+    if (INM != IN_GRID) {
+        inp[0] = vrow >= 0 ? a.W + ((long long)d.wrow * a.w_rhs + rid) * n : a.subtab;
+        ink[0] = vrow >= 0 ? 1 : 0;
+    }
+    struct Slot {
+        cplx<T> f[KS];   // operand of step s
+        zd g[NG];        // data of step s + 1
+        zd sh, ism;      // s1 between blocks s and s + 1; 1 / (s1 h^2) at block s + 1
     };
-    // t_k = g_k - E_{k-1} y_{k-1} for this lane's entries into tb[k & 1]
-    // (shm, ism: s at line k - 1/2 and 1 / s^2 at line k - 1 of axis 1).  The
-    // data term is g_k (grid rows of X), g_k times the Dirichlet coupling
-    // (boundary data on the carrying row), selected per lane; each input mode
-    // forms only its own term (a select where the mode needs no product).
-    bool carry[4];
+    // data of block s + 1 (the middle block past the last step: unused)
+    auto fetch = [&](Slot& S, int s) {
+        const int sc = min(s, H.np);
+        M.load(S.f, H.blk(sc));
+        const int k = H.blk(sc + 1);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) carry[v] = rowv[v] && row[v] == grow;
-    auto put_input = [&](int k, const zd (&g)[4], const cplx<T> (&y)[4], zd shm, zd ism) {
-        const cplx<T> shc = ccast<T>(shm);
-        zd cin = mk(0.0, 0.0);
-        if constexpr (INM != IN_GRID) cin = -(coupl * ism);
+        for (int e = 0; e < NG; ++e) S.g[e] = inp[e][(long long)(k - 1) * ink[e]];
+        S.sh = a.ax.sh[H.half_line(sc)];
+        if (INM != IN_GRID) S.ism = a.ax.inv_sh2[k - 1];
+    };
+    cplx<T> u[4];
+    auto input = [&](const zd (&g)[NG], zd ism, cplx<T> shc, const cplx<T> (&y)[4], int buf) {
+        cplx<T> gb;
+        if constexpr (INM != IN_GRID) gb = ccast<T>(g[0] * -(coupl * ism));
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            zd dv;
+            cplx<T> t;
             if constexpr (INM == IN_GRID)
-                dv = csel(inX[v], g[v], mk(0.0, 0.0));
+                t = csel(use[v], ccast<T>(g[v % NG]), mk<T>(T(0), T(0)));
             else
-                dv = csel(carry[v], g[v] * cin, mk(0.0, 0.0));
-            cplx<T> t = ccast<T>(dv);
-            t = t - (shc * sinv2[v]) * y[v];              // y = 0 at the first step
-            tb[k & 1][row[v]][rloc] = rowv[v] ? t : mk<T>(0, 0);
+                t = csel(use[v], gb, mk<T>(T(0), T(0)));
+            u[v] = t - (shc * sinv2[v]) * y[v];
+            if constexpr (NW > 1) tb[buf][16 * M.rt + Mfma<T>::row(M.l, v)][li] = u[v];
         }
     };
-
-    // The loads of a step are issued two steps ahead into one of two register
-    // slots; the step loops run in pairs so that the slots stay in fixed
-    // registers (a register copy would wait for its load).
-    auto fetch_to = [&](cplx<T> (&p)[FPT], int blk) {
-        const cplx<T>* Fk = F + (long long)blk * FS;
+    Slot sl[NS];
+    {
+        zd g0[NG];
+        const int k = H.blk(1);
 #pragma unroll
-        for (int u = 0; u < FPT; ++u) p[u] = Fk[min(tid + u * SB, FS - 1)];
-    };
-    auto stash_from = [&](const cplx<T> (&p)[FPT], int buf) {
+        for (int e = 0; e < NG; ++e) g0[e] = inp[e][(long long)(k - 1) * ink[e]];
+        const zd ism0 = a.ax.inv_sh2[k - 1];
 #pragma unroll
-        for (int u = 0; u < FPT; ++u) {
-            const int e = tid + u * SB;
-            Fs[buf][e] = (e < FS) ? p[u] : mk<T>(0, 0);
-        }
-    };
-    cplx<T> yk[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) yk[v] = mk<T>(0, 0);
-
-    // IN_TWIST has no forward sweep: the maps' solutions start from columns of
-    // the diagonal blocks of H^-1 and only propagate towards block 1
-    if constexpr (INM != IN_TWIST) {
-        // forward sweep: y_k = S_k^-1 t_k; block k-1 (S_k^-1) sits in ring slot
-        // k & 1.  Slot of step k: the input g_{k+1}, the couplings of lines k, k+1
-        // and block k, all used at the end of step k.  The last step stashes block
-        // n-2 (already in its ring slot) and forms an input nobody reads: the
-        // backward pass finds block n-2 where it expects it and overwrites tb.
-        struct FwdSlot {
-            cplx<T> pf[FPT];
-            zd g[4];
-            zd sh, ism;
-        };
-        auto prefetch_f = [&](FwdSlot& S, int k) {
-            load_in(min(k + 1, n), S.g);
-            fetch_to(S.pf, k <= n - 1 ? k : max(n - 2, 0));
-            const int kc = min(k, n - 1);
-            S.sh = a.ax.sh[kc];
-            S.ism = a.ax.inv_sh2[kc];
-        };
-        FwdSlot fsl[2];
-        {
-            zd g0[4];
-            load_in(1, g0);
-            fetch_to(fsl[0].pf, 0);
-            const zd sh0 = a.ax.sh[0], ism0 = a.ax.inv_sh2[0];
-            stash_from(fsl[0].pf, 1);
-            put_input(1, g0, yk, sh0, ism0);
-        }
-        prefetch_f(fsl[0], 1);
-        prefetch_f(fsl[1], 2);
-        // one full wait before the loop: with nothing outstanding on entry, the
-        // waits inside the loop count only the loop's own operations (otherwise the
-        // compiler merges in the prologue's shorter history and waits for all)
-        __builtin_amdgcn_s_waitcnt(0);
-        auto fwd_step = [&](int k, FwdSlot& S, auto pre) {
-            const int buf = k & 1;
-            __syncthreads();
-            const CTile<T> acc = product(buf, buf);
-    #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                yk[v] = mk<T>(acc.re[v], acc.im[v]);
-                Y[((long long)(k - 1) * LR + row[v]) * SRB + rloc] = yk[v];   // rows past L: zero
-            }
-            stash_from(S.pf, (k + 1) & 1);                               // block k
-            put_input(k + 1, S.g, yk, S.sh, S.ism);
-            // the slot's next loads after its last use, so that they reuse its registers
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (decltype(pre)::value) prefetch_f(S, k + 2);
-        };
-        int kf = 1;
-        for (; kf + 1 <= n; kf += 2) {
-            fwd_step(kf, fsl[0], std::true_type{});
-            fwd_step(kf + 1, fsl[1], std::true_type{});
-        }
-        if (kf <= n) fwd_step(kf, fsl[0], std::false_type{});   // the last step: nothing to fetch
+        for (int q = 0; q < NS; ++q) fetch(sl[q], 1 + q);
+        const cplx<T> y0[4] = {mk<T>(0, 0), mk<T>(0, 0), mk<T>(0, 0), mk<T>(0, 0)};
+        input(g0, ism0, mk<T>(T(0), T(0)), y0, 1);
     }
+    // nothing outstanding on entry: the waits in the loop count its own operations
+    __builtin_amdgcn_s_waitcnt(0);
+    auto step = [&](int s, Slot& S, auto pre) {
+        if constexpr (NW > 1) __syncthreads();
+        const CTile<T> acc = M.product(S.f, u, tb[NW > 1 ? s & 1 : 0]);
+        cplx<T> y[4];
+        const unsigned ys = (unsigned)(H.blk(s) - 1) * ystep;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            y[v] = mk<T>(acc.re[v], acc.im[v]);
+            buf_store(ry, yoff[v], ys, y[v]);
+        }
+        input(S.g, S.ism, ccast<T>(S.sh), y, (s + 1) & 1);
+        // the slot's next loads after its last use, so that they reuse its registers
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(pre)::value) fetch(S, s + NS);
+    };
+    int s = 1;
+    for (; s + NS - 1 <= H.np; s += NS)
+#pragma unroll
+        for (int q = 0; q < NS; ++q) step(s + q, sl[q], std::true_type{});
+#pragma unroll
+    for (int q = 0; q < NS - 1; ++q)
+        if (s + q <= H.np) step(s + q, sl[q], std::false_type{});
+}
 
-    // backward sweep: v_n = y_n, v_k = y_k - S_k^-1 E_k v_{k+1}; block k-1 in
-    // ring slot k & 1.  Slot of step k: y_k, the values its outputs add to and
-    // the coupling of lines k-1, k (used in step k), and block k-2 (stashed at
-    // the end of step k).  Step 1 stashes and forms data nobody reads.
-    const int jout = (d.kind == ASP_SUB_R) ? (d.xe - d.lo) : (d.xs - d.lo);   // OUT_LINE row
-    // IN_TWIST: the solutions of this chunk start at blocks slot + 1 <= kmax
-    // and are zero above; kind 0 reads its map entries on line jout, kind 1
-    // (unit data on line jout) on the data line grow
-    const int kmax = (INM == IN_TWIST) ? min((ch + 1) * SRB, n) : n;
-    const bool tw1 = INM == IN_TWIST && a.twist_kind == 1;
-    const int jrow = tw1 ? grow : jout;
-    const int omode = (d.kind == ASP_SUB_L) ? a.out_mode_L : a.out_mode;
-    zd* const outp = (d.kind == ASP_SUB_L) ? a.out_L : a.out;
-    // map modes write the outgoing line only (known at compile time, so the
-    // grid-output state takes no registers); the others store v on X_p
-    const bool grid_out = NOSTAGE ? false : omode != OUT_LINE;
-    // Grid outputs on the first SROW lines of X are staged in LDS and written
-    // KO steps at a time (whole 128-byte lines per right-hand side and line);
-    // the other lines of X (the first and last layers are wider) are written
-    // at every step.
-    const bool bufo = a.buf_ok != 0;
-    const bool staging = !NOSTAGE && grid_out && bufo;
-    int xr[4];
-    bool stgd[4];
+// backward pass of one half: the middle block, then x_s = y_s - S^-1 E x_{s+1}
+// outwards; outputs on the lines of X.  IN_TWIST (the boundary maps): chains
+// towards the end of the half that start from columns of the diagonal blocks
+// of H^-1 (kind 0) or from the unit vectors at the middle block (kind 2).
+template <typename T, int LR, int INM, bool SPL>
+__global__ __launch_bounds__(4 * LR) void solve2d_bwd_kernel(SolveArgs a) {
+    static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
+    static_assert(4 * LR * 4 <= SINK_ELEMS, "four discard entries per thread");
+    using Tile = BlockTile<T, LR, SPL>;
+    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T>();
+    constexpr bool TW = INM == IN_TWIST;
+    __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
+    extern __shared__ __align__(16) unsigned char dyn[];
+    cplx<T>* const stg = reinterpret_cast<cplx<T>*>(dyn);   // [line][rhs][KO + 1]
+    const int n = a.n, p = mid_block(n);
+    int jl, ch, dir, nchunk;
+    bool below = false;   // IN_TWIST kind 0: the triangle away from the diagonal's chains
+    if constexpr (TW) {
+        // kind 0: chunk ch of a half starts at step min(16 (ch + 1), columns); the
+        // longest chains of every problem first, in dispatch order
+        const int w = (int)blockIdx.x;
+        if (a.twist_kind == 0) {
+            nchunk = (p + RC - 1) / RC;
+            if (w >= a.njobs * nchunk * 4) return;
+            ch = nchunk - 1 - w / (4 * a.njobs);
+            const int r = w % (4 * a.njobs);
+            below = r & 1;
+            dir = (r >> 1) & 1;
+            jl = r >> 2;
+            if (dir && ch * RC >= n - p) return;
+        } else {
+            nchunk = (a.nact + RC - 1) / RC;
+            if (w >= a.njobs * nchunk * 2) return;
+            ch = w % nchunk;
+            dir = (w / nchunk) & 1;
+            jl = w / (2 * nchunk);
+        }
+    } else {
+        nchunk = (a.nact + RC - 1) / RC;
+        const SolveItem it(a.njobs, nchunk);
+        if (!it.ok) return;
+        jl = it.jl;
+        ch = it.ch;
+        dir = it.dir;
+    }
+    const SubDesc d = a.desc[a.jobs[jl < a.njobs0 ? jl : a.jobs1 + jl - a.njobs0]];
+    const int L = d.L;
+    const long long N = a.N;
+    const Half H(n, dir);
+    if (!TW && dir && H.np == 0) return;
+    Tile M;
+    M.init(d, reinterpret_cast<const cplx<T>*>(a.fac) + d.fac_off);
+    const int li = M.li;
+    const zd* tab = a.subtab + d.tab_off;
+    const int slot = ch * RC + li;
+    const int grow = (d.kind == ASP_SUB_R) ? 0 : L - 1;
+    const int jout = (d.kind == ASP_SUB_R) ? (d.xe - d.lo) : (d.xs - d.lo);   // outgoing line
+    const zd coupl = (d.kind == ASP_SUB_R) ? tab[0] : tab[L];
+    int row[4];
+    bool rowv[4];
+    cplx<T> sinv2[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        xr[v] = d.lo + row[v] - d.xs;
-        stgd[v] = staging && inX[v] && xr[v] < SROW;
+        row[v] = 16 * M.rt + Mfma<T>::row(M.l, v);
+        rowv[v] = row[v] < L;
+        sinv2[v] = rowv[v] ? ccast<T>(tab[L + 1 + row[v]]) : mk<T>(0, 0);
     }
-    // IN_TWIST: y_k is the starting vector of the solution that starts at
-    // block k (slot = k - 1), zero otherwise: column grow (kind 0, times the
-    // unit data's coupling) or jout (kind 1) of G_k, the diagonal block of H^-1
-    const cplx<T>* const Gcol = reinterpret_cast<const cplx<T>*>(a.Tout) +
-                                (INM == IN_TWIST ? d.g_off : 0) + (tw1 ? LR : 0);
-    const cplx<T> cin_s = tw1 ? mk<T>(T(1), T(0))
-                              : ccast<T>(-(coupl * a.ax.inv_sh2[min(slot, n - 1)]));
-    auto load_y = [&](int k, cplx<T> (&yv)[4]) {
-        if constexpr (INM == IN_TWIST) {
-            const long long kk = max(k, 1);
-            const bool st = valid && slot == k - 1;
+    // kind 0: columns (below: rows) of this half, counted from its end, chunk by
+    // chunk; the half of block p takes it too.  smax: the chain's first step
+    const int ncol = TW && a.twist_kind == 0 ? H.np + (dir ? 0 : 1) : a.nact;
+    const bool valid = slot < ncol;
+    const int rid = !TW && valid ? (a.act ? a.act[slot] : slot) : 0;
+    const int smax = TW && a.twist_kind == 0 ? min((ch + 1) * RC, ncol) : H.np + 1;
+
+    // -- y of a step -----------------------------------------------------------
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+        TW ? static_cast<void*>(reinterpret_cast<cplx<T>*>(a.Tout) + d.g_off)
+           : static_cast<void*>(reinterpret_cast<cplx<T>*>(a.y) +
+                                ((long long)jl * nchunk + ch) * n * LR * RC),
+        0, 0x7fffffff, BUF_DW3);
+    constexpr unsigned ystep = (TW ? 2 * LR : LR * RC) * sizeof(cplx<T>);
+    unsigned yoff[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const cplx<T> g0 = Gcol[(kk - 1) * 2 * LR + row[v]];
-                yv[v] = (st && rowv[v]) ? cin_s * g0 : mk<T>(0, 0);
-            }
-        } else {
-            const long long kk = max(k, 1);     // blocks before the first: y = 0
+    for (int v = 0; v < 4; ++v)
+        yoff[v] = !rowv[v] ? BUF_OOB
+                  : TW     ? (unsigned)(((below ? LR : 0) + row[v]) * sizeof(cplx<T>))
+                           : (unsigned)((row[v] * RC + li) * sizeof(cplx<T>));
+    // kind 0: the starting vector of the solution that starts at this lane's
+    // block, zero at the others: column grow of G_k times the unit data's
+    // coupling, or column jout (below); kind 2 adds nothing after the start
+    const cplx<T> cin_s =
+        TW && !below ? ccast<T>(-(coupl * a.ax.inv_sh2[H.blk(min(slot, n - 1) + 1) - 1])) : mk<T>(T(1), T(0));
+    auto load_y = [&](int s, cplx<T> (&y)[4]) {
+        const int k = H.blk(max(s, 1));
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const cplx<T> y0 = Y[((kk - 1) * LR + row[v]) * SRB + rloc];
-                yv[v] = (k >= 1) ? y0 : mk<T>(0, 0);
-            }
+        for (int v = 0; v < 4; ++v) y[v] = buf_load<T>(ry, yoff[v], (unsigned)(k - 1) * ystep);
+    };
+    auto use_y = [&](int s, cplx<T> (&y)[4]) {
+        if constexpr (TW) {
+            const bool st = a.twist_kind == 0 && valid && slot == s - 1;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) y[v] = csel(st, cin_s * y[v], mk<T>(T(0), T(0)));
         }
     };
-    // the one entry of this lane on the OUT_LINE row, if any
-    int jsel = -1;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (rowv[e] && row[e] == jrow) jsel = e;
-    // boundary maps in row tiles of 16: entry (row r, column c) at (r / 16) n 16 +
-    // 16 c + r % 16, so that a sweep workgroup's 16 rows are one contiguous run
-    cplx<T>* const Tbase = reinterpret_cast<cplx<T>*>(a.Tout) + d.tr_off;
-    const bool tkeep = valid && jsel >= 0;
-    auto tidx = [&](int k) { return ((long long)((k - 1) >> 4) * n + slot) * 16 + ((k - 1) & 15); };
-    // IN_TWIST kind 1: the entry (row slot, column k - 1)
-    auto tidx1 = [&](int k) { return ((long long)(slot >> 4) * n + (k - 1)) * 16 + (slot & 15); };
-    bool keep[4];
-    zd* gout[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        keep[e] = valid && inX[e];
-        gout[e] = outp + (long long)rid * N + (long long)n * (lcl[e] - 1);
-    }
-    // With a.buf_ok the outputs go through a buffer resource: a lane that keeps
-    // nothing gives an offset past the range and the hardware drops the write
-    // (no memory traffic, no branch).  Otherwise such writes go to the discard
-    // buffer.
+
+    // -- outputs ----------------------------------------------------------------
+    zd* const outp = (d.kind == ASP_SUB_L) ? a.out_L : a.out;
+    const bool bufo = a.buf_ok != 0;
+    cplx<T>* const Tbase = reinterpret_cast<cplx<T>*>(a.Tout) + (TW ? d.tr_off : 0);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        grid_out ? static_cast<void*>(outp) : static_cast<void*>(Tbase), 0, 0x7fffffff, BUF_DW3);
-    unsigned boff[4];   // byte offsets at step 1
+        TW ? static_cast<void*>(Tbase) : static_cast<void*>(outp), 0, 0x7fffffff, BUF_DW3);
+    zd* const sink = a.sink + threadIdx.x * 4;
+    // Grid outputs: the first a.srow lines of X are staged in LDS and written KO
+    // steps at a time (whole 128-byte lines per right-hand side and line), each
+    // wavefront its own rows; the other lines of X (the first and last layers are
+    // wider) are written at every step.  Without a.buf_ok everything is.
+    const int nst = !TW && bufo ? min(d.xe - d.xs + 1, a.srow) : 0;
+    int xr[4];
+    bool stgd[4], dirw[4];
+    bool any_dir = false;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        boff[e] = grid_out ? ((keep[e] && !stgd[e])
-                                  ? (unsigned)(((long long)rid * N + (long long)n * (lcl[e] - 1)) * 16)
-                                  : BUF_OOB)
-                           : BUF_OOB;   // OUT_LINE offsets are formed per step
-    auto emit = [&](int k, const cplx<T> (&v)[4]) {
-        if (!grid_out) {
-            cplx<T> x = v[0];
+    for (int v = 0; v < 4; ++v) {
+        const int line = d.lo + row[v];
+        const bool inX = rowv[v] && line >= d.xs && line <= d.xe;
+        xr[v] = line - d.xs;
+        stgd[v] = inX && xr[v] < nst;
+        dirw[v] = inX && !stgd[v];
+        any_dir = any_dir || dirw[v];
+    }
+    any_dir = __any(any_dir);
+    // blocks this half writes: dir 0 takes the middle block
+    const int kmin = dir ? p + 1 : 1, kmax = dir ? n : p;
+    int frid[2];
+    bool fval[2];
 #pragma unroll
-            for (int e = 1; e < 4; ++e) x = csel(jsel == e, v[e], x);
-            bool kp = tkeep;
-            long long ti = tidx(k);
-            if constexpr (INM == IN_TWIST) {
-                if (tw1) {
-                    // entry (slot, k - 1) below the diagonal, with the unit data's
-                    // coupling of column k - 1
-                    kp = kp && k - 1 < slot;
-                    ti = tidx1(k);
-                    x = ccast<T>(-(coupl * a.ax.inv_sh2[k - 1])) * x;
-                } else {
-                    kp = kp && k - 1 <= slot;   // on and above the diagonal
+    for (int h = 0; h < 2; ++h) {
+        const int fs = ch * RC + 8 * h + (M.l >> 3);
+        fval[h] = !TW && fs < a.nact;
+        frid[h] = fval[h] ? (a.act ? a.act[fs] : fs) : 0;
+    }
+    auto flush = [&](int g) {
+        wave_lds_fence();
+        const int i1 = g * KO + (M.l & 7);
+        const bool kin = i1 + 1 >= kmin && i1 + 1 <= kmax;
+        for (int x = 0; x < nst; ++x) {
+            const int r = d.xs - d.lo + x;
+            if ((r >> 4) != M.rt) continue;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const cplx<T> val = stg[(x * RC + 8 * h + (M.l >> 3)) * (KO + 1) + (M.l & 7)];
+                const unsigned off = (unsigned)(((long long)frid[h] * N + (long long)n * (d.xs + x - 1) + i1) * 16);
+                buf_store(rs, kin && fval[h] ? off : BUF_OOB, 0u, ccast<double>(val));
+            }
+        }
+        wave_lds_fence();
+    };
+    // IN_TWIST: the wavefront and lanes holding the row a map entry is read from
+    const int jrow = below ? grow : jout;
+    const bool jmine = TW && (jrow >> 4) == M.rt, gmine = TW && (grow >> 4) == M.rt, omine = TW && (jout >> 4) == M.rt;
+    auto pick = [&](const cplx<T> (&x)[4], int r, bool& hit) {
+        cplx<T> y = x[0];
+        hit = row[0] == r;
+#pragma unroll
+        for (int v = 1; v < 4; ++v) {
+            y = csel(row[v] == r, x[v], y);
+            hit = hit || row[v] == r;
+        }
+        return y;
+    };
+    auto emit = [&](int s, const cplx<T> (&x)[4]) {
+        const int k = H.blk(s);
+        if constexpr (TW) {
+            bool hit;
+            if (a.twist_kind == 0) {
+                if (!jmine) return;
+                // boundary maps in row tiles of 16: entry (row r, column c) at
+                // (r / 16) n 16 + 16 c + r % 16
+                cplx<T> y = pick(x, jrow, hit);
+                const int c = H.blk(slot + 1) - 1;   // this lane's column (below: row)
+                const int r_ = below ? c : k - 1, c_ = below ? k - 1 : c;
+                if (below) y = ccast<T>(-(coupl * a.ax.inv_sh2[k - 1])) * y;
+                const bool kp = hit && valid && (below ? s - 1 < slot : s - 1 <= slot);
+                const long long ti = ((long long)(r_ >> 4) * n + c_) * 16 + (r_ & 15);
+                if (bufo)
+                    buf_store(rs, kp ? (unsigned)(ti * sizeof(cplx<T>)) : BUF_OOB, 0u, y);
+                else if (kp)
+                    Tbase[ti] = y;
+            } else {
+                // rows grow and jout of the propagator from the middle block to k
+                if (gmine) {
+                    const cplx<T> y = pick(x, grow, hit);
+                    buf_store(ry, hit && valid ? (unsigned)(((k - 1) * 2 * LR + slot) * sizeof(cplx<T>)) : BUF_OOB, 0u, y);
+                }
+                if (omine) {
+                    const cplx<T> y = pick(x, jout, hit);
+                    buf_store(ry, hit && valid ? (unsigned)(((k - 1) * 2 * LR + LR + slot) * sizeof(cplx<T>)) : BUF_OOB, 0u, y);
                 }
             }
-            if (bufo)
-                buf_store(rs, kp ? (unsigned)(ti * sizeof(cplx<T>)) : BUF_OOB, x);
-            else
-                *(kp ? Tbase + ti : sinkT) = x;
             return;
         }
-        if constexpr (!NOSTAGE) {
-            if (staging) {
-                cplx<T>* sg = stg + ((((k - 1) / KO) & 1) * KO + (k - 1) % KO) * SROW * SRB;
+        if (k < kmin || k > kmax) return;   // the middle block in half 1
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (stgd[e]) sg[xr[e] * SRB + rloc] = v[e];
+        for (int v = 0; v < 4; ++v)
+            if (stgd[v]) stg[(xr[v] * RC + li) * (KO + 1) + (k - 1) % KO] = x[v];
+        if (any_dir) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const bool on = dirw[v] && valid;
+                const long long o = (long long)rid * N + (long long)n * (d.lo + row[v] - 1) + (k - 1);
+                const zd y = ccast<double>(x[v]);
+                if (bufo)
+                    buf_store(rs, on ? (unsigned)(o * 16) : BUF_OOB, 0u, y);
+                else
+                    *(on ? outp + o : sink + v) = y;
             }
         }
+        if (nst > 0 && (dir ? ((k - 1) % KO == KO - 1 || k == n) : (k - 1) % KO == 0)) flush((k - 1) / KO);
+    };
+
+    // -- start --------------------------------------------------------------------
+    struct Slot {
+        cplx<T> f[KS], y[4];   // operand and y of step s
+        zd sh;                 // s1 between blocks s - 1 and s
+    };
+    auto fetch = [&](Slot& S, int s) {
+        const int sc = max(s, 1);
+        M.load(S.f, H.blk(sc));
+        load_y(s, S.y);
+        S.sh = a.ax.sh[H.half_line(max(s - 1, 0))];
+    };
+    cplx<T> x[4], u[4];
+    // E x_{s+1} (sh: s1 between blocks s and s + 1) for step s
+    auto coupled = [&](int s, cplx<T> shc) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const zd x = ccast<double>(v[e]);
-            if (bufo)
-                buf_store(rs, boff[e] + (unsigned)(k - 1) * 16u, x);
-            else
-                *(keep[e] ? gout[e] + (k - 1) : sink + e) = x;
+        for (int v = 0; v < 4; ++v) {
+            u[v] = (shc * sinv2[v]) * x[v];
+            if constexpr (NW > 1) tb[s & 1][row[v]][li] = u[v];
         }
     };
-    // write out the staged steps g KO + 1 .. g KO + KO: thread (line, rhs) of
-    // the staged block writes KO consecutive entries; lanes past the block
-    // pass offsets past the range
-    const int fx = min(tid / SRB, SROW - 1), frl = tid % SRB;
-    const int fslot = ch * SRB + frl;
-    const int nxs = min(d.xe - d.xs + 1, SROW);
-    const bool fvalid = staging && tid < SROW * SRB && tid / SRB < nxs && fslot < a.nact;
-    const int frid = fvalid ? (a.act ? a.act[fslot] : fslot) : 0;
-    const unsigned fbase =
-        fvalid ? (unsigned)(((long long)frid * N + (long long)n * (d.xs + fx - 1)) * 16) : BUF_OOB;
-    auto flush = [&](int g) {
-        if constexpr (!NOSTAGE) {
-            const cplx<T>* sg = stg + (g & 1) * KO * SROW * SRB + fx * SRB + frl;
+    Slot sl[NS];
 #pragma unroll
-            for (int q = 0; q < KO; ++q) {
-                const int st = g * KO + 1 + q;
-                const unsigned off = (st <= n) ? fbase + (unsigned)(st - 1) * 16u : BUF_OOB;
-                buf_store(rs, off, ccast<double>(sg[q * SROW * SRB]));
-            }
-        }
-    };
-    // E_k v_{k+1} for this lane's entries into tb[k & 1] (shk: s at line k + 1/2)
-    auto put_coupled = [&](int k, const cplx<T> (&v)[4], zd shk) {
-        const cplx<T> shc = ccast<T>(shk);
+    for (int q = 0; q < NS; ++q) fetch(sl[q], smax - 1 - q);
+    if constexpr (TW) {
+        if (a.twist_kind == 0) {
+            load_y(smax, x);
+            use_y(smax, x);
+        } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) tb[k & 1][row[e]][rloc] = (shc * sinv2[e]) * v[e];
-    };
-    struct BwdSlot {
-        cplx<T> pf[FPT];
-        cplx<T> y[4];
-        zd sh;
-    };
-    auto prefetch_b = [&](BwdSlot& S, int k) {
-        load_y(k, S.y);
-        fetch_to(S.pf, max(k - 2, 0));
-        S.sh = a.ax.sh[max(k - 1, 0)];
-    };
-    BwdSlot bsl[2];
-    {
-        const zd shn = a.ax.sh[max(kmax - 1, 0)];
-        if constexpr (INM == IN_TWIST) {
-            // no forward sweep: the starting vectors at the top block, and block
-            // kmax - 2 (S_{kmax-1}^-1) into the ring slot the first step reads
-            load_y(kmax, yk);
-            cplx<T> pf0[FPT];
-            fetch_to(pf0, max(kmax - 2, 0));
-            stash_from(pf0, (kmax - 1) & 1);
+            for (int v = 0; v < 4; ++v) x[v] = mk<T>(row[v] == slot ? T(1) : T(0), T(0));
         }
-        emit(kmax, yk);
-        put_coupled(kmax - 1, yk, shn);    // kmax = 1: data nobody reads
+        if (a.twist_kind == 0 || dir == 0) emit(smax, x);
+    } else {
+        // x_p = M_p^-1 (g_p - E_{p-1} y_{p-1} - E_p y_{p+1})
+        cplx<T> ym[4], yp[4], f[KS];
+        M.load(f, p);
+        const cplx<T> cm = p > 1 ? ccast<T>(a.ax.sh[p - 1]) : mk<T>(T(0), T(0));
+        const cplx<T> cp = p < n ? ccast<T>(a.ax.sh[p]) : mk<T>(T(0), T(0));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            ym[v] = buf_load<T>(ry, p > 1 ? yoff[v] : BUF_OOB, (unsigned)(max(p - 1, 1) - 1) * ystep);
+            yp[v] = buf_load<T>(ry, p < n ? yoff[v] : BUF_OOB, (unsigned)(min(p + 1, n) - 1) * ystep);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int line = d.lo + row[v];
+            cplx<T> t = mk<T>(T(0), T(0));
+            if (INM == IN_GRID && rowv[v] && line >= d.xs && line <= d.xe)
+                t = ccast<T>(a.r[(long long)rid * N + (long long)n * (line - 1) + p - 1]);
+            if (INM == IN_BOUNDARY && rowv[v] && row[v] == grow)
+                t = ccast<T>(a.W[((long long)d.wrow * a.w_rhs + rid) * n + p - 1] * -(coupl * a.ax.inv_sh2[p - 1]));
+            u[v] = (t - (cm * sinv2[v]) * ym[v]) - (cp * sinv2[v]) * yp[v];
+            if constexpr (NW > 1) tb[smax & 1][row[v]][li] = u[v];
+        }
+        if constexpr (NW > 1) __syncthreads();
+        const CTile<T> acc = M.product(f, u, tb[NW > 1 ? smax & 1 : 0]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = mk<T>(acc.re[v], acc.im[v]);
+        emit(smax, x);
     }
-    cplx<T> (&vk)[4] = yk;
-    prefetch_b(bsl[0], kmax - 1);
-    prefetch_b(bsl[1], kmax - 2);
+    if (smax > 1) coupled(smax - 1, ccast<T>(a.ax.sh[H.half_line(smax - 1)]));
     __builtin_amdgcn_s_waitcnt(0);
-    auto bwd_step = [&](int k, BwdSlot& S, auto pre) {
-        const int buf = k & 1;
-        __syncthreads();
-        if (staging && k % KO == 0) flush(k / KO);   // steps k+1 .. k+KO are staged
-        const CTile<T> acc = product(buf, buf);
+    auto step = [&](int s, Slot& S, auto pre) {
+        if constexpr (NW > 1) __syncthreads();
+        const CTile<T> acc = M.product(S.f, u, tb[NW > 1 ? s & 1 : 0]);
+        use_y(s, S.y);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) vk[e] = S.y[e] - mk<T>(acc.re[e], acc.im[e]);
-        emit(k, vk);
-        stash_from(S.pf, (k - 1) & 1);                               // block k-2
-        put_coupled(k - 1, vk, S.sh);
+        for (int v = 0; v < 4; ++v) x[v] = S.y[v] - mk<T>(acc.re[v], acc.im[v]);
+        emit(s, x);
+        coupled(s - 1, ccast<T>(S.sh));
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(pre)::value) prefetch_b(S, k - 2);
+        if constexpr (decltype(pre)::value) fetch(S, s - NS);
     };
-    int kb = kmax - 1;
-    for (; kb - 1 >= 1; kb -= 2) {
-        bwd_step(kb, bsl[0], std::true_type{});
-        bwd_step(kb - 1, bsl[1], std::true_type{});
+    int s = smax - 1;
+    for (; s - NS + 1 >= 1; s -= NS)
+#pragma unroll
+        for (int q = 0; q < NS; ++q) step(s - q, sl[q], std::true_type{});
+#pragma unroll
+    for (int q = 0; q < NS - 1; ++q)
+        if (s - q >= 1) step(s - q, sl[q], std::false_type{});
+}
+
+// ----------------------------------------------------------------------------
+// The two quadrants of a boundary map across the middle block p: for r and c on
+// either side of it (or one of them p),
+//   T[r][c] = cin_c (row jout of Phi_r) M_p^-1 (row grow of Phi_c)^T,
+// Phi_k the propagator from block p to block k (x_k = Phi_k x_p without data in
+// between), whose two rows the kind-2 chains left in the column buffer: rank L.
+// One wavefront per 16 columns and half of the row tiles it needs; the product
+// Z = M_p^-1 (rows grow)^T first, whose result tile is the operand of the next
+// product in its own lanes.  FP32 and FP64 products (also with ASP_PREC_BF16X3).
+// Bound by the writes of the map entries (n^2 / 2 per problem).
+// ----------------------------------------------------------------------------
+template <typename T, int LR>
+__global__ __launch_bounds__(256) void map_cross_kernel(SolveArgs a) {
+    constexpr int JT = LR / 16;
+    const int n = a.n, p = mid_block(n);
+    const int ntile = (n + 15) / 16;
+    const int jl = blockIdx.y;
+    const int ctile = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (ctile >= ntile) return;
+    const SubDesc d = a.desc[a.jobs[jl < a.njobs0 ? jl : a.jobs1 + jl - a.njobs0]];
+    const int L = d.L;
+    const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+    const zd* tab = a.subtab + d.tab_off;
+    const zd coupl = (d.kind == ASP_SUB_R) ? tab[0] : tab[L];
+    const cplx<T>* F = reinterpret_cast<const cplx<T>*>(a.fac) + d.fac_off + (long long)(p - 1) * L * LR;
+    const cplx<T>* G = reinterpret_cast<const cplx<T>*>(a.Tout) + d.g_off;
+    cplx<T>* const Tm = reinterpret_cast<cplx<T>*>(a.Tout) + d.tr_off;
+    // Z[j][c], j in the accumulator order of JT tiles
+    const int c = 16 * ctile + li, cc = min(c, n - 1);
+    CTile<T> Z[JT];
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) Z[jt].zero();
+    for (int i0 = 0; i0 < L; i0 += 4) {
+        const int i = i0 + lk;
+        const cplx<T> b = csel(i < L, G[(long long)cc * 2 * LR + min(i, L - 1)], mk<T>(T(0), T(0)));
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) cmac(Z[jt], F[(long long)min(i, L - 1) * LR + 16 * jt + li], b);
     }
-    if (kb >= 1) bwd_step(kb, bsl[0], std::false_type{});
-    if (staging) {
-        __syncthreads();
-        flush(0);
+    const cplx<T> cin = ccast<T>(-(coupl * a.ax.inv_sh2[cc]));
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const cplx<T> z = cin * mk<T>(Z[jt].re[v], Z[jt].im[v]);
+            Z[jt].re[v] = z.x;
+            Z[jt].im[v] = z.y;
+        }
+    // row tiles with rows on the other side of some column of this tile
+    const bool has_left = 16 * ctile < p, has_right = min(16 * ctile + 15, n - 1) >= p;
+    const int t0 = has_right ? 0 : p / 16, t1 = has_left ? ntile : (p + 15) / 16;
+    for (int rtile = t0; rtile < t1; ++rtile) {
+        const int r = 16 * rtile + li, rc = min(r, n - 1);
+        CTile<T> D;
+        D.zero();
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int j = 16 * jt + Mfma<T>::row(l, v);
+                const cplx<T> b = csel(j < L, G[(long long)rc * 2 * LR + LR + min(j, L - 1)], mk<T>(T(0), T(0)));
+                cmac(D, mk<T>(Z[jt].re[v], Z[jt].im[v]), b);
+            }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int cq = 16 * ctile + Mfma<T>::row(l, v);
+            if (r < n && cq < n && (r < p) != (cq < p))
+                Tm[((long long)rtile * n + cq) * 16 + li] = mk<T>(D.re[v], D.im[v]);
+        }
     }
 }
 
@@ -1047,17 +1382,30 @@ hipError_t launch_sweep_hand(const asp_plan* P, const zd* z, const zd* stage, zd
 }
 
 hipError_t launch_factor2d(const asp_plan* P, hipStream_t st) {
-    const int nsub = (int)P->subs.size();
     AxisTables ax{P->d_axis, P->d_axis + (P->n + 1), P->d_axis + (2 * P->n + 1)};
-    const bool wide = std::max(P->LR_M, P->LR_RL) > 32;
+    const int LX = std::max(P->LR_M, P->LR_RL);
+    auto cls = [&](int first, int count, int LR) {
+        FactorClass c{first, count, LR, 0, 0};
+        for (int s = first; s < first + count; ++s) c.npair = std::max(c.npair, (P->subs[s].L + 1) / 2);
+        c.blocks = (count + LX / LR - 1) / (LX / LR);
+        return c;
+    };
+    const FactorClass cm = cls(0, P->m, P->LR_M);
+    const FactorClass cr = cls(P->m, (int)P->subs.size() - P->m, P->LR_RL);
+    auto go = [&](auto* k, auto* fac) {
+        hipLaunchKernelGGL(k, dim3(cm.blocks + cr.blocks), dim3(8 * LX), 0, st, P->d_desc, cm, cr, ax,
+                           P->d_subtab, P->d_ksq, P->n, fac, P->d_flag);
+    };
     if (P->prec != ASP_PREC_FP64) {
-        auto k = wide ? factor2d_kernel<float, MAXL> : factor2d_kernel<float, 32>;
-        hipLaunchKernelGGL(k, dim3(nsub), dim3(FB), 0, st, P->d_desc, ax, P->d_subtab, P->d_ksq,
-                           P->n, reinterpret_cast<zf*>(P->d_fac), P->d_flag);
+        zf* f = reinterpret_cast<zf*>(P->d_fac);
+        if (LX == 16) go(factor2d_kernel<float, 16>, f);
+        else if (LX == 32) go(factor2d_kernel<float, 32>, f);
+        else go(factor2d_kernel<float, 64>, f);
     } else {
-        auto k = wide ? factor2d_kernel<double, MAXL> : factor2d_kernel<double, 32>;
-        hipLaunchKernelGGL(k, dim3(nsub), dim3(FB), 0, st, P->d_desc, ax, P->d_subtab, P->d_ksq,
-                           P->n, reinterpret_cast<zd*>(P->d_fac), P->d_flag);
+        zd* f = reinterpret_cast<zd*>(P->d_fac);
+        if (LX == 16) go(factor2d_kernel<double, 16>, f);
+        else if (LX == 32) go(factor2d_kernel<double, 32>, f);
+        else go(factor2d_kernel<double, 64>, f);
     }
     return hipGetLastError();
 }
@@ -1068,7 +1416,7 @@ static hipError_t launch_rgf_t(const asp_plan* P, const int* jobs0, const int* j
     AxisTables ax{P->d_axis, P->d_axis + (P->n + 1), P->d_axis + (2 * P->n + 1)};
     const cplx<TS>* fac = reinterpret_cast<const cplx<TS>*>(P->d_fac);
     cplx<TS>* tb = reinterpret_cast<cplx<TS>*>(P->d_T);
-    const dim3 grid(njobs, nlists);
+    const dim3 grid(njobs, nlists, 2);
     if (P->LR_RL == 16)
         hipLaunchKernelGGL((rgf2d_kernel<TS, 16>), grid, dim3(FB), 0, st, P->d_desc, jobs0, jobs1, ax,
                            P->d_subtab, P->n, fac, tb);
@@ -1091,48 +1439,64 @@ hipError_t launch_rgf2d(const asp_plan* P, int job0, int job1, int njobs, hipStr
 }
 
 // one kernel per (precision, row count, input mode): the M-solves, the R/L
-// solves and the transfer-map solves are separate kernels
-template <int LR, int INM>
-static hipError_t launch_solve_lr(const asp_plan* P, const SolveArgs& a, int blocks, hipStream_t st) {
-    if (P->prec == ASP_PREC_BF16X3)
-        hipLaunchKernelGGL((solve2d_kernel<float, LR, INM, true>), dim3(blocks), dim3(SB), 0, st, a);
-    else if (P->prec != ASP_PREC_FP64)
-        hipLaunchKernelGGL((solve2d_kernel<float, LR, INM>), dim3(blocks), dim3(SB), 0, st, a);
-    else
-        hipLaunchKernelGGL((solve2d_kernel<double, LR, INM>), dim3(blocks), dim3(SB), 0, st, a);
+// solves and the map chains are separate kernels
+template <typename T, int LR, int INM, bool SPL>
+static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st) {
+    if (INM == IN_TWIST) {
+        const int half = (mid_block(a.n) + RC - 1) / RC;
+        const unsigned blocks = a.twist_kind == 0 ? 4u * a.njobs * half : 2u * a.njobs * nchunk;
+        hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL>), dim3(blocks), dim3(4 * LR), 0, st, a);
+        return hipGetLastError();
+    }
+    constexpr int FWD = INM == IN_TWIST ? IN_GRID : INM;   // map chains have no forward pass
+    const unsigned blocks = (2u * a.njobs * nchunk + 7) / 8 * 8;
+    hipLaunchKernelGGL((solve2d_fwd_kernel<T, LR, FWD, SPL>), dim3(blocks), dim3(4 * LR), 0, st, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const size_t lds = (size_t)a.srow * RC * (KO + 1) * sizeof(cplx<T>);
+    hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL>), dim3(blocks), dim3(4 * LR), lds, st, a);
     return hipGetLastError();
 }
 
+template <int LR, int INM>
+static hipError_t launch_solve_lr(const asp_plan* P, const SolveArgs& a, int nchunk, hipStream_t st) {
+    if (P->prec == ASP_PREC_BF16X3) return launch_solve_t<float, LR, INM, true>(a, nchunk, st);
+    if (P->prec != ASP_PREC_FP64) return launch_solve_t<float, LR, INM, false>(a, nchunk, st);
+    return launch_solve_t<double, LR, INM, false>(a, nchunk, st);
+}
+
 template <int LR>
-static hipError_t launch_solve_mode(const asp_plan* P, const SolveArgs& a, int blocks,
+static hipError_t launch_solve_mode(const asp_plan* P, const SolveArgs& a, int in_mode, int nchunk,
                                     hipStream_t st) {
-    if (a.in_mode == IN_GRID) return launch_solve_lr<LR, IN_GRID>(P, a, blocks, st);
-    if (a.in_mode == IN_BOUNDARY) return launch_solve_lr<LR, IN_BOUNDARY>(P, a, blocks, st);
-    if (a.in_mode == IN_TWIST) return launch_solve_lr<LR, IN_TWIST>(P, a, blocks, st);
+    if (in_mode == IN_GRID) return launch_solve_lr<LR, IN_GRID>(P, a, nchunk, st);
+    if (in_mode == IN_BOUNDARY) return launch_solve_lr<LR, IN_BOUNDARY>(P, a, nchunk, st);
+    if (in_mode == IN_TWIST) return launch_solve_lr<LR, IN_TWIST>(P, a, nchunk, st);
     return hipErrorInvalidValue;
+}
+
+template <typename T>
+static hipError_t launch_cross_t(int LR, const SolveArgs& a, hipStream_t st) {
+    const dim3 grid(((a.n + 15) / 16 + 3) / 4, a.njobs);
+    if (LR == 16) hipLaunchKernelGGL((map_cross_kernel<T, 16>), grid, dim3(256), 0, st, a);
+    else if (LR == 32) hipLaunchKernelGGL((map_cross_kernel<T, 32>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((map_cross_kernel<T, 64>), grid, dim3(256), 0, st, a);
+    return hipGetLastError();
 }
 
 int solve_rhs_per_block(int LR) { return 1024 / LR; }
 
-// forward results of one workgroup: n blocks x LR rows x 1024 / LR right-hand sides
+// forward results: n blocks x LR rows x 1024 / LR right-hand sides
 long long solve_scratch_per_block(const asp_plan* P) { return (long long)P->n * 1024; }
 
-hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t st) {
-    if (L.njobs <= 0 || L.nact <= 0) return hipSuccess;
-    // the map solves write the outgoing line, the others store v on X_p
-    const bool twist = L.in_mode == IN_TWIST;
-    if (twist ? L.out_mode != OUT_LINE
-              : (L.out_mode != OUT_GRID_STORE || (L.out_L && L.out_mode_L != OUT_GRID_STORE)))
-        return hipErrorInvalidValue;
+static SolveArgs solve_args(const asp_plan* P, const SolveLaunch& L) {
     SolveArgs a;
     a.desc = P->d_desc;
     a.jobs = P->d_jobs + L.job0;
     a.njobs = L.njobs;
+    a.njobs0 = L.njobs0 ? L.njobs0 : L.njobs;
+    a.jobs1 = L.job1 - L.job0;
     a.act = L.act;
     a.nact = L.nact;
-    a.in_mode = L.in_mode;
-    a.out_mode = L.out_mode;
-    a.out_mode_L = L.out_L ? L.out_mode_L : L.out_mode;
     a.out_L = L.out_L ? L.out_L : L.out;
     a.fac = P->d_fac;
     a.ax = AxisTables{P->d_axis, P->d_axis + (P->n + 1), P->d_axis + (2 * P->n + 1)};
@@ -1143,28 +1507,41 @@ hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t s
     a.out = L.out;
     a.Tout = P->d_T;
     a.y = P->d_y;
-    a.y_per_wave = solve_scratch_per_block(P);
     a.sink = P->d_sink;
-    {
-        const size_t esz = P->prec != ASP_PREC_FP64 ? sizeof(zf) : sizeof(zd);
-        const long long lim = 1LL << 31;
-        const long long grid_bytes = (long long)std::max(P->ws_rhs, L.nact) * P->N * (long long)sizeof(zd);
-        const long long line_bytes = (long long)((P->n + 15) / 16 * 16) * P->n * (long long)esz;
-        // map outputs (OUT_LINE) address the map only
-        a.buf_ok = ((L.out_mode == OUT_LINE || grid_bytes < lim) && line_bytes < lim) ? 1 : 0;
-    }
+    const size_t esz = P->prec != ASP_PREC_FP64 ? sizeof(zf) : sizeof(zd);
+    const long long lim = 1LL << 31;
+    // map chains address one problem's map, the others the grid vectors
+    const long long bytes = L.in_mode == IN_TWIST
+                                ? (long long)((P->n + 15) / 16 * 16) * P->n * (long long)esz
+                                : (long long)std::max(P->ws_rhs, L.nact) * P->N * (long long)sizeof(zd);
+    a.buf_ok = bytes < lim ? 1 : 0;
     a.twist_kind = L.twist_kind;
+    // the lines of an interior layer, in up to two groups of four
+    a.srow = P->b <= STG_MAX / 2 ? STG_MAX / 2 : STG_MAX;
     a.n = P->n;
     a.N = P->N;
+    return a;
+}
+
+hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t st) {
+    if (L.njobs <= 0 || L.nact <= 0) return hipSuccess;
+    const SolveArgs a = solve_args(P, L);
     const int LR = L.rl ? P->LR_RL : P->LR_M;   // every job of one launch shares its row count
-    const int srb = solve_rhs_per_block(LR);
-    const long long B = (long long)L.njobs * ((L.nact + srb - 1) / srb);
+    const int nchunk = (L.nact + RC - 1) / RC;
     // IN_TWIST uses no forward-result scratch
-    if (!twist && B > P->y_waves) return hipErrorInvalidValue;
-    const int blocks = (int)(((B + 7) / 8) * 8);
-    if (LR == 16) return launch_solve_mode<16>(P, a, blocks, st);
-    if (LR == 32) return launch_solve_mode<32>(P, a, blocks, st);
-    return launch_solve_mode<64>(P, a, blocks, st);
+    if (L.in_mode != IN_TWIST &&
+        (long long)L.njobs * nchunk * P->n * LR * RC > P->y_waves * solve_scratch_per_block(P))
+        return hipErrorInvalidValue;
+    if (LR == 16) return launch_solve_mode<16>(P, a, L.in_mode, nchunk, st);
+    if (LR == 32) return launch_solve_mode<32>(P, a, L.in_mode, nchunk, st);
+    return launch_solve_mode<64>(P, a, L.in_mode, nchunk, st);
+}
+
+hipError_t launch_map_cross(const asp_plan* P, const SolveLaunch& L, hipStream_t st) {
+    if (L.njobs <= 0) return hipSuccess;
+    const SolveArgs a = solve_args(P, L);
+    if (P->prec != ASP_PREC_FP64) return launch_cross_t<float>(P->LR_RL, a, st);
+    return launch_cross_t<double>(P->LR_RL, a, st);
 }
 
 static int sweep_slots(int nact) { return (nact + SW_RT - 1) / SW_RT * SW_RT; }
