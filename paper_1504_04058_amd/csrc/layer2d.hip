@@ -20,6 +20,13 @@
 
 namespace {
 
+// at most 256 registers per lane (two wavefronts per SIMD): the accumulators of
+// the matrix instructions then live in ordinary registers.  With a larger
+// budget the compiler puts them in the accumulation registers and copies them
+// out and back around every scalar use (150 copies per pivot pair of the
+// factorization).
+#define ASP_PLAIN_ACC(...) __attribute__((amdgpu_waves_per_eu(__VA_ARGS__)))
+
 constexpr int WAVE = 64;
 static_assert(WAVE * 16 <= SINK_ELEMS, "sixteen discard entries per lane");
 
@@ -87,10 +94,21 @@ __device__ __forceinline__ void wave_lds_fence() {
 // and A[i][k] = A[k][i] otherwise, so the pivot columns are read from the pivot
 // rows.  A zero or non-finite pivot is reported as a breakdown.  Arithmetic in
 // double; the stored factor is rounded to TS.
-// What bounds it: the chain pivot row -> LDS -> 2 x 2 inverse (two FP64
-// divisions) -> update, once per pair and block; hence two pivots per exchange
-// and both halves at once.
+// What bounds it: the chain pivot rows -> LDS -> 2 x 2 inverse (two dependent
+// FP64 reciprocals) -> update, once per pair and block, about 1500 cycles; hence
+// two pivots per exchange, both halves at once and few instructions per pair
+// (n = 255, layers of 8 lines, FP64: 2.66 ms with one direction, one pivot per
+// exchange and vector arithmetic, 0.99 ms now; n = 1023: 11.9 -> 4.7 ms).
 // ----------------------------------------------------------------------------
+// 1 / p, q = |p|^2: the hardware reciprocal estimate with two Newton steps
+// (full precision) instead of an IEEE division, half the latency
+__device__ __forceinline__ zd cinv_fast(zd p, double q) {
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(fma(-q, r, 1.0), r, r);
+    r = fma(fma(-q, r, 1.0), r, r);
+    return mk(p.x * r, -p.y * r);
+}
+
 template <typename TS, int LR>
 __device__ __forceinline__ void factor2d_body(const SubDesc& d, bool live, int npair, int wl, AxisTables ax,
                                               const zd* __restrict__ subtab,
@@ -103,7 +121,7 @@ __device__ __forceinline__ void factor2d_body(const SubDesc& d, bool live, int n
     const int rt = wl % NW;
     const int L = d.L;
     const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
-    zd* rowbuf = rowbuf_ + H.dir * 4 * LR;      // [parity][2][LR]
+    zd* rowbuf = rowbuf_ + H.dir * (4 * LR + 8);   // [parity]: two rows of LR, a 2 x 2 block
     const zd* tab = subtab + d.tab_off;
     const zd* ssh = tab;                // s at half lines lo-1/2 .. hi+1/2
     const zd* sinv2 = tab + L + 1;      // 1/(s h^2) on lines lo..hi
@@ -178,67 +196,87 @@ __device__ __forceinline__ void factor2d_body(const SubDesc& d, bool live, int n
     int par = 0;
     auto invert = [&]() {
         for (int tb = 0; tb < CT; ++tb) {
+            const bool strip = rt == tb;   // this wavefront holds the pivot rows
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 if (8 * tb + q >= npair) break;
                 const int kk = 16 * tb + 2 * q;
                 const int vk = q >> 1;
-                zd* R0 = rowbuf + par * 2 * LR;
-                const zd* R1 = R0 + LR;
+                zd* R0 = rowbuf + par * (2 * LR + 4);   // rows kk, kk + 1, then the pivot block
+                zd* const PB = R0 + 2 * LR;
                 par ^= 1;
-                const bool mine = rt == tb && (lk >> 1) == (q & 1);   // lanes holding the pivot rows
-                if (mine)
+                const bool mine = strip && (lk >> 1) == (q & 1);   // lanes holding the pivot rows
+                const bool ep = (li >> 1) == q;                    // ... the pivot columns of tile tb
+                if (mine) {
 #pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) R0[(lk & 1) * LR + 16 * ct + li] = mk(re[ct][vk], im[ct][vk]);
+                    for (int ct = 0; ct < CT; ++ct) {
+                        zd x = mk(re[ct][vk], im[ct][vk]);
+                        if (ct == tb) {
+                            // the pivot block apart; in its place the identity, whose product
+                            // with the inverse gives the pivot columns
+                            if (ep) PB[2 * (lk & 1) + (li & 1)] = x;
+                            x = csel(ep, mk((li & 1) == (lk & 1) ? 1.0 : 0.0, 0.0), x);
+                        }
+                        R0[(lk & 1) * LR + 16 * ct + li] = x;
+                    }
+                }
                 if constexpr (NW == 1)
                     wave_lds_fence();
                 else
                     __syncthreads();
-                const zd a = R0[kk], b = R0[kk + 1], c = R1[kk], dd = R1[kk + 1];
+                const zd a = PB[0], b = PB[1], dd = PB[3];
                 zd r0[CT], r1[CT];
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     r0[ct] = R0[16 * ct + li];
-                    r1[ct] = R1[16 * ct + li];
+                    r1[ct] = R0[LR + 16 * ct + li];
                 }
-                // -A[i][kk], -A[i][kk+1] of row i = 16 rt + li, as the lane's K entry
+                // row i = 16 rt + li of -[A[i][kk] A[i][kk+1]], this lane's K entry of
+                // the real and the imaginary plane; the pivot rows take the rows of
+                // the inverse times the rows themselves (unit entries)
                 const zd ci = R0[(lk >> 1) * LR + 16 * rt + li];
                 const double sg = 16 * rt + li < kk ? 1.0 : -1.0;
                 const bool odd = lk & 1;
-                const double are = sg * (odd ? -ci.y : ci.x);
-                const double aim = sg * (odd ? ci.x : ci.y);
-                // the 2 x 2 pivot block [a b; c d], eliminated in order
-                const double pa = abs2(a);
-                const zd i1 = cinv(a);
-                const zd m = c * i1;
-                const zd p2 = dd - m * b;
-                const double pb = abs2(p2);
-                const zd i2 = cinv(p2);
-                if (!(pa > 1e-300) || !(pb > 1e-300) || !isfinite(pa) || !isfinite(pb)) bad = true;
+                double are = sg * (odd ? -ci.y : ci.x);
+                double aim = sg * (odd ? ci.x : ci.y);
+                // pivot columns and rows start from zero
+                if (strip) {
+                    are = ep ? (lk == 2 * (li & 1) ? 1.0 : 0.0) : are;
+                    aim = ep ? (lk == 2 * (li & 1) + 1 ? 1.0 : 0.0) : aim;
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    // the pivot columns take the columns of the inverse
-                    const bool e0 = ct == tb && li == 2 * q, e1 = ct == tb && li == 2 * q + 1;
-                    const zd x0 = csel(e0, mk(1.0, 0.0), csel(e1, zero, r0[ct]));
-                    const zd x1 = csel(e1, mk(1.0, 0.0), csel(e0, zero, r1[ct]));
-                    const zd w1 = i2 * (x1 - m * x0);
-                    const zd w0 = i1 * (x0 - b * w1);
-                    if (ct == tb) {
-                        const bool ep = e0 || e1;
+                    for (int ct = 0; ct < CT; ++ct) {
+                        re[ct][vk] = mine ? 0.0 : re[ct][vk];
+                        im[ct][vk] = mine ? 0.0 : im[ct][vk];
+                    }
+                }
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+                    if (ct == tb)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             re[ct][v] = ep ? 0.0 : re[ct][v];
                             im[ct][v] = ep ? 0.0 : im[ct][v];
                         }
-                    }
-                    const zd wk = csel(lk < 2, w0, w1);
-                    const double bk = odd ? wk.y : wk.x;
+                // the inverse of the 2 x 2 pivot block [a b; b d], eliminated in order
+                const double pa = abs2(a);
+                const zd i1 = cinv_fast(a, pa);
+                const zd m = b * i1;
+                const zd p2 = dd - m * b;
+                const double pb = abs2(p2);
+                const zd i2 = cinv_fast(p2, pb);
+                const zd p01 = -(m * i2);
+                const zd p00 = i1 - m * p01;
+                if (!(pa > 1e-300) || !(pb > 1e-300) || !isfinite(pa) || !isfinite(pb)) bad = true;
+                // this lane's K entry of the inverse times the rows: re / im of row
+                // kk (lk = 0, 1) or kk + 1 (lk = 2, 3)
+                const zd c0 = csel(lk < 2, p00, p01), c1 = csel(lk < 2, p01, i2);
+                const double f0 = odd ? c0.y : c0.x, f1 = odd ? c0.x : -c0.y;
+                const double f2 = odd ? c1.y : c1.x, f3 = odd ? c1.x : -c1.y;
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    const double bk = fma(f0, r0[ct].x, fma(f1, r0[ct].y, fma(f2, r1[ct].x, f3 * r1[ct].y)));
                     re[ct] = D::mac(are, bk, re[ct]);
                     im[ct] = D::mac(aim, bk, im[ct]);
-                    // the pivot rows
-                    const zd wr = csel(odd, w1, w0);
-                    re[ct][vk] = mine ? wr.x : re[ct][vk];
-                    im[ct][vk] = mine ? wr.y : im[ct][vk];
                 }
             }
         }
@@ -329,13 +367,13 @@ struct FactorClass {
     int blocks;
 };
 template <typename TS, int LX>
-__global__ __launch_bounds__(8 * LX) void factor2d_kernel(const SubDesc* __restrict__ desc,
+__global__ __launch_bounds__(8 * LX) ASP_PLAIN_ACC(2) void factor2d_kernel(const SubDesc* __restrict__ desc,
                                                          FactorClass cm, FactorClass cr, AxisTables ax,
                                                          const zd* __restrict__ subtab,
                                                          const double* __restrict__ ksq, int n,
                                                          cplx<TS>* __restrict__ fac,
                                                          int* __restrict__ flag) {
-    __shared__ zd rows[8 * LX];      // pivot rows [problem][half][parity][2][LR]
+    __shared__ zd rows[8 * LX + 16 * (LX / 16)];   // pivot rows of every problem
     __shared__ zd xch[LX * LX];      // R_{p+1}^-1 of every problem
     const bool ism = (int)blockIdx.x < cm.blocks;
     const FactorClass c = ism ? cm : cr;
@@ -346,7 +384,7 @@ __global__ __launch_bounds__(8 * LX) void factor2d_kernel(const SubDesc* __restr
     const int idx = g * per + slot;
     const bool live = idx < c.count;
     const SubDesc d = desc[c.first + min(idx, c.count - 1)];
-    zd* rb = rows + slot * 8 * c.LR;
+    zd* rb = rows + slot * (8 * c.LR + 16);
     zd* xc = xch + slot * c.LR * c.LR;
     const int wl = w % wpp;
     if (LX == 16 || c.LR == 16)
@@ -644,8 +682,11 @@ struct SolveItem {
     }
 };
 
-template <typename T>
-constexpr int nslot() { return sizeof(T) == 4 ? 3 : 2; }
+// register slots of a step's loads (three measured the same at n = 1023 with
+// twice the registers) and wavefronts per SIMD the registers are held to
+constexpr int NSLOT = 2;
+template <typename T, int LR>
+constexpr int solve_waves() { return LR == 64 ? 1 : sizeof(T) == 4 ? 3 : 2; }
 
 // forward pass of one half: y_s = S^-1 t_s, t_s = g_s - E y_{s-1}.  Every
 // memory operation of the step loop is issued by every lane, from a valid
@@ -653,10 +694,10 @@ constexpr int nslot() { return sizeof(T) == 4 ? 3 : 2; }
 // branch around one: the wait for a load issued some steps ahead then counts
 // exactly the operations issued after it.
 template <typename T, int LR, int INM, bool SPL>
-__global__ __launch_bounds__(4 * LR) void solve2d_fwd_kernel(SolveArgs a) {
+__global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_fwd_kernel(SolveArgs a) {
     static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
     using Tile = BlockTile<T, LR, SPL>;
-    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T>();
+    constexpr int NW = Tile::NW, KS = Tile::KS, NS = NSLOT;
     __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
     const int nchunk = (a.nact + RC - 1) / RC;
     const SolveItem it(a.njobs, nchunk);
@@ -782,11 +823,11 @@ __global__ __launch_bounds__(4 * LR) void solve2d_fwd_kernel(SolveArgs a) {
 // towards the end of the half that start from columns of the diagonal blocks
 // of H^-1 (kind 0) or from the unit vectors at the middle block (kind 2).
 template <typename T, int LR, int INM, bool SPL>
-__global__ __launch_bounds__(4 * LR) void solve2d_bwd_kernel(SolveArgs a) {
+__global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_bwd_kernel(SolveArgs a) {
     static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
     static_assert(4 * LR * 4 <= SINK_ELEMS, "four discard entries per thread");
     using Tile = BlockTile<T, LR, SPL>;
-    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T>();
+    constexpr int NW = Tile::NW, KS = Tile::KS, NS = NSLOT;
     constexpr bool TW = INM == IN_TWIST;
     __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
     extern __shared__ __align__(16) unsigned char dyn[];
