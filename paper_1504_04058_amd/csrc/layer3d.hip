@@ -182,6 +182,33 @@ __device__ __forceinline__ void store_acc(cplx<T>* A, long long ld, int r0, int 
             }
 }
 
+// the transpose of the accumulated tile (r, c) to A(r0 + c, c0 + r): four lanes
+// write 128 contiguous bytes of a column in FP32
+template <typename T>
+__device__ __forceinline__ void store_acc_t(cplx<T>* A, long long ld, int r0, int c0,
+                                            const CTile<T> acc[2][2], T sign) {
+    const int l = lane_id(), w = wave_id();
+    const int R0 = 32 * (w >> 1), C0 = 32 * (w & 1);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int r = R0 + 16 * b + (l & 15);
+            cplx<T>* col = A + (long long)(c0 + r) * ld + r0 + C0 + 16 * a;
+            if constexpr (std::is_same<T, float>::value) {
+                f32x4* q = reinterpret_cast<f32x4*>(col + 4 * (l >> 4));
+                q[0] = f32x4{sign * acc[a][b].re[0], sign * acc[a][b].im[0], sign * acc[a][b].re[1],
+                             sign * acc[a][b].im[1]};
+                q[1] = f32x4{sign * acc[a][b].re[2], sign * acc[a][b].im[2], sign * acc[a][b].re[3],
+                             sign * acc[a][b].im[3]};
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    col[Mfma<T>::row(l, v)] = mk<T>(sign * acc[a][b].re[v], sign * acc[a][b].im[v]);
+            }
+        }
+}
+
 // ---------------------------------------------------------------------------
 // factorization
 // ---------------------------------------------------------------------------
@@ -244,6 +271,21 @@ __global__ __launch_bounds__(256) void form3d_kernel(Form3Args a) {
     A[(long long)c * Bp + r] = ccast<T>(val);
 }
 
+// registers held to what the LDS copies allow in wavefronts per SIMD (four
+// workgroups of a CU in FP32, two in FP64), accumulators in ordinary registers
+#define ASP_GJ_WAVES(T) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+
+// The matrices are complex symmetric, and an in-place elimination without
+// pivoting keeps that up to a sign: after the panels of a set E,
+//   A[C,I] = A[I,C]^T  if both or neither of I, C are in E,
+//   A[C,I] = -A[I,C]^T otherwise.
+// So only the tiles on and above the diagonal are kept up to date (half the
+// trailing updates, half the panel products, half the traffic); a panel's tiles
+// below the diagonal hold its columns -A[I,J] D^-1 for the update, and the pass
+// of a matrix's last panel mirrors what is read from below the diagonal: the
+// eliminated part and, in a front, the Schur complement.
+// 3D n = 63 by nested dissection, FP32: factorization 88.6 -> 62 ms
+// (FP64, n = 39 with thin auxiliary PML: 23.2 -> 13.6 ms).
 struct GjArgs {
     const SubDesc* desc;
     const int* jobs;
@@ -360,10 +402,12 @@ __global__ __launch_bounds__(64 * PVG) void gj_pivot_kernel(GjArgs a) {
     if (threadIdx.x == 0 && bad) *a.flag = 1;
 }
 
-// Panel step of panel jp: row-tile workgroups set A[I,J] = -A[I,J] D^-1,
-// column-tile workgroups keep A[J,C] in Rbuf and set A[J,C] = D^-1 A[J,C].
+// Panel step of panel jp, one workgroup per tile t: R[t] keeps the panel row
+// A[J,t] as it was (below the diagonal: from A[t,J]).  t > jp: A[J,t] = D^-1
+// A[J,t], and the panel column -(A[J,t])^T goes below the diagonal; t < jp:
+// A[t,J] = -A[t,J] D^-1.
 template <typename T>
-__global__ __launch_bounds__(NT) void gj_panel_kernel(GjArgs a) {
+__global__ __launch_bounds__(NT) ASP_GJ_WAVES(T) void gj_panel_kernel(GjArgs a) {
     // the products run over the panel in two halves of 32 through half-size LDS
     // copies (33.5 KB in FP32, 67 KB in FP64 instead of 66.5 and 133)
     __shared__ cplx<T> sP[TB * KLD];
@@ -372,8 +416,7 @@ __global__ __launch_bounds__(NT) void gj_panel_kernel(GjArgs a) {
     const GjMat gm = gj_mat(a, js);
     const int Bp = gm.Bp, nt = Bp / TB;
     if (a.jp >= gm.npiv) return;
-    const bool rowt = (int)blockIdx.x < a.ntmax;
-    const int t = rowt ? blockIdx.x : blockIdx.x - a.ntmax;
+    const int t = blockIdx.x;
     if (t >= nt || t == a.jp) return;
     cplx<T>* A = static_cast<cplx<T>*>(a.fac) + gm.off;
     const int J0 = a.jp * TB;
@@ -386,23 +429,29 @@ __global__ __launch_bounds__(NT) void gj_panel_kernel(GjArgs a) {
     // panel buffers of a front: slots of Bp x 64 entries (rows of J1, rows of
     // J2, columns of J1), column-major with leading dimension 64 / Bp
     const long long slot = (long long)Bp * TB;
-    if (rowt) {
-        // acc = A[t, J] D
+    cplx<T>* R = static_cast<cplx<T>*>(a.Rbuf) + gm.roff + a.rsel * slot;
+    cplx<T>* C2 = static_cast<cplx<T>*>(a.Rbuf) + gm.roff + 2 * slot;   // columns of J1 (save_c)
+    const int rl = threadIdx.x & 31, cg = threadIdx.x >> 5;
+    if (t < a.jp) {
+        // acc = A[t, J] D; R[t] = -A[t, J]^T
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             __syncthreads();
             load_half_cols(sP, A, Bp, t * TB, J0 + (TB / 2) * h);
             load_half_rows(sQ, D, TB, (TB / 2) * h, 0);
             __syncthreads();
+#pragma unroll 4
+            for (int e = 0; e < 8; ++e) {
+                const int c = cg + 8 * e;
+                R[(long long)(t * TB + c) * TB + (TB / 2) * h + rl] = -sP[c * KLD + rl];
+            }
             tile_product<T, TB / 2, KLD, LDT>(sP, sQ, acc);
         }
         store_acc(A, Bp, t * TB, J0, acc, T(-1));
-        if (a.save_c)
-            store_acc(static_cast<cplx<T>*>(a.Rbuf) + gm.roff + 2 * slot, Bp, t * TB, 0, acc, T(-1));
+        if (a.jp == gm.npiv - 1) store_acc_t(A, Bp, J0, t * TB, acc, T(-1));   // mirrored: the last panel
+        if (a.save_c) store_acc(C2, Bp, t * TB, 0, acc, T(-1));
     } else {
-        // acc = D A[J, t]; A[J, t] also goes to the row buffer R
-        cplx<T>* R = static_cast<cplx<T>*>(a.Rbuf) + gm.roff + a.rsel * slot;
-        const int rl = threadIdx.x & 31, cg = threadIdx.x >> 5;
+        // acc = D A[J, t]; R[t] = A[J, t]
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             __syncthreads();
@@ -417,10 +466,25 @@ __global__ __launch_bounds__(NT) void gj_panel_kernel(GjArgs a) {
             tile_product<T, TB / 2, KLD, LDT>(sP, sQ, acc);
         }
         store_acc(A, Bp, J0, t * TB, acc, T(1));
+        store_acc_t(A, Bp, t * TB, J0, acc, T(-1));
+        if (a.save_c) store_acc_t(C2, Bp, t * TB, 0, acc, T(-1));
     }
 }
 
-// Trailing update of panel jp: A[I,C] += A[I,J] R[J,C] for I, C outside the
+// tile (ti, tj), ti <= tj, of index x in the upper triangle
+__device__ __forceinline__ void tri_tile(int x, int& ti, int& tj) {
+    tj = (int)((sqrtf(8.f * x + 1.f) - 1.f) * 0.5f);
+    if (tj * (tj + 1) / 2 > x) --tj;
+    if ((tj + 1) * (tj + 2) / 2 <= x) ++tj;
+    ti = x - tj * (tj + 1) / 2;
+}
+
+// whether the update of the last panel also writes tile (ti, tj) mirrored
+__device__ __forceinline__ bool gj_mirror(const GjArgs& a, const GjMat& gm, int ti, int tj) {
+    return a.jp == gm.npiv - 1 && ti != tj && (ti < gm.npiv) == (tj < gm.npiv);
+}
+
+// Trailing update of panel jp: A[I,C] += A[I,J] R[J,C] for I <= C outside the
 // panel; the pivot tile becomes D^-1.
 // acc += P Q for the trailing update, P = Pm(pr0.., pc0..) (64 x 64, leading
 // dimension pld) and Q = Qm(0.., qc0..) (leading dimension TB), the k range in
@@ -440,7 +504,7 @@ __device__ __forceinline__ void gj_update_product(cplx<T>* sP, cplx<T>* sQ, cons
 }
 
 template <typename T>
-__global__ __launch_bounds__(NT) void gj_update_kernel(GjArgs a) {
+__global__ __launch_bounds__(NT) ASP_GJ_WAVES(T) void gj_update_kernel(GjArgs a) {
     // the products run over the panel in two halves of 32, so that the LDS
     // copies take half a tile each (33.5 KB in FP32, 67 KB in FP64 instead of
     // 66.5 and 133): more workgroups share a CU
@@ -450,8 +514,9 @@ __global__ __launch_bounds__(NT) void gj_update_kernel(GjArgs a) {
     const GjMat gm = gj_mat(a, js);
     const int Bp = gm.Bp, nt = Bp / TB;
     if (a.jp >= gm.npiv) return;
-    const int ti = blockIdx.x % a.ntmax, tj = blockIdx.x / a.ntmax;
-    if (ti >= nt || tj >= nt) return;
+    int ti, tj;
+    tri_tile(blockIdx.x, ti, tj);
+    if (tj >= nt) return;
     cplx<T>* A = static_cast<cplx<T>*>(a.fac) + gm.off;
     const int J0 = a.jp * TB;
     if (tj == a.jp) {
@@ -471,10 +536,6 @@ __global__ __launch_bounds__(NT) void gj_update_kernel(GjArgs a) {
     // column tiles now, the rest with the next panel's update
     const bool narrow = a.mode == GJ_NARROW && a.jp + 1 < gm.npiv;
     if (narrow && ti != a.jp + 1 && tj != a.jp + 1) return;
-    // a front's boundary rows in already eliminated separator columns hold
-    // -F_BI F_II^-1, which nothing reads again (the solves use its transpose
-    // K^T from the separator rows): not updated
-    if (!narrow && a.fr && ti >= gm.npiv && tj < a.jp) return;
     const long long slot = (long long)Bp * TB;
     const cplx<T>* R = static_cast<const cplx<T>*>(a.Rbuf) + gm.roff + a.rsel * slot;
     // the first half's loads are issued before the accumulators', so that its
@@ -497,6 +558,7 @@ __global__ __launch_bounds__(NT) void gj_update_kernel(GjArgs a) {
         gj_update_product(sP, sQ, R1 + 2 * slot, Bp, ti * TB, 0, R1, tj * TB, acc);
     }
     store_acc(A, Bp, ti * TB, tj * TB, acc, T(1));
+    if (gj_mirror(a, gm, ti, tj)) store_acc_t(A, Bp, tj * TB, ti * TB, acc, T(1));
 }
 
 // Trailing update with real-split bf16 products (ASP_PREC_BF16X3): the same
@@ -521,14 +583,15 @@ __device__ __forceinline__ void split_store(SplitPlanes& S, int i, int k, zf v) 
 __device__ __forceinline__ bf16x8 ld8(const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
 
-__global__ __launch_bounds__(NT) void gj_update_bf16x3_kernel(GjArgs a) {
+__global__ __launch_bounds__(NT) ASP_GJ_WAVES(double) void gj_update_bf16x3_kernel(GjArgs a) {
     __shared__ SplitPlanes sP, sQ;   // P[r][k], Q^T[c][k]
     const int js = blockIdx.y;
     const GjMat gm = gj_mat(a, js);
     const int Bp = gm.Bp, nt = Bp / TB;
     if (a.jp >= gm.npiv) return;
-    const int ti = blockIdx.x % a.ntmax, tj = blockIdx.x / a.ntmax;
-    if (ti >= nt || tj >= nt) return;
+    int ti, tj;
+    tri_tile(blockIdx.x, ti, tj);
+    if (tj >= nt) return;
     zf* A = static_cast<zf*>(a.fac) + gm.off;
     const int J0 = a.jp * TB;
     if (tj == a.jp) {
@@ -544,10 +607,6 @@ __global__ __launch_bounds__(NT) void gj_update_bf16x3_kernel(GjArgs a) {
         return;
     }
     if (ti == a.jp) return;
-    // a front's boundary rows in already eliminated separator columns hold
-    // -F_BI F_II^-1, which nothing reads again (the solves use its transpose
-    // K^T from the separator rows): not updated
-    if (a.fr && ti >= gm.npiv && tj < a.jp) return;
     const zf* R = static_cast<const zf*>(a.Rbuf) + gm.roff;
     {
         // P(r, k) = A(ti*64 + r, J0 + k): reads coalesced over r
@@ -601,6 +660,7 @@ __global__ __launch_bounds__(NT) void gj_update_bf16x3_kernel(GjArgs a) {
             }
     }
     store_acc(A, Bp, ti * TB, tj * TB, acc, 1.0f);
+    if (gj_mirror(a, gm, ti, tj)) store_acc_t(A, Bp, tj * TB, ti * TB, acc, 1.0f);
 }
 
 // ---------------------------------------------------------------------------
@@ -897,7 +957,7 @@ namespace {
 constexpr int PIVOT_MANY = 512;
 
 void launch_gj(const asp_plan* P, const GjArgs& a, int njobs, hipStream_t st) {
-    dim3 g0(njobs), g1(2 * a.ntmax, njobs), g2(a.ntmax * a.ntmax, njobs);
+    dim3 g0(njobs), g1(a.ntmax, njobs), g2(a.ntmax * (a.ntmax + 1) / 2, njobs);
     if (P->prec != ASP_PREC_FP64) {
         if (njobs > PIVOT_MANY)
             hipLaunchKernelGGL((gj_pivot_kernel<float, 4>), g0, dim3(256), 0, st, a);

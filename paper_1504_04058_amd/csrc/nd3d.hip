@@ -74,7 +74,8 @@ constexpr int CPW = 16;      // front columns of one assembly / copy-out workgro
 // F(r, c): the symmetric-form couplings of the 7-point operator between the
 // unknowns of rows r and c if one of them is a separator unknown, plus the
 // children's Schur complements on the pairs they share; identity / zero on
-// the padding.  One workgroup per CPW consecutive front columns: what depends
+// the padding; tiles on and above the diagonal only (the elimination reads no
+// others).  One workgroup per CPW consecutive front columns: what depends
 // on a column (its part and line, grid point, the children's columns) is
 // decoded once into LDS, each thread decodes a row once and writes it in all
 // CPW columns (one coalesced row segment per wave and column).
@@ -122,7 +123,9 @@ __global__ __launch_bounds__(NT) void nd_assemble_kernel(AsmArgs a) {
     }
     __syncthreads();
     cplx<T>* out0 = static_cast<cplx<T>*>(a.F) + F.foff + (long long)c0 * F.f;
-    for (int r = threadIdx.x; r < F.f; r += NT) {
+    // tiles on and above the diagonal: the elimination reads no others
+    const int rend = (c0 / 64 + 1) * 64;
+    for (int r = threadIdx.x; r < rend; r += NT) {
         const Part pr = decode(r, F.ipad, nd.nI, nd.nB, L);
         const int k = pr.k;
         const bool live = pr.part < 2;
