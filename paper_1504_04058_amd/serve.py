@@ -12,7 +12,10 @@ server
 * batches continuously: the right-hand sides of all queued requests for a key
   go into the next GMRES call on that key's plan, so requests that arrive while
   the key is busy join the following batch; different keys run concurrently on
-  their own HIP streams from a pool of worker threads;
+  their own HIP streams from a pool of worker threads.  While other keys
+  occupy the device, a request for an idle key waits up to ``JOIN_S`` seconds
+  from its arrival for others of the same key (a solve costs little more with
+  more right-hand sides, and would share the device with the running ones);
 * records arrival, start and completion times, from which p50/p99 latency and
   solves/s follow.
 
@@ -28,6 +31,9 @@ import time
 from typing import Dict, List, Optional
 
 import numpy as np
+
+
+JOIN_S = 0.0015   # about the time of a small solve
 
 
 @dataclasses.dataclass
@@ -221,6 +227,7 @@ class Server:
         self._used = 0              # bytes of resident factors + running workspaces
         self._peak = 0
         self._arrivals_done = False
+        self._wake = 0.05           # longest wait of an idle worker
         self._results: Dict[int, Result] = {}
         self.evictions = 0
         self.factorizations = 0
@@ -258,8 +265,18 @@ class Server:
             res.done = now
 
     # -- scheduling ----------------------------------------------------------------------
+    def _hold(self, e, q):
+        """Seconds for which the queued requests of an idle key still wait for
+        company, 0 if they run now."""
+        if not self.realtime or self._arrivals_done or sum(r.nrhs for r in q) >= self.max_rhs:
+            return 0.0
+        if not any(o.busy or o.creating for o in self._cache.values() if o is not e):
+            return 0.0
+        return q[0].arrival + JOIN_S - (time.perf_counter() - self._t0)
+
     def _pick(self):
         """Next unit of work under the lock: ('create', req) or ('solve', entry, reqs)."""
+        self._wake = 0.05
         for key, q in self._queue.items():
             if not q:
                 continue
@@ -280,6 +297,10 @@ class Server:
                 self._cache[key] = e
                 return ("create", e, req, fw)
             if e.busy or e.creating:
+                continue
+            hold = self._hold(e, q)
+            if hold > 0.0:
+                self._wake = min(self._wake, hold)
                 continue
             batch, total = [], 0
             while q and (not batch or total + q[0].nrhs <= self.max_rhs):
@@ -314,7 +335,7 @@ class Server:
                             not any(e.busy or e.creating for e in self._cache.values()):
                         self._lock.notify_all()
                         return
-                    self._lock.wait(0.05)
+                    self._lock.wait(self._wake)
                     work = self._pick()
             if work[0] == "create":
                 _, e, req, fw = work
