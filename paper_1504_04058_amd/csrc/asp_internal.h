@@ -258,7 +258,8 @@ struct asp_plan {
     int nd_levels = 0;
     std::vector<int> nd_lvl_nodes;            // nodes per level (root: level 0)
     std::vector<long long> nd_lvl_front0;     // first front of each level
-    std::vector<int> nd_lvl_fmax;             // largest front of each level
+    std::vector<int> nd_lvl_fmax;             // largest front of each level,
+    std::vector<int> nd_lvl_imax, nd_lvl_bmax;   // separator part and boundary part
     std::vector<NdNode> nd_nodes;             // level by level
     std::vector<int> nd_node0;                // first node of each level
     std::vector<int> nd_cols, nd_inv;
@@ -576,6 +577,7 @@ struct NdLevel {
     const NdFront* fr_all;   // every front
     long long front0;        // first front of the level
     int nn;                  // nodes in the level
+    int fmax, imax, bmax;    // largest front, separator part, boundary part of the level
     long long child0;        // first front of the next level (children), -1: none
     int nnc;                 // nodes in the next level
 };
@@ -599,7 +601,7 @@ hipError_t launch_nd_input(const asp_plan* P, const int* jobs, int njobs, int in
                            const zd* r, const zd* Win, const int* act, int nact, hipStream_t st);
 // forward (fwd = 1) or backward step over one level for the jobs
 hipError_t launch_nd_level(const asp_plan* P, const NdLevel& lv, const int* jobs, int njobs,
-                           int fwd, int fmax, int nact, hipStream_t st);
+                           int fwd, int nact, hipStream_t st);
 // outputs of the solved slabs on X_p, as launch modes of the block solves
 hipError_t launch_nd_output(const asp_plan* P, const int* jobs, int njobs, bool two_sided,
                             const int out_mode[2], zd* const out[2], const zd* U, zd* Wout,

@@ -113,6 +113,9 @@ NdLevel level_of(const asp_plan* P, int d) {
     const bool last = d + 1 >= P->nd_levels;
     lv.child0 = last ? -1 : P->nd_lvl_front0[d + 1];
     lv.nnc = last ? 0 : P->nd_lvl_nodes[d + 1];
+    lv.fmax = P->nd_lvl_fmax[d];
+    lv.imax = P->nd_lvl_imax[d];
+    lv.bmax = P->nd_lvl_bmax[d];
     return lv;
 }
 
@@ -148,9 +151,9 @@ void solve_cost_nd(const asp_plan* P, int sub, int nact, double* bytes, double* 
 // forward levels (leaves to root), then backward levels (root to leaves)
 asp_status nd_solve(asp_plan* P, const int* jobs, int njobs, int nact) {
     for (int d = P->nd_levels - 1; d >= 0; --d)
-        ASP_HIP(P, launch_nd_level(P, level_of(P, d), jobs, njobs, 1, P->nd_lvl_fmax[d], nact, P->stream));
+        ASP_HIP(P, launch_nd_level(P, level_of(P, d), jobs, njobs, 1, nact, P->stream));
     for (int d = 0; d < P->nd_levels; ++d)
-        ASP_HIP(P, launch_nd_level(P, level_of(P, d), jobs, njobs, 0, P->nd_lvl_fmax[d], nact, P->stream));
+        ASP_HIP(P, launch_nd_level(P, level_of(P, d), jobs, njobs, 0, nact, P->stream));
     return ASP_OK;
 }
 
@@ -250,7 +253,16 @@ asp_status nd_setup(asp_plan* P) {
     P->fac_elems = moff;
     P->fac_bytes = (size_t)moff * esz(P);
     P->nd_lvl_fmax.assign(D, 0);
-    for (int d = 0; d < D; ++d) P->nd_lvl_fmax[d] = level_fmax(P, d, 0, ns);
+    P->nd_lvl_imax.assign(D, 0);
+    P->nd_lvl_bmax.assign(D, 0);
+    for (int d = 0; d < D; ++d) {
+        P->nd_lvl_fmax[d] = level_fmax(P, d, 0, ns);
+        const long long i0 = P->nd_lvl_front0[d];
+        for (long long i = i0; i < i0 + (long long)ns * P->nd_lvl_nodes[d]; ++i) {
+            P->nd_lvl_imax[d] = std::max(P->nd_lvl_imax[d], P->nd_fronts[i].ipad);
+            P->nd_lvl_bmax[d] = std::max(P->nd_lvl_bmax[d], P->nd_fronts[i].f - P->nd_fronts[i].ipad);
+        }
+    }
     P->nd_vtot = voff;
     P->nd_xtot = xoff;
     // factorization groups: problems whose level buffers (two adjacent levels

@@ -18,8 +18,6 @@ namespace {
 
 constexpr int RW = 16;       // right-hand sides per chunk
 constexpr int NT = 256;      // threads of a workgroup
-constexpr int RT = 4;        // 16-row tiles of one product workgroup (64 rows)
-constexpr int NW = 4;        // waves splitting the inner dimension of a product
 constexpr int YMAX = 65535;  // largest grid y
 
 struct Part {
@@ -236,22 +234,29 @@ __global__ __launch_bounds__(NT) void nd_vec_kernel(SolveNdArgs a) {
 }
 
 // Forward (FWD): v_B -= K^T v_I over the boundary rows.  Backward: x_I =
-// F_II^-1 v_I - K x_B into the slab vector.  64 output rows x 16 right-hand
-// sides per workgroup; four waves split the inner dimension in batches of 16
-// (next batch loaded before the current products) and reduce through LDS in a
-// fixed order.
-template <typename T, bool FWD>
-__global__ __launch_bounds__(NT) void nd_prod_kernel(SolveNdArgs a) {
+// F_II^-1 v_I - K x_B into the slab vector.  16 RT output rows x 16 right-hand
+// sides per workgroup; NW waves split the inner dimension in batches of 16, PF
+// batches in flight in fixed register slots, and reduce through LDS in a fixed
+// order.  Two shapes: launches of many row blocks take 64 rows and four waves
+// (the front streamed once, bound by memory); launches of few (the top levels,
+// and every level of a sweep step with its two problems) take 16 rows and
+// sixteen waves, which shortens the chain of batches and fills four times as
+// many compute units.
+template <typename T, bool FWD, int RT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(RT == 4 ? 2 : 4)))
+void nd_prod_kernel(SolveNdArgs a) {
+    constexpr int PF = RT == 1 && sizeof(T) == 4 ? 3 : 2;
     __shared__ cplx<T> red[NW][RT][64][4];
     const int y = a.ybase + blockIdx.y;
     const int j = y / a.nn, pos = y - j * a.nn;
     const int sub = a.jobs[j];
     const NdFront F = a.fr[a.front0 + (long long)sub * a.nn + pos];
     const int rows = FWD ? F.f - F.ipad : F.ipad;
-    const int r0 = blockIdx.x * 64;
+    const int r0 = blockIdx.x * 16 * RT;
     if (r0 >= rows) return;
     const NdNode nd = a.nodes[F.node];
     const int L = F.L;
+    const float rL = 1.0f / (float)L;
     const int inner = FWD ? F.ipad : F.f;
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int li = l & 15, lk = l >> 4;
@@ -267,62 +272,80 @@ __global__ __launch_bounds__(NT) void nd_prod_kernel(SolveNdArgs a) {
     for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e) p1[t][e] = p2[t][e] = p3[t][e] = 0.f;
-    // operands of one batch: A(row, c) for the RT row tiles, the vector at c
-    auto load = [&](int c0, cplx<T> (&m)[RT][4], cplx<T> (&t)[4]) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int c = c0 + 4 * u + lk;
+    struct Batch {
+        cplx<T> m[RT][4], t[4];
+    };
+    // operands of batch b: A(row, c) for the RT row tiles, the vector at c; entry
+    // u of a lane is column 16 b + 4 lk + u, so that the forward product (K
+    // transposed) reads four consecutive entries per lane
+    auto load = [&](Batch& B, int b) {
+        const int cb = 16 * b + 4 * lk;
+        if constexpr (FWD) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
-                const int row = r0 + 16 * rt + li;
-                m[rt][u] = FWD ? M[(long long)(F.ipad + row) * ld + c] : M[(long long)c * ld + row];
+                const cplx<T>* q = M + (long long)(F.ipad + r0 + 16 * rt + li) * ld + cb;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) B.m[rt][u] = q[u];
             }
-            if (FWD || c < F.ipad) {
-                t[u] = v[(long long)c * RW + li];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) B.t[u] = v[(long long)(cb + u) * RW + li];
+        } else {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) B.m[rt][u] = M[(long long)(cb + u) * ld + r0 + 16 * rt + li];
+            if (16 * b < F.ipad) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) B.t[u] = v[(long long)(cb + u) * RW + li];
             } else {
-                const int q = c - F.ipad, b = q / L;
-                const bool in = q < nd.nB * L;
-                const int col = a.cols[nd.b_off + (in ? b : 0)];
-                const cplx<T> xv = x[((long long)col * L + (q - b * L)) * RW + li];
-                t[u] = csel(in, mk<T>(-xv.x, -xv.y), mk<T>(T(0), T(0)));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int q = cb + u - F.ipad;
+                    const int bc = (int)(((float)q + 0.5f) * rL);   // q / L (q < 2^20)
+                    const bool in = bc < nd.nB;
+                    const int col = a.cols[nd.b_off + (in ? bc : 0)];
+                    const cplx<T> xv = x[((long long)col * L + (in ? q - bc * L : 0)) * RW + li];
+                    B.t[u] = csel(in, mk<T>(-xv.x, -xv.y), mk<T>(T(0), T(0)));
+                }
             }
         }
     };
-    const int nb = inner / 16;
-    int b = w;
-    if (b < nb) {
-        cplx<T> mc[RT][4], tc[4], mn[RT][4], tn[4];
-        load(16 * b, mc, tc);
-        for (;;) {
-            const int bn = b + NW;
-            if (bn < nb) load(16 * bn, mn, tn);
-            if constexpr (std::is_same<T, float>::value) {
-                // three-product form: p1 += (m_r + m_i) t_r, p2 += m_r (t_i - t_r),
-                // p3 += m_i (t_r + t_i); re = p1 - p3, im = p1 + p2
+    auto multiply = [&](const Batch& B) {
+        if constexpr (std::is_same<T, float>::value) {
+            // three-product form: p1 += (m_r + m_i) t_r, p2 += m_r (t_i - t_r),
+            // p3 += m_i (t_r + t_i); re = p1 - p3, im = p1 + p2
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float td = tc[u].y - tc[u].x, ts = tc[u].x + tc[u].y;
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        p1[rt] = Mfma<float>::mac(mc[rt][u].x + mc[rt][u].y, tc[u].x, p1[rt]);
-                        p2[rt] = Mfma<float>::mac(mc[rt][u].x, td, p2[rt]);
-                        p3[rt] = Mfma<float>::mac(mc[rt][u].y, ts, p3[rt]);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) cmac(acc[rt], mc[rt][u], tc[u]);
-            }
-            if (bn >= nb) break;
-            // the next batch becomes the current one (register renames)
             for (int u = 0; u < 4; ++u) {
-                tc[u] = tn[u];
+                const float td = B.t[u].y - B.t[u].x, ts = B.t[u].x + B.t[u].y;
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) mc[rt][u] = mn[rt][u];
+                for (int rt = 0; rt < RT; ++rt) {
+                    p1[rt] = Mfma<float>::mac(B.m[rt][u].x + B.m[rt][u].y, B.t[u].x, p1[rt]);
+                    p2[rt] = Mfma<float>::mac(B.m[rt][u].x, td, p2[rt]);
+                    p3[rt] = Mfma<float>::mac(B.m[rt][u].y, ts, p3[rt]);
+                }
             }
-            b = bn;
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) cmac(acc[rt], B.m[rt][u], B.t[u]);
+        }
+    };
+    const int nb = inner / 16;
+    const int nbw = (nb - w + NW - 1) / NW;   // batches w, w + NW, .. of this wave
+    if (nbw > 0) {
+        Batch B[PF];
+#pragma unroll
+        for (int q = 0; q < PF; ++q) load(B[q], w + NW * min(q, nbw - 1));
+        for (int i = 0; i < nbw; i += PF) {
+#pragma unroll
+            for (int q = 0; q < PF; ++q) {
+                if (i + q < nbw) {
+                    multiply(B[q]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (i + q + PF < nbw) load(B[q], w + NW * (i + q + PF));
+                }
+            }
         }
     }
     if constexpr (std::is_same<T, float>::value) {
@@ -339,9 +362,7 @@ __global__ __launch_bounds__(NT) void nd_prod_kernel(SolveNdArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) red[w][rt][l][e] = mk<T>(acc[rt].re[e], acc[rt].im[e]);
     __syncthreads();
-#pragma unroll
-    for (int o = 0; o < RT; ++o) {
-        const int id = threadIdx.x + NT * o;   // (rt, lane, element)
+    for (int id = threadIdx.x; id < 256 * RT; id += 64 * NW) {   // (rt, lane, element)
         const int e = id & 3, l2 = (id >> 2) & 63, rt = id >> 8;
         cplx<T> s = red[0][rt][l2][e];
 #pragma unroll
@@ -508,8 +529,33 @@ hipError_t launch_nd_copyout(const asp_plan* P, const NdFront* fr, int nfr, cons
     return hipGetLastError();
 }
 
+// Shape of a product launch over ny fronts of at most `rows` output rows and
+// `inner` columns: with enough row blocks of 64 to fill the chip a few times
+// over the wide shape (each front streamed once); below that 16 rows per
+// workgroup, sixteen waves where the inner dimension gives each at least two
+// batches and all workgroups fit the chip at once, else four.  3D n = 63, two
+// problems per sweep step, backward: 16 fronts of 1152 columns 24 -> 12 us
+// (64 rows and four waves against 16 and sixteen), 128 fronts of 640 columns 32
+// -> 21 us (four waves), 3328 leaf fronts (the M problems) 593 against 505 us
+// with the wide shape.  The counts leave out the chunks of right-hand sides, so
+// that a right-hand side's result does not depend on the batch.
+constexpr long long ND_WIDE = 1024, ND_FEW = 512;
+constexpr int ND_DEEP = 512;
+
+template <typename T, bool FWD>
+static void launch_nd_prod(const SolveNdArgs& a, int rows, int inner, int ny, unsigned gy, int chunks,
+                           hipStream_t st) {
+    if (rows <= 0) return;   // the root has no boundary part
+    if ((long long)ny * ((rows + 63) / 64) >= ND_WIDE)
+        hipLaunchKernelGGL((nd_prod_kernel<T, FWD, 4, 4>), dim3((rows + 63) / 64, gy, chunks), dim3(256), 0, st, a);
+    else if (inner >= ND_DEEP && (long long)ny * ((rows + 15) / 16) <= ND_FEW)
+        hipLaunchKernelGGL((nd_prod_kernel<T, FWD, 1, 16>), dim3((rows + 15) / 16, gy, chunks), dim3(1024), 0, st, a);
+    else
+        hipLaunchKernelGGL((nd_prod_kernel<T, FWD, 1, 4>), dim3((rows + 15) / 16, gy, chunks), dim3(256), 0, st, a);
+}
+
 hipError_t launch_nd_level(const asp_plan* P, const NdLevel& lv, const int* jobs, int njobs,
-                           int fwd, int fmax, int nact, hipStream_t st) {
+                           int fwd, int nact, hipStream_t st) {
     SolveNdArgs a;
     a.fr = lv.fr_all;
     a.nodes = P->d_nd_nodes;
@@ -533,21 +579,18 @@ hipError_t launch_nd_level(const asp_plan* P, const NdLevel& lv, const int* jobs
         a.ybase = y0;
         const unsigned gy = (unsigned)std::min(YMAX, ny - y0);
         if (fwd) {
-            dim3 gv((unsigned)(((long long)fmax * RW + NT - 1) / NT), gy, chunks);
-            dim3 gp((unsigned)((fmax + 63) / 64), gy, chunks);
+            dim3 gv((unsigned)(((long long)lv.fmax * RW + NT - 1) / NT), gy, chunks);
             if (f32) {
                 hipLaunchKernelGGL(nd_vec_kernel<float>, gv, dim3(NT), 0, st, a);
-                hipLaunchKernelGGL((nd_prod_kernel<float, true>), gp, dim3(NT), 0, st, a);
+                launch_nd_prod<float, true>(a, lv.bmax, lv.imax, ny, gy, chunks, st);
             } else {
                 hipLaunchKernelGGL(nd_vec_kernel<double>, gv, dim3(NT), 0, st, a);
-                hipLaunchKernelGGL((nd_prod_kernel<double, true>), gp, dim3(NT), 0, st, a);
+                launch_nd_prod<double, true>(a, lv.bmax, lv.imax, ny, gy, chunks, st);
             }
+        } else if (f32) {
+            launch_nd_prod<float, false>(a, lv.imax, lv.fmax, ny, gy, chunks, st);
         } else {
-            dim3 gp((unsigned)((fmax + 63) / 64), gy, chunks);
-            if (f32)
-                hipLaunchKernelGGL((nd_prod_kernel<float, false>), gp, dim3(NT), 0, st, a);
-            else
-                hipLaunchKernelGGL((nd_prod_kernel<double, false>), gp, dim3(NT), 0, st, a);
+            launch_nd_prod<double, false>(a, lv.imax, lv.fmax, ny, gy, chunks, st);
         }
     }
     return hipGetLastError();
