@@ -1215,12 +1215,21 @@ struct SweepArgs {
 
 
 constexpr int SW_ROWS = 16;    // output rows (i1) per block: one matrix-core tile
-constexpr int SW_RT = 32;      // right-hand sides per block: two tiles
-constexpr int SW_W = 8;        // wavefronts per block, splitting the columns of T
+// One tile of right-hand sides per block while all blocks fit the CUs at once,
+// else two (each column of T then serves two); four wavefronts up to 192
+// columns, else eight.  A step's products take 2 x 16 x 16 columns of the FP64
+// (FP32) matrix cores per batch and wavefront, so an empty or half-filled
+// second tile is pure latency: per step at n = 150, 3 right-hand sides, FP64
+// 8.7 -> 5.4 us (5.8 with eight wavefronts), n = 511, 8, FP32 8.3 -> 7.1 (8.6
+// with four), n = 700, 24, FP64 18.4 -> 12.5; n = 1023, 64 (two tiles) 14.3.
+// The number of wavefronts depends on n alone: a right-hand side's sums are the
+// same in any batch.
+constexpr int SW_ONE_TILE = 256, SW_FEW_COLUMNS = 192;
+constexpr int SW_RT = 32;      // the slot count is a multiple of two tiles
 
-// W_out = T W_in for 16 outputs i1 and 32 right-hand sides: a complex product
-// on the matrix cores.  Each wavefront takes a contiguous eighth of the
-// columns of T in batches of 16 (four k-steps); two batches sit in two fixed
+// W_out = T W_in for 16 outputs i1 and NT tiles of 16 right-hand sides: a
+// complex product on the matrix cores.  Each of NWV wavefronts takes a
+// contiguous share of the columns of T in batches of 16 (four k-steps); two batches sit in two fixed
 // register slots, and a slot is refilled right after its products, so one
 // batch is in flight while the other is multiplied.  Every load is issued
 // (columns past the wavefront's range read its last column again) and the
@@ -1229,15 +1238,15 @@ constexpr int SW_W = 8;        // wavefronts per block, splitting the columns of
 // LDS and are added in wavefront order (fixed, so a result does not depend on
 // the other right-hand sides or on scheduling).  The two blocks of a row tile
 // are 64 block ids apart and so share an XCD and its L2 copy of T.
-template <typename T, bool SPL = false>
-__global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
-    __shared__ cplx<T> red[SW_W][2][64][4];
+template <typename T, bool SPL, int NT, int NWV>
+__global__ __launch_bounds__(64 * NWV) ASP_PLAIN_ACC(2) void sweep_step_kernel(SweepArgs a) {
+    __shared__ cplx<T> red[NWV][NT][64][4];
     const int side = blockIdx.z;
     const int n = a.n;
     const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int li = l & 15, lk = l >> 4;
     const int k0 = blockIdx.x * SW_ROWS;
-    const int s0 = blockIdx.y * SW_RT;
+    const int s0 = blockIdx.y * 16 * NT;
     if (s0 >= a.nact) return;
     const cplx<T>* __restrict__ Tm = reinterpret_cast<const cplx<T>*>(a.T) + a.t_off[side];
     const cplx<T>* __restrict__ Wi = reinterpret_cast<const cplx<T>*>(a.Wt_in[side]);
@@ -1245,30 +1254,43 @@ __global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
     // this block's 16 rows of T: one contiguous run of row-tile blockIdx.x (rows
     // past n are padding, their outputs are not stored)
     const cplx<T>* __restrict__ Tt = Tm + (long long)blockIdx.x * n * 16 + li;
-    const int per = (n + 16 * SW_W - 1) / (16 * SW_W) * 16;
+    const int per = (n + 16 * NWV - 1) / (16 * NWV) * 16;
     const int cb = wv * per, ce = min(cb + per, n);
-    // one output per thread (tile t2o, lane l2, element v_); its u~ value is
+    // OPT outputs per thread (tile t2, lane l2, element v); their u~ values are
     // read now, ahead of the products.  Column li of tile t2 is right-hand side
-    // 2 li + t2, so that a lane's two right-hand sides of a column of W are
+    // NT li + t2, so that a lane's two right-hand sides of a column of W are
     // adjacent (one 16-byte load in FP32).
-    const int tid = threadIdx.x;
-    const int v_ = tid & 3, l2 = (tid >> 2) & 63, t2o = tid >> 8;
-    const int ko = k0 + Mfma<T>::row(l2, v_);
-    const int slot = s0 + 2 * (l2 & 15) + t2o;
-    const bool okout = ko < n && slot < a.nact;
-    const int id = okout ? (a.act ? a.act[slot] : slot) : 0;
-    const zd uval = a.Ugrid[(long long)id * a.N + (long long)n * (a.line[side] - 1) + (okout ? ko : 0)];
+    constexpr int OPT = (256 * NT + 64 * NWV - 1) / (64 * NWV);
+    struct Out {
+        int t2, l2, v, k, slot, id;
+        bool ok;
+        zd u;
+    } out[OPT];
+#pragma unroll
+    for (int o = 0; o < OPT; ++o) {
+        Out& q = out[o];
+        const int t = threadIdx.x + 64 * NWV * o;
+        q.v = t & 3;
+        q.l2 = (t >> 2) & 63;
+        q.t2 = min(t >> 8, NT - 1);
+        q.k = k0 + Mfma<T>::row(q.l2, q.v);
+        q.slot = s0 + NT * (q.l2 & 15) + q.t2;
+        q.ok = t < 256 * NT && q.k < n && q.slot < a.nact;
+        q.id = q.ok ? (a.act ? a.act[q.slot] : q.slot) : 0;
+        q.u = a.Ugrid[(long long)q.id * a.N + (long long)n * (a.line[side] - 1) + (q.ok ? q.k : 0)];
+    }
     // FP32: three real products per complex one (p1 = (ar + ai) br,
     // p2 = ar (bi - br), p3 = ai (br + bi); re = p1 - p3, im = p1 + p2), the
     // matrix-core work of the step down by a quarter; FP64: the four products
-    KTile3 kacc[2];
-    CTile<T> acc[2];
-    acc[0].zero();
-    acc[1].zero();
-    kacc[0].zero();
-    kacc[1].zero();
+    KTile3 kacc[NT];
+    CTile<T> acc[NT];
+#pragma unroll
+    for (int t2 = 0; t2 < NT; ++t2) {
+        acc[t2].zero();
+        kacc[t2].zero();
+    }
     struct Batch {
-        cplx<T> av[4], bv[4][2];
+        cplx<T> av[4], bv[4][NT];
         bool ok[4];
     };
     auto load = [&](Batch& B, int c0) {
@@ -1278,7 +1300,7 @@ __global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
             const int cc = min(c, ce - 1);
             B.av[u] = Tt[(long long)cc * 16];
 #pragma unroll
-            for (int t2 = 0; t2 < 2; ++t2) B.bv[u][t2] = Wi[(long long)cc * ws + s0 + 2 * li + t2];
+            for (int t2 = 0; t2 < NT; ++t2) B.bv[u][t2] = Wi[(long long)cc * ws + s0 + NT * li + t2];
             B.ok[u] = c < ce;
         }
     };
@@ -1287,7 +1309,7 @@ __global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
         for (int u = 0; u < 4; ++u) {
             const cplx<T> av = csel(B.ok[u], B.av[u], mk<T>(T(0), T(0)));
 #pragma unroll
-            for (int t2 = 0; t2 < 2; ++t2) {
+            for (int t2 = 0; t2 < NT; ++t2) {
                 if constexpr (sizeof(T) == 4)
                     kmac3(kacc[t2], av, B.bv[u][t2]);
                 else
@@ -1300,7 +1322,7 @@ __global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
     auto multiply_split = [&](const Batch& B0, const Batch& B1) {
         if constexpr (SPL) {
 #pragma unroll
-            for (int t2 = 0; t2 < 2; ++t2) {
+            for (int t2 = 0; t2 < NT; ++t2) {
                 float ar[8], ai[8], br[8], bi[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -1333,6 +1355,8 @@ __global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
             __builtin_amdgcn_sched_barrier(0);
             load(b0, c0 + 32);
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NT == 1)
+                if (c0 + 16 >= cb + per) break;
             multiply(b1);
             __builtin_amdgcn_sched_barrier(0);
             load(b1, c0 + 48);
@@ -1341,7 +1365,7 @@ __global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
     }
     if constexpr (sizeof(T) == 4 && !SPL) {
 #pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2)
+        for (int t2 = 0; t2 < NT; ++t2)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 acc[t2].re[v] = kacc[t2].p1[v] - kacc[t2].p3[v];
@@ -1349,17 +1373,21 @@ __global__ __launch_bounds__(64 * SW_W) void sweep_step_kernel(SweepArgs a) {
             }
     }
 #pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2)
+    for (int t2 = 0; t2 < NT; ++t2)
 #pragma unroll
         for (int v = 0; v < 4; ++v) red[wv][t2][l][v] = mk<T>(acc[t2].re[v], acc[t2].im[v]);
     __syncthreads();
-    if (!okout) return;
-    cplx<T> sum = red[0][t2o][l2][v_];
 #pragma unroll
-    for (int q = 1; q < SW_W; ++q) sum = sum + red[q][t2o][l2][v_];
-    const zd val = ccast<double>(sum) + uval;
-    a.W[a.w_out[side] + (long long)id * n + ko] = val;
-    reinterpret_cast<cplx<T>*>(a.Wt_out[side])[(long long)ko * ws + slot] = ccast<T>(val);
+    for (int o = 0; o < OPT; ++o) {
+        const Out& q = out[o];
+        if (!q.ok) continue;
+        cplx<T> sum = red[0][q.t2][q.l2][q.v];
+#pragma unroll
+        for (int w = 1; w < NWV; ++w) sum = sum + red[w][q.t2][q.l2][q.v];
+        const zd val = ccast<double>(sum) + q.u;
+        a.W[a.w_out[side] + (long long)q.id * n + q.k] = val;
+        reinterpret_cast<cplx<T>*>(a.Wt_out[side])[(long long)q.k * ws + q.slot] = ccast<T>(val);
+    }
 }
 
 // W rows of the first sweep step: u~_{1,1} on the last line of X_1 (right-going)
@@ -1614,6 +1642,21 @@ hipError_t launch_sweep_seed(const asp_plan* P, zd* W, long long outR, long long
     return hipGetLastError();
 }
 
+template <typename T, bool SPL, int NWV>
+static void launch_sweep_w(const SweepArgs& a, hipStream_t st) {
+    const int tiles = (a.n + SW_ROWS - 1) / SW_ROWS, ct = (a.nact + 15) / 16;
+    if (2 * tiles * ct <= SW_ONE_TILE)
+        hipLaunchKernelGGL((sweep_step_kernel<T, SPL, 1, NWV>), dim3(tiles, ct, 2), dim3(64 * NWV), 0, st, a);
+    else
+        hipLaunchKernelGGL((sweep_step_kernel<T, SPL, 2, NWV>), dim3(tiles, (ct + 1) / 2, 2), dim3(64 * NWV), 0, st, a);
+}
+
+template <typename T, bool SPL>
+static void launch_sweep_t(const SweepArgs& a, hipStream_t st) {
+    if (a.n <= SW_FEW_COLUMNS) launch_sweep_w<T, SPL, 4>(a, st);
+    else launch_sweep_w<T, SPL, 8>(a, st);
+}
+
 hipError_t launch_sweep_step(const asp_plan* P, int t, zd* W, int w_rhs, const int* act, int nact,
                              hipStream_t st) {
     // step t moves the right-going sweep from layer p = t+1 to p+1 and the
@@ -1642,12 +1685,8 @@ hipError_t launch_sweep_step(const asp_plan* P, int t, zd* W, int w_rhs, const i
     a.ws = ws;
     a.n = P->n;
     a.N = P->N;
-    dim3 grid((P->n + SW_ROWS - 1) / SW_ROWS, ws / SW_RT, 2);
-    if (P->prec == ASP_PREC_BF16X3)
-        hipLaunchKernelGGL((sweep_step_kernel<float, true>), grid, dim3(64 * SW_W), 0, st, a);
-    else if (P->prec != ASP_PREC_FP64)
-        hipLaunchKernelGGL(sweep_step_kernel<float>, grid, dim3(64 * SW_W), 0, st, a);
-    else
-        hipLaunchKernelGGL(sweep_step_kernel<double>, grid, dim3(64 * SW_W), 0, st, a);
+    if (P->prec == ASP_PREC_BF16X3) launch_sweep_t<float, true>(a, st);
+    else if (P->prec != ASP_PREC_FP64) launch_sweep_t<float, false>(a, st);
+    else launch_sweep_t<double, false>(a, st);
     return hipGetLastError();
 }
