@@ -25,32 +25,20 @@ void dev_free(void* p) {
     devmem_free(p);
 }
 
-// workgroups of a solve launch per problem of LR rows over `nact` right-hand sides
-int groups_of(int nact, int LR) {
-    const int srb = solve_rhs_per_block(LR);
-    return (nact + srb - 1) / srb;
-}
+// elements of one slot-fastest vector of an apply over nrhs right-hand sides
+size_t vec2_elems(const asp_plan* P, int nrhs) { return (size_t)nrhs * P->N; }
 
-// workgroups of the layer solves of one apply over nrhs right-hand sides: the
-// M-solves, then the R and L solves in one launch
-long long apply_groups(const asp_plan* P, int nrhs) {
-    return std::max((long long)P->m * groups_of(nrhs, P->LR_M),
-                    (long long)std::max(2 * P->m - 2, 1) * groups_of(nrhs, P->LR_RL));
-}
-
-// forward-substitution scratch for at least `waves` workgroups
-asp_status ensure_y(asp_plan* P, long long waves) {
-    if (waves <= P->y_waves) return ASP_OK;
-    ASP_HIP(P, hipStreamSynchronize(P->stream));
-    dev_free(P->d_y);
-    P->d_y = nullptr;
-    P->y_waves = 0;
-    char* y = nullptr;
-    if (dev_alloc(P, &y, (size_t)waves * solve_scratch_per_block(P) * elem_bytes(P)) != ASP_OK)
-        return ASP_ERR_OOM;
-    P->d_y = y;
-    P->y_waves = waves;
-    return ASP_OK;
+// the vectors of an apply over nact right-hand sides in the plan's workspace
+Apply2 apply2_of(const asp_plan* P, int nact) {
+    Apply2 v;
+    char* b = reinterpret_cast<char*>(P->d_U);
+    const size_t len = vec2_elems(P, P->ws_rhs) * elem_bytes(P);
+    v.R = v.A = b;
+    v.U = b + len;
+    v.C = b + 2 * len;
+    v.W = P->d_W;
+    v.nact = nact;
+    return v;
 }
 
 // algorithmic bytes and flops of a batch of layer solves: each factor entry
@@ -69,10 +57,8 @@ void solve_cost(const asp_plan* P, int sub0, int nsub, int nact, double io_vecto
 
 }  // namespace
 
-long long apply_scratch_groups(const asp_plan* P, int nrhs) { return apply_groups(P, nrhs); }
-
 size_t solve_scratch_bytes(const asp_plan* P) {
-    return (size_t)P->y_waves * solve_scratch_per_block(P) * elem_bytes(P);
+    return P->dim == 2 ? (size_t)P->y_elems * elem_bytes(P) : 0;
 }
 
 size_t factor_work_estimate(const asp_plan* P) {
@@ -154,69 +140,68 @@ extern "C" asp_status asp_timing_read(asp_plan* P, int cls, int* launches, doubl
 asp_status ensure_apply_ws(asp_plan* P, int nrhs) {
     if (P->dim == 3)
         return P->rec ? rec_ensure_ws(P, nrhs) : P->nd ? nd_ensure_ws(P, nrhs) : ensure_apply_ws3(P, nrhs);
+    nrhs = std::min(nrhs, apply_max_rhs(P));   // an apply runs in passes of at most that many
     if (nrhs <= P->ws_rhs) return ASP_OK;
     ASP_HIP(P, hipStreamSynchronize(P->stream));
     dev_free(P->d_U);
     dev_free(P->d_W);
-    dev_free(P->d_stage);
     dev_free(P->d_wt);
-    P->d_U = P->d_W = P->d_stage = nullptr;
-    P->d_wt = nullptr;
-    P->wt_elems = 0;
+    dev_free(P->d_y);
+    P->d_U = P->d_W = nullptr;
+    P->d_wt = P->d_y = nullptr;
+    P->wt_elems = P->y_elems = 0;
     P->ws_rhs = 0;
     P->ws_bytes = 0;
-    const size_t vec = (size_t)nrhs * P->N;
+    const size_t esz = elem_bytes(P);
+    const size_t vec = 3 * vec2_elems(P, nrhs) * esz;
     const size_t wlen = (size_t)std::max(2 * P->m - 2, 1) * nrhs * P->n;
-    if (dev_alloc(P, &P->d_U, vec) != ASP_OK) return ASP_ERR_OOM;
+    const long long we = sweep_wt_len(P, nrhs), ye = solve_scratch_elems(P, nrhs);
+    char* bufs[3] = {nullptr, nullptr, nullptr};
+    const size_t bytes[3] = {vec, (size_t)we * esz, (size_t)ye * esz};
+    for (int i = 0; i < 3; ++i)
+        if (dev_alloc(P, &bufs[i], bytes[i]) != ASP_OK) {
+            for (char* b : bufs) dev_free(b);
+            return ASP_ERR_OOM;
+        }
+    P->d_U = reinterpret_cast<zd*>(bufs[0]);
+    P->d_wt = bufs[1];
+    P->wt_elems = we;
+    P->d_y = bufs[2];
+    P->y_elems = ye;
     if (dev_alloc(P, &P->d_W, wlen) != ASP_OK) return ASP_ERR_OOM;
-    if (dev_alloc(P, &P->d_stage, vec) != ASP_OK) return ASP_ERR_OOM;
-    {
-        const long long we = sweep_wt_len(P, nrhs);
-        char* wt = nullptr;
-        if (dev_alloc(P, &wt, (size_t)we * elem_bytes(P)) != ASP_OK) return ASP_ERR_OOM;
-        P->d_wt = wt;
-        P->wt_elems = we;
-    }
-    asp_status s = ensure_y(P, apply_groups(P, nrhs));
-    if (s != ASP_OK) return s;
     P->ws_rhs = nrhs;
-    P->ws_bytes = (2 * vec + wlen) * sizeof(zd) + (size_t)P->wt_elems * elem_bytes(P);
+    P->ws_bytes = vec + wlen * sizeof(zd) + (size_t)we * esz;
     return ASP_OK;
 }
 
 // ---------------------------------------------------------------------------
 // apply (Algorithm 2)
 // ---------------------------------------------------------------------------
-// z = M^-1 r for the right-hand-side ids act[0..nact) (device list, NULL for
-// 0..nact-1) of batches laid out with stride N.
-asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int nact) {
-    if (P->dim == 3)
-        return P->rec ? rec_apply(P, r, z, act, nact)
-                      : P->nd ? nd_apply(P, r, z, act, nact) : apply3d_internal(P, r, z, act, nact);
+// One pass of a 2D apply over the right-hand sides act[0..nact) (NULL: id0 ..).
+static asp_status apply_pass2d(asp_plan* P, const zd* r, zd* z, const int* act, int id0, int nact) {
     hipStream_t st = P->stream;
     const int m = P->m;
-    const int w_rhs = P->ws_rhs;
+    const Apply2 v = apply2_of(P, nact);
     double by, fl;
     // u~_{q,q} = G~^M_q f_q for q = 1..m, all at once
     {
         SolveLaunch L;
         L.job0 = 0;
         L.njobs = m;
-        L.act = act;
         L.nact = nact;
         L.in_mode = IN_GRID;
-        L.r = r;
-        L.out = (m == 1) ? z : P->d_U;
+        L.r = v.R;
+        L.out = v.U;
         solve_cost(P, 0, m, nact, 2.0, &by, &fl);
         KTimer t(P, ASP_K_SOLVE_M, by, fl);
+        ASP_HIP(P, launch_pack2d(P, v, r, P->N, 1, P->n, 0, act, id0, st));
         ASP_HIP(P, launch_solve2d(P, L, st));
         t.end();
     }
-    if (m == 1) return ASP_OK;
-    if (P->sweep_seq) {
+    if (m > 1 && P->sweep_seq) {
         // Algorithm 2 as stated: R_{t+1} and L_{m-t} solved in step t (one launch),
         // each handing its outgoing boundary line (plus u~) to the next problem of
-        // its sweep; R outputs a_p in z, L outputs c_p in the staging grid
+        // its sweep; R outputs a_p in A, L outputs c_p in C
         double sb = 0, sf = 0;
         for (int t = 1; t <= m - 1; ++t) {
             double b1, f1;
@@ -228,78 +213,74 @@ asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int n
             sf += f1;
         }
         KTimer t(P, ASP_K_SWEEP, sb, sf, 1 + (m - 1) + (m - 2));
-        const long long rowR = (long long)P->wrow(P->idx_R(2)) * w_rhs * P->n;
-        const long long rowL = (long long)P->wrow(P->idx_L(m - 1)) * w_rhs * P->n;
-        ASP_HIP(P, launch_sweep_seed(P, P->d_W, rowR, rowL, act, nact, st));
+        ASP_HIP(P, launch_sweep_seed(P, v, P->wrow(P->idx_R(2)), P->wrow(P->idx_L(m - 1)), st));
         const int nsub = (int)P->subs.size();
         for (int s = 1; s <= m - 1; ++s) {
             SolveLaunch L;
             L.job0 = nsub + 2 * (s - 1);
             L.njobs = 2;
             L.rl = true;
-            L.act = act;
             L.nact = nact;
             L.in_mode = IN_BOUNDARY;
-            L.out = z;
-            L.out_L = P->d_stage;
-            L.W = P->d_W;
-            L.w_rhs = w_rhs;
+            L.out = v.A;
+            L.out_L = v.C;
+            L.W = v.W;
             ASP_HIP(P, launch_solve2d(P, L, st));
             if (s < m - 1)
-                ASP_HIP(P, launch_sweep_hand(
-                               P, z, P->d_stage, P->d_W,
-                               (long long)P->wrow(P->idx_R(s + 2)) * w_rhs * P->n, P->X[s][1],
-                               (long long)P->wrow(P->idx_L(m - s - 1)) * w_rhs * P->n,
-                               P->X[m - s - 1][0], act, nact, st));
+                ASP_HIP(P, launch_sweep_hand(P, v, P->wrow(P->idx_R(s + 2)), P->X[s][1],
+                                             P->wrow(P->idx_L(m - s - 1)), P->X[m - s - 1][0], st));
         }
         t.end();
-        KTimer tc(P, ASP_K_COMBINE, 5.0 * nact * (double)P->N * sizeof(zd), 0.0);
-        ASP_HIP(P, launch_combine3d(P, z, P->d_U, P->d_stage, P->X[0][1], P->X[m - 2][1], true,
-                                    act, nact, st));
-        tc.end();
-        return ASP_OK;
-    }
-    // the two sweeps: the boundary values u~^R_{p,1:p} and u~^L_{p,p:m}
-    // accumulated layer by layer (W rows hold the data entering R_p / L_p); the
-    // seed and the m-2 steps are timed as one span of m-1 launches
-    {
-        const double esz = elem_bytes(P);
-        const double nn = (double)P->n * P->n;
-        const double steps = m - 2;
-        KTimer t(P, ASP_K_SWEEP,
-                 4.0 * nact * P->n * sizeof(zd) + steps * (2.0 * nn * esz + 6.0 * nact * P->n * sizeof(zd)),
-                 steps * 2.0 * nn * nact * 8.0, m - 1);
-        const long long rowR = (long long)P->wrow(P->idx_R(2)) * w_rhs * P->n;
-        const long long rowL = (long long)P->wrow(P->idx_L(m - 1)) * w_rhs * P->n;
-        ASP_HIP(P, launch_sweep_seed(P, P->d_W, rowR, rowL, act, nact, st));
-        for (int s = 1; s <= m - 2; ++s) ASP_HIP(P, launch_sweep_step(P, s, P->d_W, w_rhs, act, nact, st));
-        t.end();
-    }
-    // u~_p = u~_{p,1:p-1} + u~_{p,p} + u~_{p,p+1:m}: one launch of every R_p
-    // (z = a on X_p, p > 1) and L_p (c into the staging grid), then
-    // z = U + c on X_1, z += U + c on X_p (1 < p < m) and z += U on X_m
-    {
+    } else if (m > 1) {
+        // the two sweeps: the boundary values u~^R_{p,1:p} and u~^L_{p,p:m}
+        // accumulated layer by layer (W rows hold the data entering R_p / L_p); the
+        // seed and the m-2 steps are timed as one span of m-1 launches
+        {
+            const double esz = elem_bytes(P);
+            const double nn = (double)P->n * P->n;
+            const double steps = m - 2;
+            KTimer t(P, ASP_K_SWEEP,
+                     4.0 * nact * P->n * sizeof(zd) + steps * (2.0 * nn * esz + 6.0 * nact * P->n * sizeof(zd)),
+                     steps * 2.0 * nn * nact * 8.0, m - 1);
+            ASP_HIP(P, launch_sweep_seed(P, v, P->wrow(P->idx_R(2)), P->wrow(P->idx_L(m - 1)), st));
+            for (int s = 1; s <= m - 2; ++s) ASP_HIP(P, launch_sweep_step(P, v, s, st));
+            t.end();
+        }
+        // one launch of every R_p (a on X_p, p > 1) and L_p (c, p < m)
         SolveLaunch L;
         L.job0 = P->idx_R(2);
         L.njobs = 2 * m - 2;
         L.rl = true;
-        L.act = act;
         L.nact = nact;
         L.in_mode = IN_BOUNDARY;
-        L.out = z;
-        L.out_L = P->d_stage;
-        L.W = P->d_W;
-        L.w_rhs = w_rhs;
+        L.out = v.A;
+        L.out_L = v.C;
+        L.W = v.W;
         solve_cost(P, L.job0, 2 * m - 2, nact, 2.0, &by, &fl);
         KTimer t(P, ASP_K_SOLVE_RL, by, fl);
         ASP_HIP(P, launch_solve2d(P, L, st));
         t.end();
     }
+    // u~_p = u~_{p,1:p-1} + u~_{p,p} + u~_{p,p+1:m}
     {
         KTimer t(P, ASP_K_COMBINE, 5.0 * nact * (double)P->N * sizeof(zd), 0.0);
-        ASP_HIP(P, launch_combine3d(P, z, P->d_U, P->d_stage, P->X[0][1], P->X[m - 2][1], true,
-                                    act, nact, st));
+        ASP_HIP(P, launch_unpack2d(P, v, v.U, m > 1 ? v.A : nullptr, m > 1 ? v.C : nullptr, P->X[0][1] + 1,
+                                   m > 1 ? P->X[m - 2][1] : 0, z, P->N, 1, P->n, 0, act, id0, st));
         t.end();
+    }
+    return ASP_OK;
+}
+
+// z = M^-1 r for the right-hand-side ids act[0..nact) (device list, NULL for
+// 0..nact-1) of batches laid out with stride N.
+asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int nact) {
+    if (P->dim == 3)
+        return P->rec ? rec_apply(P, r, z, act, nact)
+                      : P->nd ? nd_apply(P, r, z, act, nact) : apply3d_internal(P, r, z, act, nact);
+    // passes of as many right-hand sides as the workspace holds
+    for (int s0 = 0; s0 < nact; s0 += P->ws_rhs) {
+        const asp_status s = apply_pass2d(P, r, z, act ? act + s0 : nullptr, s0, std::min(nact - s0, P->ws_rhs));
+        if (s != ASP_OK) return s;
     }
     return ASP_OK;
 }
@@ -464,31 +445,30 @@ extern "C" asp_status asp_subsolve(asp_plan* P, int kind, int p, const void* in,
                       : P->nd ? nd_subsolve(P, idx, in, out, nrhs) : subsolve3d(P, idx, in, out, nrhs);
     const SubDesc& d = P->subs[idx];
     hipStream_t st = P->stream;
-    const size_t row = sizeof(zd);
-    const long long Np = P->S * (d.xe - d.xs + 1);
-    SolveLaunch L;
-    L.job0 = idx;
-    L.njobs = 1;
-    L.rl = kind != ASP_SUB_M;
-    L.nact = nrhs;
-    L.out = P->d_stage;
-    if (kind == ASP_SUB_M) {
-        // y on X_p into a grid-shaped copy of the input
-        ASP_HIP(P, hipMemcpy2DAsync(P->d_U + (long long)(d.xs - 1) * P->S, P->N * row, in,
-                                    Np * row, Np * row, nrhs, hipMemcpyDeviceToDevice, st));
-        L.in_mode = IN_GRID;
-        L.r = P->d_U;
-    } else {
-        // w into this problem's boundary-data rows
-        ASP_HIP(P, hipMemcpyAsync(P->d_W + (long long)d.wrow * P->ws_rhs * P->n, in,
-                                  (size_t)nrhs * P->n * row, hipMemcpyDeviceToDevice, st));
-        L.in_mode = IN_BOUNDARY;
-        L.W = P->d_W;
-        L.w_rhs = P->ws_rhs;
+    const int lines = d.xe - d.xs + 1;
+    const long long Np = P->S * lines;
+    for (int s0 = 0; s0 < nrhs; s0 += P->ws_rhs) {
+        const int na = std::min(nrhs - s0, P->ws_rhs);
+        Apply2 v = apply2_of(P, na);
+        SolveLaunch L;
+        L.job0 = idx;
+        L.njobs = 1;
+        L.rl = kind != ASP_SUB_M;
+        L.nact = na;
+        L.out = v.U;
+        if (kind == ASP_SUB_M) {
+            ASP_HIP(P, launch_pack2d(P, v, static_cast<const zd*>(in), Np, d.xs, d.xe, d.xs - 1, nullptr, s0, st));
+            L.in_mode = IN_GRID;
+            L.r = v.R;
+        } else {
+            ASP_HIP(P, launch_boundary2d(P, v, static_cast<const zd*>(in) + (long long)s0 * P->n, d.wrow, st));
+            L.in_mode = IN_BOUNDARY;
+            L.W = v.W;
+        }
+        ASP_HIP(P, launch_solve2d(P, L, st));
+        ASP_HIP(P, launch_unpack2d(P, v, v.U, nullptr, nullptr, 0, 0, static_cast<zd*>(out), Np, d.xs, d.xe,
+                                   d.xs - 1, nullptr, s0, st));
     }
-    ASP_HIP(P, launch_solve2d(P, L, st));
-    ASP_HIP(P, hipMemcpy2DAsync(out, Np * row, P->d_stage + (long long)(d.xs - 1) * P->S,
-                                P->N * row, Np * row, nrhs, hipMemcpyDeviceToDevice, st));
     return ASP_OK;
 }
 
@@ -507,11 +487,13 @@ extern "C" asp_status asp_workspace_estimate(const asp_plan* P, int nrhs, int re
         return ASP_OK;
     }
     const double vec = (double)nrhs * P->N * sizeof(zd);
-    const double wrows = (double)std::max(2 * P->m - 2, 1) * nrhs * P->n * sizeof(zd);
-    const double wt = (double)sweep_wt_len(P, nrhs) * esz;
-    const double y = (double)apply_groups(P, nrhs) * solve_scratch_per_block(P) * esz;
+    const int pass = std::min(nrhs, apply_max_rhs(P));
+    const double vec2 = 3.0 * vec2_elems(P, pass) * esz;
+    const double wrows = (double)std::max(2 * P->m - 2, 1) * pass * P->n * sizeof(zd);
+    const double wt = (double)sweep_wt_len(P, pass) * esz;
+    const double y = (double)solve_scratch_elems(P, pass) * esz;
     const double krylov = vec * (2.0 * restart + 2.0) + krylov_small_bytes(P->N, nrhs);
-    *bytes = (size_t)(2.0 * vec + wrows + wt + y + krylov);
+    *bytes = (size_t)(vec2 + wrows + wt + y + krylov);
     return ASP_OK;
 }
 
@@ -543,6 +525,6 @@ extern "C" asp_status asp_release_workspace(asp_plan* P) {
     // the layer solves' scratch (shared by asp_factor and the applies)
     dev_free(P->d_y);
     P->d_y = nullptr;
-    P->y_waves = 0;
+    P->y_elems = 0;
     return ASP_OK;
 }

@@ -169,8 +169,6 @@ struct AxisTables {
 // ---------------------------------------------------------------------------
 // the plan
 // ---------------------------------------------------------------------------
-constexpr int SINK_ELEMS = 1024;   // complex128 entries of the discard buffer
-
 struct asp_plan {
     // problem
     int dim = 0, n = 0, b = 0, gamma = 0, g = 0, m = 0;
@@ -206,7 +204,6 @@ struct asp_plan {
     size_t fac_bytes = 0;
     long long fac_elems = 0;
     int* d_flag = nullptr;            // breakdown flag of the factorization
-    zd* d_sink = nullptr;             // SINK_ELEMS entries: target of stores a lane discards
     bool factored = false;
 
     // boundary-to-boundary maps T^R_p, T^L_p (1 < p < m), n x n each, column-major
@@ -216,13 +213,13 @@ struct asp_plan {
 
     // apply workspaces (grown on demand)
     int ws_rhs = 0;
-    zd* d_U = nullptr;      // u~_{p,p} on every layer
-    zd* d_W = nullptr;      // sweep boundary data: (2m-2) rows x ws_rhs x n
-    zd* d_stage = nullptr;  // grid-shaped staging for asp_subsolve
+    zd* d_U = nullptr;      // 3D: u~_{p,p} on every layer; 2D: the three vectors R, U, C of Apply2
+    zd* d_W = nullptr;      // 2D sweep boundary data: (2m-2) rows x n x ws_rhs
+    zd* d_stage = nullptr;  // 3D: the L outputs
     void* d_wt = nullptr;   // sweep data, transposed, in the factor precision
     long long wt_elems = 0;
-    void* d_y = nullptr;    // forward-substitution scratch, y_waves workgroups
-    long long y_waves = 0;
+    void* d_y = nullptr;    // 2D forward-substitution scratch, y_elems entries
+    long long y_elems = 0;
     size_t ws_bytes = 0;
 
     // per-kernel-class timing (asp_timing_enable / asp_timing_read)
@@ -340,7 +337,7 @@ hipError_t launch_residual(const asp_plan* P, const zd* b, const zd* x, zd* out,
 hipError_t launch_factor2d(const asp_plan* P, hipStream_t st);
 
 // batched layer solves for the jobs d_jobs[job0 .. job0+njobs) (all M, or all
-// R/L: rl) and the right-hand sides act[0..nact) (NULL: 0..nact-1): out = v on X_p.
+// R/L: rl) and nact right-hand sides, on slot-fastest vectors (Apply2): out = v on X_p.
 //   in_mode   IN_GRID: data = r on X_p;  IN_BOUNDARY: boundary data from the
 //             W rows of the problems;  IN_TWIST: the chains of the boundary
 //             maps of the jobs d_jobs[job0 .. job0+njobs0) and, in the same
@@ -349,15 +346,13 @@ struct SolveLaunch {
     int job0 = 0, njobs = 0;
     int job1 = 0, njobs0 = 0;
     bool rl = false;
-    const int* act = nullptr;
-    int nact = 0;
+    int nact = 0;                // right-hand sides
     int in_mode = IN_GRID;
-    const zd* r = nullptr;
+    const void* r = nullptr;
     const zd* W = nullptr;
-    int w_rhs = 0;
-    zd* out = nullptr;
+    void* out = nullptr;
     // a launch over R and L problems: the L problems write here instead (NULL: out)
-    zd* out_L = nullptr;
+    void* out_L = nullptr;
     // IN_TWIST: 0 = the map entries between blocks of the same half, 2 = rows
     // grow and jout of the propagators from the middle block (nact = the rows
     // of the middle block), over the columns of the diagonal blocks
@@ -376,28 +371,41 @@ hipError_t launch_rgf2d(const asp_plan* P, int job0, int job1, int njobs, hipStr
 hipError_t devmem_alloc(void** p, size_t bytes);
 void devmem_free(void* p);
 
-// right-hand sides handled by one solve workgroup for problems of LR rows, and
-// the scratch entries of one workgroup (the same for every LR)
-int solve_rhs_per_block(int LR);
+// The vectors of a 2D apply over nact right-hand sides hold them (slots)
+// fastest, in the factor precision: (line, i1, slot) at ((line - 1) n + i1) nact +
+// slot.  R is the data, later A; U the M-solutions, A and C the outputs of the
+// R and L problems; W the boundary rows of the R/L problems, in double.
+struct Apply2 {
+    void *R, *U, *A, *C;
+    zd* W;
+    int nact;
+};
+int apply_max_rhs(const asp_plan* P);                         // of one pass of an apply
+long long solve_scratch_elems(const asp_plan* P, int nrhs);   // forward results of an apply
+// the caller's vectors (stride entries apart, their first line `line_off` + 1;
+// vectors act[slot], or id0 + slot) on sweep lines line0 .. line1 into v.R, and
+// z = U + A + C back (A from line a_from, C up to line c_to; NULL: left out)
+hipError_t launch_pack2d(const asp_plan* P, const Apply2& v, const zd* r, long long stride, int line0, int line1,
+                         int line_off, const int* act, int id0, hipStream_t st);
+// the caller's boundary values (n per right-hand side) into W row `row`
+hipError_t launch_boundary2d(const asp_plan* P, const Apply2& v, const zd* w, int row, hipStream_t st);
+hipError_t launch_unpack2d(const asp_plan* P, const Apply2& v, const void* U, const void* A, const void* C,
+                           int a_from, int c_to, zd* z, long long stride, int line0, int line1, int line_off,
+                           const int* act, int id0, hipStream_t st);
 // the most sweep lines a 2D auxiliary problem may have with blocks of LR rows
 // (LR = 16, 32, 64) in element type T: the solve kernels keep two blocks in
 // LDS, which at LR = 64 holds 64 lines of FP32 and 48 of FP64
 template <typename T>
 constexpr int max_lines_2d(int LR) { return LR <= 32 ? 32 : (sizeof(T) == 4 ? 64 : 48); }
-long long solve_scratch_per_block(const asp_plan* P);
-// the W rows that start the two sweeps (from u~_{1,1} and u~_{m,m} in U)
-hipError_t launch_sweep_seed(const asp_plan* P, zd* W, long long outR, long long outL,
-                             const int* act, int nact, hipStream_t st);
+// the W rows (row indices) that start the two sweeps (from u~_{1,1} and u~_{m,m} in U)
+hipError_t launch_sweep_seed(const asp_plan* P, const Apply2& v, int rowR, int rowL, hipStream_t st);
 // the boundary lines the R_{t+1} / L_{m-t} solves of a sequential sweep step hand
-// on: W rows rowR / rowL (R outputs in z, L outputs in stage, both without U)
-// get the output plus U on line lineR / lineL
-hipError_t launch_sweep_hand(const asp_plan* P, const zd* z, const zd* stage, zd* W,
-                             long long rowR, int lineR, long long rowL, int lineL, const int* act,
-                             int nact, hipStream_t st);
-// sweep step t = 1..m-2 (both directions); workspace sizes for nrhs right-hand sides
-int sweep_wt_len(const asp_plan* P, int nrhs);
-hipError_t launch_sweep_step(const asp_plan* P, int t, zd* W, int w_rhs, const int* act, int nact,
+// on: W rows rowR / rowL get A / C plus U on line lineR / lineL
+hipError_t launch_sweep_hand(const asp_plan* P, const Apply2& v, int rowR, int lineR, int rowL, int lineL,
                              hipStream_t st);
+// sweep step t = 1..m-2 (both directions); workspace size for nrhs right-hand sides
+int sweep_wt_len(const asp_plan* P, int nrhs);
+hipError_t launch_sweep_step(const asp_plan* P, const Apply2& v, int t, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // 3D auxiliary problems
@@ -453,7 +461,7 @@ hipError_t launch_plane3d(const asp_plan* P, const zd* U, int line0, int line1, 
                           const int* act, int nact, hipStream_t st);
 // z = U + C on lines 1..split, z += C on lines split+1..upto
 hipError_t launch_combine3d(const asp_plan* P, zd* z, const zd* U, const zd* C, int split,
-                            int upto, bool all_u, const int* act, int nact, hipStream_t st);
+                            int upto, const int* act, int nact, hipStream_t st);
 
 // timing of one launch: constructed before the launch, end() after it
 struct KTimer {
@@ -506,9 +514,6 @@ hipError_t launch_scale_vec(const zd* w, zd* v, const zd* scal, long long N, con
 // host-side pieces shared by the entry points
 asp_status ensure_apply_ws(asp_plan* P, int nrhs);
 asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int nact);
-// workgroups (each with solve_scratch_per_block entries of scratch) of the
-// 2D layer solves of one apply over nrhs right-hand sides
-long long apply_scratch_groups(const asp_plan* P, int nrhs);
 // right-hand sides per chunk of the 3D nested-dissection solves
 constexpr int ND_CHUNK = 16;
 // device bytes of the 2D layer solves' forward-substitution scratch now allocated

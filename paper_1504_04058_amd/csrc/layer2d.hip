@@ -27,9 +27,6 @@ namespace {
 // factorization).
 #define ASP_PLAIN_ACC(...) __attribute__((amdgpu_waves_per_eu(__VA_ARGS__)))
 
-constexpr int WAVE = 64;
-static_assert(WAVE * 16 <= SINK_ELEMS, "sixteen discard entries per lane");
-
 // raw buffer stores: dword 3 of the resource (32-bit data format) and an
 // offset past any range, whose writes the hardware drops
 constexpr int BUF_DW3 = 0x00020000;
@@ -537,33 +534,36 @@ __device__ __forceinline__ void kmac3(KTile3& c, zf a, zf b) {
     c.p3 = Mfma<float>::mac(a.y, b.x + b.y, c.p3);
 }
 
+// Vectors inside an apply hold the right-hand sides (slots) fastest, in the
+// factor precision: entry (sweep line, i1, slot) at ((line - 1) n + i1) ws +
+// slot, ws the number of right-hand sides; boundary data of an R/L problem in
+// double at (row n + i1) ws + slot.  A wavefront's 16 right-hand sides of a grid point
+// are then one contiguous run (128 bytes in FP32), where the caller's layout
+// puts each in a line of its own and a block step uses 16 bytes of it (written
+// through an LDS stage and flushed every eight steps, that cost the R/L solves a
+// third of their time).  n = 1023, 64 right-hand sides, FP32, ms per apply with
+// the caller's layout / this one: M 4.34 / 3.84 (its copy in included), R and L
+// 4.02 / 2.71, final sum 0.80 / 0.54.
 struct SolveArgs {
     const SubDesc* desc;
     const int* jobs;
     int njobs, njobs0, jobs1;   // jobs[0 .. njobs0) and jobs[jobs1 .. ): njobs in all
-    const int* act;      // right-hand-side ids (NULL: 0..nact-1)
-    int nact;
-    zd* out_L;           // L problems of a launch with both kinds: their own output
+    int nact;            // right-hand sides (columns of a map), slots of the vectors
     const void* fac;
     AxisTables ax;
     const zd* subtab;
-    const zd* r;         // IN_GRID: grid vectors
-    const zd* W;         // IN_BOUNDARY: boundary data per (problem, rhs)
-    int w_rhs;           // right-hand-side stride of W (in n-vectors)
-    zd* out;             // grid vectors
+    const void* r;       // IN_GRID: data
+    const zd* W;         // IN_BOUNDARY: boundary data
+    void* out;           // solutions on X_p
+    void* out_L;         // ... of the L problems
     void* Tout;          // IN_TWIST: boundary-to-boundary maps
     void* y;             // forward results [problem][chunk][block][LR][16]
-    zd* sink;            // discard buffer: four entries per thread
-    int buf_ok;          // output byte offsets fit the 31-bit buffer range
+    int buf_ok;          // IN_TWIST: the byte offsets of a map fit the 31-bit buffer range
     int twist_kind;      // IN_TWIST: 0 both triangles of each half, 2 the propagators
-    int srow;            // staged output lines per workgroup
     int n;
-    long long N;
 };
 
 constexpr int RC = 16;         // right-hand sides per workgroup: one matrix-core tile
-constexpr int KO = 8;          // output steps per flush: whole 128-byte lines of complex128
-constexpr int STG_MAX = 8;     // most staged output lines
 
 // 8 or 16 bytes through a buffer resource, zero past its range
 template <typename T>
@@ -710,9 +710,6 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     M.init(d, reinterpret_cast<const cplx<T>*>(a.fac) + d.fac_off);
     const int li = M.li;
     const zd* tab = a.subtab + d.tab_off;
-    const int slot = it.ch * RC + li;
-    const bool valid = slot < a.nact;
-    const int rid = valid ? (a.act ? a.act[slot] : slot) : 0;
     const int grow = (d.kind == ASP_SUB_R) ? 0 : L - 1;          // row carrying boundary data
     const zd coupl = (d.kind == ASP_SUB_R) ? tab[0] : tab[L];    // s at lo-1/2 or hi+1/2
     // forward results through a buffer resource: rows past L are dropped
@@ -722,14 +719,22 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     constexpr unsigned ystep = LR * RC * sizeof(cplx<T>);
     unsigned yoff[4];
     cplx<T> sinv2[4];
-    // step data: grid data of the rows of X (IN_GRID), or the boundary data on
-    // the carrying row (IN_BOUNDARY, one entry per lane at most); other lanes
-    // read a fixed table entry
+    // step data: the rows of X (IN_GRID), or the boundary data on the carrying
+    // row (IN_BOUNDARY, one entry per lane at most); rows without data and lanes
+    // past the right-hand sides lie past the resource's range and read zero
+    const bool valid = it.ch * RC + li < a.nact;
     constexpr int NG = INM == IN_GRID ? 4 : 1;
-    const zd* inp[NG];
-    int ink[NG];
+    using TG = std::conditional_t<INM == IN_GRID, T, double>;
+    const long long line_len = (long long)n * a.nact;
+    const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(
+        INM == IN_GRID ? static_cast<void*>(const_cast<cplx<T>*>(static_cast<const cplx<T>*>(a.r)) +
+                                            (d.xs - 1) * line_len + it.ch * RC)
+                       : static_cast<void*>(const_cast<zd*>(a.W) + d.wrow * line_len + it.ch * RC),
+        0, 0x7fffffff, BUF_DW3);
+    const unsigned gstep = (unsigned)(a.nact * sizeof(cplx<TG>));
+    unsigned goff[NG];
     bool use[4];
-    int vrow = -1;
+    if (INM != IN_GRID) goff[0] = BUF_OOB;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int row = 16 * M.rt + Mfma<T>::row(M.l, v);
@@ -739,20 +744,15 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         sinv2[v] = rowv ? ccast<T>(tab[L + 1 + row]) : mk<T>(0, 0);
         if (INM == IN_GRID) {
             use[v] = rowv && line >= d.xs && line <= d.xe;
-            inp[v % NG] = use[v] ? a.r + (long long)rid * a.N + (long long)n * (line - 1) : a.subtab;
-            ink[v % NG] = use[v] ? 1 : 0;
+            goff[v % NG] = use[v] && valid ? (unsigned)(((line - d.xs) * line_len + li) * sizeof(cplx<TG>)) : BUF_OOB;
         } else {
             use[v] = rowv && row == grow;
-            if (use[v]) vrow = v;
+            if (use[v] && valid) goff[0] = (unsigned)(li * sizeof(cplx<TG>));
         }
-    }
-    if (INM != IN_GRID) {
-        inp[0] = vrow >= 0 ? a.W + ((long long)d.wrow * a.w_rhs + rid) * n : a.subtab;
-        ink[0] = vrow >= 0 ? 1 : 0;
     }
     struct Slot {
         cplx<T> f[KS];   // operand of step s
-        zd g[NG];        // data of step s + 1
+        cplx<TG> g[NG];  // data of step s + 1
         zd sh, ism;      // s1 between blocks s and s + 1; 1 / (s1 h^2) at block s + 1
     };
     // data of block s + 1 (the middle block past the last step: unused)
@@ -761,19 +761,19 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         M.load(S.f, H.blk(sc));
         const int k = H.blk(sc + 1);
 #pragma unroll
-        for (int e = 0; e < NG; ++e) S.g[e] = inp[e][(long long)(k - 1) * ink[e]];
+        for (int e = 0; e < NG; ++e) S.g[e] = buf_load<TG>(rg, goff[e], (unsigned)(k - 1) * gstep);
         S.sh = a.ax.sh[H.half_line(sc)];
         if (INM != IN_GRID) S.ism = a.ax.inv_sh2[k - 1];
     };
     cplx<T> u[4];
-    auto input = [&](const zd (&g)[NG], zd ism, cplx<T> shc, const cplx<T> (&y)[4], int buf) {
+    auto input = [&](const cplx<TG> (&g)[NG], zd ism, cplx<T> shc, const cplx<T> (&y)[4], int buf) {
         cplx<T> gb;
-        if constexpr (INM != IN_GRID) gb = ccast<T>(g[0] * -(coupl * ism));
+        if constexpr (INM != IN_GRID) gb = ccast<T>(ccast<double>(g[0]) * -(coupl * ism));
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             cplx<T> t;
             if constexpr (INM == IN_GRID)
-                t = csel(use[v], ccast<T>(g[v % NG]), mk<T>(T(0), T(0)));
+                t = ccast<T>(g[v % NG]);
             else
                 t = csel(use[v], gb, mk<T>(T(0), T(0)));
             u[v] = t - (shc * sinv2[v]) * y[v];
@@ -782,10 +782,10 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     };
     Slot sl[NS];
     {
-        zd g0[NG];
+        cplx<TG> g0[NG];
         const int k = H.blk(1);
 #pragma unroll
-        for (int e = 0; e < NG; ++e) g0[e] = inp[e][(long long)(k - 1) * ink[e]];
+        for (int e = 0; e < NG; ++e) g0[e] = buf_load<TG>(rg, goff[e], (unsigned)(k - 1) * gstep);
         const zd ism0 = a.ax.inv_sh2[k - 1];
 #pragma unroll
         for (int q = 0; q < NS; ++q) fetch(sl[q], 1 + q);
@@ -825,13 +825,10 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
 template <typename T, int LR, int INM, bool SPL>
 __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_bwd_kernel(SolveArgs a) {
     static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
-    static_assert(4 * LR * 4 <= SINK_ELEMS, "four discard entries per thread");
     using Tile = BlockTile<T, LR, SPL>;
     constexpr int NW = Tile::NW, KS = Tile::KS, NS = NSLOT;
     constexpr bool TW = INM == IN_TWIST;
     __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
-    extern __shared__ __align__(16) unsigned char dyn[];
-    cplx<T>* const stg = reinterpret_cast<cplx<T>*>(dyn);   // [line][rhs][KO + 1]
     const int n = a.n, p = mid_block(n);
     int jl, ch, dir, nchunk;
     bool below = false;   // IN_TWIST kind 0: the triangle away from the diagonal's chains
@@ -865,7 +862,6 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     }
     const SubDesc d = a.desc[a.jobs[jl < a.njobs0 ? jl : a.jobs1 + jl - a.njobs0]];
     const int L = d.L;
-    const long long N = a.N;
     const Half H(n, dir);
     if (!TW && dir && H.np == 0) return;
     Tile M;
@@ -889,7 +885,6 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     // chunk; the half of block p takes it too.  smax: the chain's first step
     const int ncol = TW && a.twist_kind == 0 ? H.np + (dir ? 0 : 1) : a.nact;
     const bool valid = slot < ncol;
-    const int rid = !TW && valid ? (a.act ? a.act[slot] : slot) : 0;
     const int smax = TW && a.twist_kind == 0 ? min((ch + 1) * RC, ncol) : H.np + 1;
 
     // -- y of a step -----------------------------------------------------------
@@ -924,56 +919,24 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     };
 
     // -- outputs ----------------------------------------------------------------
-    zd* const outp = (d.kind == ASP_SUB_L) ? a.out_L : a.out;
     const bool bufo = a.buf_ok != 0;
     cplx<T>* const Tbase = reinterpret_cast<cplx<T>*>(a.Tout) + (TW ? d.tr_off : 0);
+    const long long line_len = (long long)n * a.nact;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        TW ? static_cast<void*>(Tbase) : static_cast<void*>(outp), 0, 0x7fffffff, BUF_DW3);
-    zd* const sink = a.sink + threadIdx.x * 4;
-    // Grid outputs: the first a.srow lines of X are staged in LDS and written KO
-    // steps at a time (whole 128-byte lines per right-hand side and line), each
-    // wavefront its own rows; the other lines of X (the first and last layers are
-    // wider) are written at every step.  Without a.buf_ok everything is.
-    const int nst = !TW && bufo ? min(d.xe - d.xs + 1, a.srow) : 0;
-    int xr[4];
-    bool stgd[4], dirw[4];
-    bool any_dir = false;
+        TW ? static_cast<void*>(Tbase)
+           : static_cast<void*>(static_cast<cplx<T>*>((d.kind == ASP_SUB_L) ? a.out_L : a.out) +
+                                (d.xs - 1) * line_len + ch * RC),
+        0, 0x7fffffff, BUF_DW3);
+    const unsigned ostep = (unsigned)(a.nact * sizeof(cplx<T>));
+    unsigned ooff[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int line = d.lo + row[v];
-        const bool inX = rowv[v] && line >= d.xs && line <= d.xe;
-        xr[v] = line - d.xs;
-        stgd[v] = inX && xr[v] < nst;
-        dirw[v] = inX && !stgd[v];
-        any_dir = any_dir || dirw[v];
+        const bool inX = valid && rowv[v] && line >= d.xs && line <= d.xe;
+        ooff[v] = inX ? (unsigned)(((line - d.xs) * line_len + li) * sizeof(cplx<T>)) : BUF_OOB;
     }
-    any_dir = __any(any_dir);
     // blocks this half writes: dir 0 takes the middle block
     const int kmin = dir ? p + 1 : 1, kmax = dir ? n : p;
-    int frid[2];
-    bool fval[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int fs = ch * RC + 8 * h + (M.l >> 3);
-        fval[h] = !TW && fs < a.nact;
-        frid[h] = fval[h] ? (a.act ? a.act[fs] : fs) : 0;
-    }
-    auto flush = [&](int g) {
-        wave_lds_fence();
-        const int i1 = g * KO + (M.l & 7);
-        const bool kin = i1 + 1 >= kmin && i1 + 1 <= kmax;
-        for (int x = 0; x < nst; ++x) {
-            const int r = d.xs - d.lo + x;
-            if ((r >> 4) != M.rt) continue;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const cplx<T> val = stg[(x * RC + 8 * h + (M.l >> 3)) * (KO + 1) + (M.l & 7)];
-                const unsigned off = (unsigned)(((long long)frid[h] * N + (long long)n * (d.xs + x - 1) + i1) * 16);
-                buf_store(rs, kin && fval[h] ? off : BUF_OOB, 0u, ccast<double>(val));
-            }
-        }
-        wave_lds_fence();
-    };
     // IN_TWIST: the wavefront and lanes holding the row a map entry is read from
     const int jrow = below ? grow : jout;
     const bool jmine = TW && (jrow >> 4) == M.rt, gmine = TW && (grow >> 4) == M.rt, omine = TW && (jout >> 4) == M.rt;
@@ -1020,21 +983,7 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         }
         if (k < kmin || k > kmax) return;   // the middle block in half 1
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (stgd[v]) stg[(xr[v] * RC + li) * (KO + 1) + (k - 1) % KO] = x[v];
-        if (any_dir) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const bool on = dirw[v] && valid;
-                const long long o = (long long)rid * N + (long long)n * (d.lo + row[v] - 1) + (k - 1);
-                const zd y = ccast<double>(x[v]);
-                if (bufo)
-                    buf_store(rs, on ? (unsigned)(o * 16) : BUF_OOB, 0u, y);
-                else
-                    *(on ? outp + o : sink + v) = y;
-            }
-        }
-        if (nst > 0 && (dir ? ((k - 1) % KO == KO - 1 || k == n) : (k - 1) % KO == 0)) flush((k - 1) / KO);
+        for (int v = 0; v < 4; ++v) buf_store(rs, ooff[v], (unsigned)(k - 1) * ostep, x[v]);
     };
 
     // -- start --------------------------------------------------------------------
@@ -1084,10 +1033,11 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         for (int v = 0; v < 4; ++v) {
             const int line = d.lo + row[v];
             cplx<T> t = mk<T>(T(0), T(0));
-            if (INM == IN_GRID && rowv[v] && line >= d.xs && line <= d.xe)
-                t = ccast<T>(a.r[(long long)rid * N + (long long)n * (line - 1) + p - 1]);
-            if (INM == IN_BOUNDARY && rowv[v] && row[v] == grow)
-                t = ccast<T>(a.W[((long long)d.wrow * a.w_rhs + rid) * n + p - 1] * -(coupl * a.ax.inv_sh2[p - 1]));
+            if (INM == IN_GRID && valid && rowv[v] && line >= d.xs && line <= d.xe)
+                t = static_cast<const cplx<T>*>(a.r)[(line - 1) * line_len + (long long)(p - 1) * a.nact + slot];
+            if (INM == IN_BOUNDARY && valid && rowv[v] && row[v] == grow)
+                t = ccast<T>(a.W[d.wrow * line_len + (long long)(p - 1) * a.nact + slot] *
+                             -(coupl * a.ax.inv_sh2[p - 1]));
             u[v] = (t - (cm * sinv2[v]) * ym[v]) - (cp * sinv2[v]) * yp[v];
             if constexpr (NW > 1) tb[smax & 1][row[v]][li] = u[v];
         }
@@ -1202,15 +1152,13 @@ struct SweepArgs {
     long long t_off[2];      // map of the problem stepped from (R, L)
     const void* Wt_in[2];    // W transposed: [i1][slot], row stride ws, type of the maps
     void* Wt_out[2];
-    zd* W;                   // W rows [rhs][i1] (complex128) of the problems stepped into
+    zd* W;                   // boundary data of the problems stepped into
     long long w_out[2];
     int line[2];             // line of u~_{p,p} added (last of X_p / first of X_p)
-    const zd* Ugrid;
-    const int* act;
-    int nact;
-    int ws;                  // padded slot count (multiple of SW_RT)
+    const void* U;           // u~_{p,p}, right-hand sides fastest
+    int nact;                // right-hand sides, slots of U and W
+    int ws;                  // slots of Wt (multiple of SW_RT)
     int n;
-    long long N;
 };
 
 
@@ -1262,9 +1210,9 @@ __global__ __launch_bounds__(64 * NWV) ASP_PLAIN_ACC(2) void sweep_step_kernel(S
     // adjacent (one 16-byte load in FP32).
     constexpr int OPT = (256 * NT + 64 * NWV - 1) / (64 * NWV);
     struct Out {
-        int t2, l2, v, k, slot, id;
+        int t2, l2, v, k, slot;
         bool ok;
-        zd u;
+        cplx<T> u;
     } out[OPT];
 #pragma unroll
     for (int o = 0; o < OPT; ++o) {
@@ -1276,8 +1224,8 @@ __global__ __launch_bounds__(64 * NWV) ASP_PLAIN_ACC(2) void sweep_step_kernel(S
         q.k = k0 + Mfma<T>::row(q.l2, q.v);
         q.slot = s0 + NT * (q.l2 & 15) + q.t2;
         q.ok = t < 256 * NT && q.k < n && q.slot < a.nact;
-        q.id = q.ok ? (a.act ? a.act[q.slot] : q.slot) : 0;
-        q.u = a.Ugrid[(long long)q.id * a.N + (long long)n * (a.line[side] - 1) + (q.ok ? q.k : 0)];
+        q.u = static_cast<const cplx<T>*>(
+            a.U)[((long long)n * (a.line[side] - 1) + (q.ok ? q.k : 0)) * a.nact + (q.ok ? q.slot : 0)];
     }
     // FP32: three real products per complex one (p1 = (ar + ai) br,
     // p2 = ar (bi - br), p3 = ai (br + bi); re = p1 - p3, im = p1 + p2), the
@@ -1384,69 +1332,215 @@ __global__ __launch_bounds__(64 * NWV) ASP_PLAIN_ACC(2) void sweep_step_kernel(S
         cplx<T> sum = red[0][q.t2][q.l2][q.v];
 #pragma unroll
         for (int w = 1; w < NWV; ++w) sum = sum + red[w][q.t2][q.l2][q.v];
-        const zd val = ccast<double>(sum) + q.u;
-        a.W[a.w_out[side] + (long long)q.id * n + q.k] = val;
+        const zd val = ccast<double>(sum) + ccast<double>(q.u);
+        a.W[a.w_out[side] + (long long)q.k * a.nact + q.slot] = val;
         reinterpret_cast<cplx<T>*>(a.Wt_out[side])[(long long)q.k * ws + q.slot] = ccast<T>(val);
     }
 }
 
 // W rows of the first sweep step: u~_{1,1} on the last line of X_1 (right-going)
-// and u~_{m,m} on the first line of X_m (left-going), plus their transposed copies
-// (padding slots zero)
+// and u~_{m,m} on the first line of X_m (left-going), plus their copies in the
+// factor precision (padding slots zero); one thread per (i1, slot)
 template <typename T>
-__global__ void sweep_seed_kernel(const zd* __restrict__ Ugrid, zd* __restrict__ W,
+__global__ void sweep_seed_kernel(const cplx<T>* __restrict__ U, zd* __restrict__ W,
                                   long long outR, long long outL, int lineR, int lineL,
-                                  cplx<T>* __restrict__ WtR, cplx<T>* __restrict__ WtL,
-                                  const int* __restrict__ act, int nact, int ws, int n,
-                                  long long N) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int slot = blockIdx.y;
+                                  cplx<T>* __restrict__ WtR, cplx<T>* __restrict__ WtL, int nact, int ws,
+                                  int n) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (long long)n * ws) return;
+    const int k = (int)(i / ws), slot = (int)(i - (long long)k * ws);
     if (slot >= nact) {
-        WtR[(long long)k * ws + slot] = mk<T>(0, 0);
-        WtL[(long long)k * ws + slot] = mk<T>(0, 0);
+        WtR[i] = mk<T>(0, 0);
+        WtL[i] = mk<T>(0, 0);
         return;
     }
-    const int id = act ? act[slot] : slot;
-    const long long u = (long long)id * N + k;
-    const zd vR = Ugrid[u + (long long)n * (lineR - 1)];
-    const zd vL = Ugrid[u + (long long)n * (lineL - 1)];
-    W[outR + (long long)id * n + k] = vR;
-    W[outL + (long long)id * n + k] = vL;
-    WtR[(long long)k * ws + slot] = ccast<T>(vR);
-    WtL[(long long)k * ws + slot] = ccast<T>(vL);
+    const cplx<T> vR = U[((long long)n * (lineR - 1) + k) * nact + slot];
+    const cplx<T> vL = U[((long long)n * (lineL - 1) + k) * nact + slot];
+    W[outR + (long long)k * nact + slot] = ccast<double>(vR);
+    W[outL + (long long)k * nact + slot] = ccast<double>(vL);
+    WtR[i] = vR;
+    WtL[i] = vL;
 }
 
 // Sequential sweep step: the boundary line R_{t+1} hands to R_{t+2} (its
 // output a plus u~ on the last line of its layer) and the one L_{m-t} hands to
 // L_{m-t-1} (c plus u~ on the first line of its layer) into their W rows
-__global__ void sweep_hand_kernel(const zd* __restrict__ z, const zd* __restrict__ stage,
-                                  const zd* __restrict__ Ugrid, zd* __restrict__ W,
-                                  long long rowR, int lineR, long long rowL, int lineL,
-                                  const int* __restrict__ act, int n, long long N) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int id = act ? act[blockIdx.y] : (int)blockIdx.y;
-    const long long u = (long long)id * N + k;
-    if (rowR >= 0) {
-        const long long g = u + (long long)n * (lineR - 1);
-        W[rowR + (long long)id * n + k] = z[g] + Ugrid[g];
+template <typename T>
+__global__ void sweep_hand_kernel(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ C,
+                                  const cplx<T>* __restrict__ U, zd* __restrict__ W, long long rowR,
+                                  int lineR, long long rowL, int lineL, int nact, int n) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long len = (long long)n * nact;
+    if (i >= len) return;
+    const long long gR = len * (lineR - 1) + i, gL = len * (lineL - 1) + i;
+    W[rowR + i] = ccast<double>(A[gR]) + ccast<double>(U[gR]);
+    W[rowL + i] = ccast<double>(C[gL]) + ccast<double>(U[gL]);
+}
+
+// the caller's boundary values (n per right-hand side) into a W row
+__global__ void boundary_row_kernel(const zd* __restrict__ w, zd* __restrict__ W, int nact, int n) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (long long)n * nact) return;
+    const int k = (int)(i / nact), slot = (int)(i - (long long)k * nact);
+    W[i] = w[(long long)slot * n + k];
+}
+
+// ----------------------------------------------------------------------------
+// Between the caller's vectors (right-hand side after right-hand side, i1
+// fastest) and the slot-fastest ones of an apply: both sides of the move are
+// contiguous runs, the transposition goes through LDS.  A block moves 1024
+// entries: nc <= 16 slots of 1024 / nc grid points of one line (nc rounded up
+// to a power of two), so that one right-hand side fills its threads too.
+// Blocks (points, lines, slots / 16).
+// ----------------------------------------------------------------------------
+constexpr int MOVE = 1024;
+struct MoveArgs {
+    const zd* r;           // pack: the caller's vectors
+    zd* z;                 // unpack: the caller's vectors
+    long long stride;      // entries between the caller's vectors
+    int line_off;          // sweep line of the caller's first line, less one
+    const int* act;        // the caller's vector of each slot (NULL: id0 + slot)
+    int id0, nact, n;
+    int pshift;            // 2^pshift grid points per block
+    const void *U, *A, *C; // unpack: their sum (A, C on some lines only)
+    void* out;             // pack: slot-fastest copy
+    int a_from, c_to;      // A on lines >= a_from, C on lines <= c_to
+    int line0;             // first sweep line of the launch
+};
+
+// the block's tile: points k0 .. k0 + np of nc slots from s0; LDS row stride
+// 2^pshift + 4 spreads the slots of a point over the banks
+struct MoveTile {
+    int k0, line, s0, nc, np, pmask, str;
+    __device__ explicit MoveTile(const MoveArgs& a) {
+        const int pts = 1 << a.pshift;
+        k0 = blockIdx.x << a.pshift;
+        line = a.line0 + blockIdx.y;
+        s0 = blockIdx.z * 16;
+        nc = min(16, a.nact - s0);
+        np = min(pts, a.n - k0);
+        pmask = pts - 1;
+        str = pts + 4;
     }
-    if (rowL >= 0) {
-        const long long g = u + (long long)n * (lineL - 1);
-        W[rowL + (long long)id * n + k] = stage[g] + Ugrid[g];
+};
+constexpr int MOVE_LDS = MOVE + 4 * 16;
+
+template <typename T>
+__global__ __launch_bounds__(256) void pack_kernel(MoveArgs a) {
+    __shared__ cplx<T> tile[MOVE_LDS];
+    const MoveTile t(a);
+    for (int e = threadIdx.x; e < t.nc << a.pshift; e += 256) {
+        const int q = e >> a.pshift, k = e & t.pmask;
+        if (k >= t.np) continue;
+        const int id = a.act ? a.act[t.s0 + q] : a.id0 + t.s0 + q;
+        tile[q * t.str + k] =
+            ccast<T>(a.r[id * a.stride + (long long)(t.line - 1 - a.line_off) * a.n + t.k0 + k]);
+    }
+    __syncthreads();
+    cplx<T>* out = static_cast<cplx<T>*>(a.out) + ((long long)(t.line - 1) * a.n + t.k0) * a.nact + t.s0;
+    for (int e = threadIdx.x; e < t.nc * t.np; e += 256) {
+        const int k = e / t.nc, q = e - k * t.nc;
+        out[(long long)k * a.nact + q] = tile[q * t.str + k];
+    }
+}
+
+// z = U + C on the lines before a_from, A + C + U between, A + U after c_to
+template <typename T>
+__global__ __launch_bounds__(256) void unpack_kernel(MoveArgs a) {
+    __shared__ zd tile[MOVE_LDS];
+    const MoveTile t(a);
+    const bool ha = a.A && t.line >= a.a_from, hc = a.C && t.line <= a.c_to;
+    const long long base = ((long long)(t.line - 1) * a.n + t.k0) * a.nact + t.s0;
+    for (int e = threadIdx.x; e < t.nc * t.np; e += 256) {
+        const int k = e / t.nc, q = e - k * t.nc;
+        const long long g = base + (long long)k * a.nact + q;
+        const zd u = ccast<double>(static_cast<const cplx<T>*>(a.U)[g]);
+        zd v = u;
+        if (ha && hc)
+            v = (ccast<double>(static_cast<const cplx<T>*>(a.A)[g]) +
+                 ccast<double>(static_cast<const cplx<T>*>(a.C)[g])) + u;
+        else if (ha || hc)
+            v = ccast<double>(static_cast<const cplx<T>*>(ha ? a.A : a.C)[g]) + u;
+        tile[q * t.str + k] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < t.nc << a.pshift; e += 256) {
+        const int q = e >> a.pshift, k = e & t.pmask;
+        if (k >= t.np) continue;
+        const int id = a.act ? a.act[t.s0 + q] : a.id0 + t.s0 + q;
+        a.z[id * a.stride + (long long)(t.line - 1 - a.line_off) * a.n + t.k0 + k] = tile[q * t.str + k];
     }
 }
 
 }  // namespace
 
-hipError_t launch_sweep_hand(const asp_plan* P, const zd* z, const zd* stage, zd* W,
-                             long long rowR, int lineR, long long rowL, int lineL, const int* act,
-                             int nact, hipStream_t st) {
-    if (nact <= 0) return hipSuccess;
-    dim3 grid((P->n + 255) / 256, nact);
-    hipLaunchKernelGGL(sweep_hand_kernel, grid, dim3(256), 0, st, z, stage, P->d_U, W, rowR, lineR,
-                       rowL, lineL, act, P->n, P->N);
+hipError_t launch_sweep_hand(const asp_plan* P, const Apply2& v, int rowR, int lineR, int rowL, int lineL,
+                             hipStream_t st) {
+    const long long len = (long long)P->n * v.nact;
+    const dim3 grid((unsigned)((len + 255) / 256));
+    if (P->prec != ASP_PREC_FP64)
+        hipLaunchKernelGGL(sweep_hand_kernel<float>, grid, dim3(256), 0, st, (const zf*)v.A, (const zf*)v.C,
+                           (const zf*)v.U, v.W, rowR * len, lineR, rowL * len, lineL, v.nact, P->n);
+    else
+        hipLaunchKernelGGL(sweep_hand_kernel<double>, grid, dim3(256), 0, st, (const zd*)v.A, (const zd*)v.C,
+                           (const zd*)v.U, v.W, rowR * len, lineR, rowL * len, lineL, v.nact, P->n);
+    return hipGetLastError();
+}
+
+hipError_t launch_boundary2d(const asp_plan* P, const Apply2& v, const zd* w, int row, hipStream_t st) {
+    const long long len = (long long)P->n * v.nact;
+    hipLaunchKernelGGL(boundary_row_kernel, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, w,
+                       v.W + row * len, v.nact, P->n);
+    return hipGetLastError();
+}
+
+// log2 of the grid points a move block takes: 1024 entries over up to 16 slots
+static int move_shift(int nact) {
+    int s = 6;
+    for (int c = std::min(nact, 16); c <= 8 && s < 10; c *= 2) ++s;
+    return s;
+}
+
+hipError_t launch_pack2d(const asp_plan* P, const Apply2& v, const zd* r, long long stride, int line0, int line1,
+                         int line_off, const int* act, int id0, hipStream_t st) {
+    MoveArgs a{};
+    a.r = r;
+    a.stride = stride;
+    a.line_off = line_off;
+    a.act = act;
+    a.id0 = id0;
+    a.nact = v.nact;
+    a.n = P->n;
+    a.pshift = move_shift(v.nact);
+    a.out = v.R;
+    a.line0 = line0;
+    const dim3 grid((P->n + (1 << a.pshift) - 1) >> a.pshift, line1 - line0 + 1, (v.nact + 15) / 16);
+    if (P->prec != ASP_PREC_FP64) hipLaunchKernelGGL(pack_kernel<float>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(pack_kernel<double>, grid, dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_unpack2d(const asp_plan* P, const Apply2& v, const void* U, const void* A, const void* C,
+                           int a_from, int c_to, zd* z, long long stride, int line0, int line1, int line_off,
+                           const int* act, int id0, hipStream_t st) {
+    MoveArgs a{};
+    a.z = z;
+    a.stride = stride;
+    a.line_off = line_off;
+    a.act = act;
+    a.id0 = id0;
+    a.nact = v.nact;
+    a.n = P->n;
+    a.pshift = move_shift(v.nact);
+    a.U = U;
+    a.A = A;
+    a.C = C;
+    a.a_from = a_from;
+    a.c_to = c_to;
+    a.line0 = line0;
+    const dim3 grid((P->n + (1 << a.pshift) - 1) >> a.pshift, line1 - line0 + 1, (v.nact + 15) / 16);
+    if (P->prec != ASP_PREC_FP64) hipLaunchKernelGGL(unpack_kernel<float>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(unpack_kernel<double>, grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -1522,8 +1616,7 @@ static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st)
     hipLaunchKernelGGL((solve2d_fwd_kernel<T, LR, FWD, SPL>), dim3(blocks), dim3(4 * LR), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t lds = (size_t)a.srow * RC * (KO + 1) * sizeof(cplx<T>);
-    hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL>), dim3(blocks), dim3(4 * LR), lds, st, a);
+    hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL>), dim3(blocks), dim3(4 * LR), 0, st, a);
     return hipGetLastError();
 }
 
@@ -1552,10 +1645,11 @@ static hipError_t launch_cross_t(int LR, const SolveArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-int solve_rhs_per_block(int LR) { return 1024 / LR; }
-
-// forward results: n blocks x LR rows x 1024 / LR right-hand sides
-long long solve_scratch_per_block(const asp_plan* P) { return (long long)P->n * 1024; }
+// forward results: n blocks of LR rows x 16 right-hand sides per problem and chunk
+long long solve_scratch_elems(const asp_plan* P, int nrhs) {
+    const long long m = P->m, mr = std::max(m * P->LR_M, (2 * m - 2) * P->LR_RL);
+    return mr * ((nrhs + RC - 1) / RC * RC) * P->n;
+}
 
 static SolveArgs solve_args(const asp_plan* P, const SolveLaunch& L) {
     SolveArgs a;
@@ -1564,46 +1658,54 @@ static SolveArgs solve_args(const asp_plan* P, const SolveLaunch& L) {
     a.njobs = L.njobs;
     a.njobs0 = L.njobs0 ? L.njobs0 : L.njobs;
     a.jobs1 = L.job1 - L.job0;
-    a.act = L.act;
     a.nact = L.nact;
-    a.out_L = L.out_L ? L.out_L : L.out;
     a.fac = P->d_fac;
     a.ax = AxisTables{P->d_axis, P->d_axis + (P->n + 1), P->d_axis + (2 * P->n + 1)};
     a.subtab = P->d_subtab;
     a.r = L.r;
     a.W = L.W;
-    a.w_rhs = L.w_rhs;
     a.out = L.out;
+    a.out_L = L.out_L ? L.out_L : L.out;
     a.Tout = P->d_T;
     a.y = P->d_y;
-    a.sink = P->d_sink;
     const size_t esz = P->prec != ASP_PREC_FP64 ? sizeof(zf) : sizeof(zd);
-    const long long lim = 1LL << 31;
-    // map chains address one problem's map, the others the grid vectors
-    const long long bytes = L.in_mode == IN_TWIST
-                                ? (long long)((P->n + 15) / 16 * 16) * P->n * (long long)esz
-                                : (long long)std::max(P->ws_rhs, L.nact) * P->N * (long long)sizeof(zd);
-    a.buf_ok = bytes < lim ? 1 : 0;
+    a.buf_ok = (long long)((P->n + 15) / 16 * 16) * P->n * (long long)esz < (1LL << 31) ? 1 : 0;
     a.twist_kind = L.twist_kind;
-    // the lines of an interior layer, in up to two groups of four
-    a.srow = P->b <= STG_MAX / 2 ? STG_MAX / 2 : STG_MAX;
     a.n = P->n;
-    a.N = P->N;
     return a;
+}
+
+// the most right-hand sides of one apply pass: a problem's lines of X (and a
+// boundary row, in double) within the 31-bit range of a buffer resource
+int apply_max_rhs(const asp_plan* P) {
+    long long lines = 1;
+    for (const auto& x : P->X) lines = std::max(lines, (long long)x[1] - x[0] + 1);
+    const long long s = ((1LL << 31) - 1) / (lines * P->n * (long long)sizeof(zd));
+    return (int)std::min<long long>(std::max<long long>(s, 1), 4096);
 }
 
 hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t st) {
     if (L.njobs <= 0 || L.nact <= 0) return hipSuccess;
-    const SolveArgs a = solve_args(P, L);
     const int LR = L.rl ? P->LR_RL : P->LR_M;   // every job of one launch shares its row count
     const int nchunk = (L.nact + RC - 1) / RC;
-    // IN_TWIST uses no forward-result scratch
-    if (L.in_mode != IN_TWIST &&
-        (long long)L.njobs * nchunk * P->n * LR * RC > P->y_waves * solve_scratch_per_block(P))
-        return hipErrorInvalidValue;
-    if (LR == 16) return launch_solve_mode<16>(P, a, L.in_mode, nchunk, st);
-    if (LR == 32) return launch_solve_mode<32>(P, a, L.in_mode, nchunk, st);
-    return launch_solve_mode<64>(P, a, L.in_mode, nchunk, st);
+    SolveLaunch part = L;
+    if (L.in_mode != IN_TWIST) {
+        // as many problems per launch as the forward-result scratch holds (all
+        // of them, but for a workspace of a fixed size that is nearly too small)
+        const long long room = P->y_elems / ((long long)nchunk * P->n * LR * RC);
+        if (room < 1 || L.nact > apply_max_rhs(P)) return hipErrorInvalidValue;
+        part.njobs = (int)std::min<long long>(L.njobs, room);
+    }
+    for (int j = 0; j < L.njobs; j += part.njobs) {
+        part.job0 = L.job0 + j;
+        part.njobs = std::min(part.njobs, L.njobs - j);
+        const SolveArgs a = solve_args(P, part);
+        const hipError_t e = LR == 16 ? launch_solve_mode<16>(P, a, L.in_mode, nchunk, st)
+                             : LR == 32 ? launch_solve_mode<32>(P, a, L.in_mode, nchunk, st)
+                                        : launch_solve_mode<64>(P, a, L.in_mode, nchunk, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_map_cross(const asp_plan* P, const SolveLaunch& L, hipStream_t st) {
@@ -1623,22 +1725,22 @@ static void* wt_buf(const asp_plan* P, int side, int pp, int ws) {
     return static_cast<char*>(P->d_wt) + ((size_t)(side * 2 + pp) * P->n * ws) * esz;
 }
 
-hipError_t launch_sweep_seed(const asp_plan* P, zd* W, long long outR, long long outL,
-                             const int* act, int nact, hipStream_t st) {
-    if (nact <= 0) return hipSuccess;
+hipError_t launch_sweep_seed(const asp_plan* P, const Apply2& v, int rowR, int rowL, hipStream_t st) {
+    if (v.nact <= 0) return hipSuccess;
     const int lineR = P->X[0][1];
     const int lineL = P->X[P->m - 1][0];
-    const int ws = sweep_slots(nact);
+    const int ws = sweep_slots(v.nact);
     if ((long long)4 * P->n * ws > P->wt_elems) return hipErrorInvalidValue;
-    dim3 grid((P->n + 255) / 256, ws);
+    const long long len = (long long)P->n * v.nact;
+    const dim3 grid((unsigned)(((long long)P->n * ws + 255) / 256));
     if (P->prec != ASP_PREC_FP64)
-        hipLaunchKernelGGL(sweep_seed_kernel<float>, grid, dim3(256), 0, st, P->d_U, W, outR, outL,
-                           lineR, lineL, (zf*)wt_buf(P, 0, 0, ws), (zf*)wt_buf(P, 1, 0, ws), act,
-                           nact, ws, P->n, P->N);
+        hipLaunchKernelGGL(sweep_seed_kernel<float>, grid, dim3(256), 0, st, (const zf*)v.U, v.W, rowR * len,
+                           rowL * len, lineR, lineL, (zf*)wt_buf(P, 0, 0, ws), (zf*)wt_buf(P, 1, 0, ws),
+                           v.nact, ws, P->n);
     else
-        hipLaunchKernelGGL(sweep_seed_kernel<double>, grid, dim3(256), 0, st, P->d_U, W, outR, outL,
-                           lineR, lineL, (zd*)wt_buf(P, 0, 0, ws), (zd*)wt_buf(P, 1, 0, ws), act,
-                           nact, ws, P->n, P->N);
+        hipLaunchKernelGGL(sweep_seed_kernel<double>, grid, dim3(256), 0, st, (const zd*)v.U, v.W, rowR * len,
+                           rowL * len, lineR, lineL, (zd*)wt_buf(P, 0, 0, ws), (zd*)wt_buf(P, 1, 0, ws),
+                           v.nact, ws, P->n);
     return hipGetLastError();
 }
 
@@ -1657,14 +1759,13 @@ static void launch_sweep_t(const SweepArgs& a, hipStream_t st) {
     else launch_sweep_w<T, SPL, 8>(a, st);
 }
 
-hipError_t launch_sweep_step(const asp_plan* P, int t, zd* W, int w_rhs, const int* act, int nact,
-                             hipStream_t st) {
+hipError_t launch_sweep_step(const asp_plan* P, const Apply2& v, int t, hipStream_t st) {
     // step t moves the right-going sweep from layer p = t+1 to p+1 and the
     // left-going sweep from layer p' = m-t to p'-1; the transposed inputs of
     // step t are ping-pong buffer (t-1) & 1
     const int m = P->m;
     const int pR = t + 1, pL = m - t;
-    const int ws = sweep_slots(nact);
+    const int ws = sweep_slots(v.nact);
     if ((long long)4 * P->n * ws > P->wt_elems) return hipErrorInvalidValue;
     SweepArgs a;
     a.T = P->d_T;
@@ -1674,17 +1775,15 @@ hipError_t launch_sweep_step(const asp_plan* P, int t, zd* W, int w_rhs, const i
         a.Wt_in[side] = wt_buf(P, side, (t - 1) & 1, ws);
         a.Wt_out[side] = wt_buf(P, side, t & 1, ws);
     }
-    a.W = W;
-    a.w_out[0] = (long long)P->wrow(P->idx_R(pR + 1)) * w_rhs * P->n;
-    a.w_out[1] = (long long)P->wrow(P->idx_L(pL - 1)) * w_rhs * P->n;
+    a.W = v.W;
+    a.w_out[0] = (long long)P->wrow(P->idx_R(pR + 1)) * v.nact * P->n;
+    a.w_out[1] = (long long)P->wrow(P->idx_L(pL - 1)) * v.nact * P->n;
     a.line[0] = P->X[pR - 1][1];
     a.line[1] = P->X[pL - 1][0];
-    a.Ugrid = P->d_U;
-    a.act = act;
-    a.nact = nact;
+    a.U = v.U;
+    a.nact = v.nact;
     a.ws = ws;
     a.n = P->n;
-    a.N = P->N;
     if (P->prec == ASP_PREC_BF16X3) launch_sweep_t<float, true>(a, st);
     else if (P->prec != ASP_PREC_FP64) launch_sweep_t<float, false>(a, st);
     else launch_sweep_t<double, false>(a, st);
