@@ -505,8 +505,8 @@ __global__ __launch_bounds__(FB) void rgf2d_kernel(const SubDesc* __restrict__ d
 // solves the middle block (each half for itself) and runs outwards.  A block
 // step is the product of S_k^-1 with the chunk's step vectors.  The wavefront's
 // rows of S_k^-1 come straight from memory into the matrix-core operand layout,
-// NSLOT steps ahead into fixed register slots (the step loops are unrolled by
-// NSLOT); columns past L lie past the buffer resource's range and read zero.
+// some steps ahead into fixed register slots (the step loops are unrolled by
+// their number); columns past L lie past the buffer resource's range and read zero.
 // With 16 rows a wavefront holds the whole step vector: the columns of the
 // product run in the order in which the result tile holds its rows, so a
 // step's result is the next step's operand without leaving its lanes (no LDS,
@@ -579,6 +579,13 @@ __device__ __forceinline__ cplx<T> buf_load(__amdgpu_buffer_rsrc_t r, unsigned o
     return v;
 }
 
+// a table entry that is the same for a whole wavefront, through the scalar cache
+// (as a plain load it would take four vector registers per slot)
+__device__ __forceinline__ zd uniform_load(const zd* p) {
+    const auto q = (const __attribute__((address_space(4))) double*)(p);
+    return mk(q[0], q[1]);
+}
+
 // one wavefront's 16-row tile of a block step
 template <typename T, int LR, bool SPL>
 struct BlockTile {
@@ -614,12 +621,8 @@ struct BlockTile {
 #pragma unroll
         for (int j = 0; j < KS; ++j) a[j] = buf_load<T>(rf, aoff[j], (unsigned)(blk - 1) * fstep);
     }
-    // S^-1 (operand a) times the step vectors: the lane's own values u (one
-    // tile) or the LDS copy tb
-    __device__ __forceinline__ CTile<T> product(const cplx<T> (&a)[KS], const cplx<T> (&u)[4],
-                                                const cplx<T> (*tb)[TBS]) const {
-        CTile<T> acc;
-        cplx<T> b[KS];
+    // the step vectors: the lane's own values u (one tile) or the LDS copy tb
+    __device__ __forceinline__ void vectors(cplx<T> (&b)[KS], const cplx<T> (&u)[4], const cplx<T> (*tb)[TBS]) const {
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
             if constexpr (NW == 1)
@@ -627,6 +630,10 @@ struct BlockTile {
             else
                 b[j] = tb[col(j)][li];
         }
+    }
+    // S^-1 (operand a) times the step vectors
+    __device__ __forceinline__ CTile<T> product(const cplx<T> (&a)[KS], const cplx<T> (&b)[KS]) const {
+        CTile<T> acc;
         const int ksn = (L + 3) >> 2;   // 4-column steps in use
         if constexpr (SPL) {
             acc.zero();
@@ -682,11 +689,18 @@ struct SolveItem {
     }
 };
 
-// register slots of a step's loads (three measured the same at n = 1023 with
-// twice the registers) and wavefronts per SIMD the registers are held to
-constexpr int NSLOT = 2;
+// Register slots of a step's loads: one fewer than that many steps are in flight.
+// A step of a 16-row problem in FP32 takes 0.4 us, less than half of a loaded
+// HBM read, and its slots are small: three steps ahead (R and L solves at n =
+// 511, ms per apply: two steps 0.353, three 0.274, five 0.276).  The other
+// steps are longer and a fourth slot would spill: two ahead; the maps' chains
+// have the chip full (three steps ahead: 5% slower).  Wavefronts per SIMD that
+// the registers are held to: at three the slots spill; FP64 in 32 rows spills a
+// little at two and is still 5% faster than at one.
+template <typename T, int LR, int INM>
+constexpr int nslot() { return LR == 16 && INM != IN_TWIST && sizeof(T) == 4 ? 4 : 3; }
 template <typename T, int LR>
-constexpr int solve_waves() { return LR == 64 ? 1 : sizeof(T) == 4 ? 3 : 2; }
+constexpr int solve_waves() { return LR == 64 ? 1 : 2; }
 
 // forward pass of one half: y_s = S^-1 t_s, t_s = g_s - E y_{s-1}.  Every
 // memory operation of the step loop is issued by every lane, from a valid
@@ -697,7 +711,7 @@ template <typename T, int LR, int INM, bool SPL>
 __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_fwd_kernel(SolveArgs a) {
     static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
     using Tile = BlockTile<T, LR, SPL>;
-    constexpr int NW = Tile::NW, KS = Tile::KS, NS = NSLOT;
+    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T, LR, INM>();
     __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
     const int nchunk = (a.nact + RC - 1) / RC;
     const SolveItem it(a.njobs, nchunk);
@@ -762,8 +776,11 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         const int k = H.blk(sc + 1);
 #pragma unroll
         for (int e = 0; e < NG; ++e) S.g[e] = buf_load<TG>(rg, goff[e], (unsigned)(k - 1) * gstep);
-        S.sh = a.ax.sh[H.half_line(sc)];
-        if (INM != IN_GRID) S.ism = a.ax.inv_sh2[k - 1];
+    };
+    auto fetch_coef = [&](Slot& S, int s) {
+        const int sc = min(s, H.np);
+        S.sh = uniform_load(a.ax.sh + H.half_line(sc));
+        if (INM != IN_GRID) S.ism = uniform_load(a.ax.inv_sh2 + H.blk(sc + 1) - 1);
     };
     cplx<T> u[4];
     auto input = [&](const cplx<TG> (&g)[NG], zd ism, cplx<T> shc, const cplx<T> (&y)[4], int buf) {
@@ -788,34 +805,52 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         for (int e = 0; e < NG; ++e) g0[e] = buf_load<TG>(rg, goff[e], (unsigned)(k - 1) * gstep);
         const zd ism0 = a.ax.inv_sh2[k - 1];
 #pragma unroll
-        for (int q = 0; q < NS; ++q) fetch(sl[q], 1 + q);
+        for (int q = 0; q < NS - 1; ++q) {
+            fetch(sl[q], 1 + q);
+            fetch_coef(sl[q], 1 + q);
+        }
         const cplx<T> y0[4] = {mk<T>(0, 0), mk<T>(0, 0), mk<T>(0, 0), mk<T>(0, 0)};
         input(g0, ism0, mk<T>(T(0), T(0)), y0, 1);
     }
     // nothing outstanding on entry: the waits in the loop count its own operations
     __builtin_amdgcn_s_waitcnt(0);
-    auto step = [&](int s, Slot& S, auto pre) {
-        if constexpr (NW > 1) __syncthreads();
-        const CTile<T> acc = M.product(S.f, u, tb[NW > 1 ? s & 1 : 0]);
-        cplx<T> y[4];
-        const unsigned ys = (unsigned)(H.blk(s) - 1) * ystep;
+    cplx<T> y[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            y[v] = mk<T>(acc.re[v], acc.im[v]);
-            buf_store(ry, yoff[v], ys, y[v]);
-        }
-        input(S.g, S.ism, ccast<T>(S.sh), y, (s + 1) & 1);
-        // the slot's next loads after its last use, so that they reuse its registers
+    for (int v = 0; v < 4; ++v) y[v] = mk<T>(T(0), T(0));
+    auto store = [&](int s) {
+        const unsigned ys = (unsigned)(H.blk(max(s, 1)) - 1) * ystep;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) buf_store(ry, yoff[v], ys, y[v]);
+    };
+    // F: the slot of step s - 1, free to take the loads of step s + NS - 1.  The
+    // step's memory operations (those loads, the previous step's results; before
+    // the first step zeros that its results overwrite) follow the reads of the
+    // step vectors: they issue in the latency of those and under the products,
+    // not between a step's result and the next barrier.
+    auto step = [&](int s, Slot& S, Slot& F, auto pre) {
+        if constexpr (NW > 1) __syncthreads();
+        cplx<T> b[KS];
+        M.vectors(b, u, tb[NW > 1 ? s & 1 : 0]);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(pre)::value) fetch(S, s + NS);
+        store(s - 1);
+        if constexpr (decltype(pre)::value) fetch(F, s + NS - 1);
+        if constexpr (NW > 1) __builtin_amdgcn_sched_barrier(0);
+        const CTile<T> acc = M.product(S.f, b);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(pre)::value) fetch_coef(F, s + NS - 1);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[v] = mk<T>(acc.re[v], acc.im[v]);
+        input(S.g, S.ism, ccast<T>(S.sh), y, (s + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
     };
     int s = 1;
     for (; s + NS - 1 <= H.np; s += NS)
 #pragma unroll
-        for (int q = 0; q < NS; ++q) step(s + q, sl[q], std::true_type{});
+        for (int q = 0; q < NS; ++q) step(s + q, sl[q], sl[(q + NS - 1) % NS], std::true_type{});
 #pragma unroll
     for (int q = 0; q < NS - 1; ++q)
-        if (s + q <= H.np) step(s + q, sl[q], std::false_type{});
+        if (s + q <= H.np) step(s + q, sl[q], sl[q], std::false_type{});
+    store(H.np);
 }
 
 // backward pass of one half: the middle block, then x_s = y_s - S^-1 E x_{s+1}
@@ -826,7 +861,7 @@ template <typename T, int LR, int INM, bool SPL>
 __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_bwd_kernel(SolveArgs a) {
     static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
     using Tile = BlockTile<T, LR, SPL>;
-    constexpr int NW = Tile::NW, KS = Tile::KS, NS = NSLOT;
+    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T, LR, INM>();
     constexpr bool TW = INM == IN_TWIST;
     __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
     const int n = a.n, p = mid_block(n);
@@ -935,8 +970,6 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         const bool inX = valid && rowv[v] && line >= d.xs && line <= d.xe;
         ooff[v] = inX ? (unsigned)(((line - d.xs) * line_len + li) * sizeof(cplx<T>)) : BUF_OOB;
     }
-    // blocks this half writes: dir 0 takes the middle block
-    const int kmin = dir ? p + 1 : 1, kmax = dir ? n : p;
     // IN_TWIST: the wavefront and lanes holding the row a map entry is read from
     const int jrow = below ? grow : jout;
     const bool jmine = TW && (jrow >> 4) == M.rt, gmine = TW && (grow >> 4) == M.rt, omine = TW && (jout >> 4) == M.rt;
@@ -981,9 +1014,9 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
             }
             return;
         }
-        if (k < kmin || k > kmax) return;   // the middle block in half 1
+        const bool skip = dir && s > H.np;   // the middle block is half 0's
 #pragma unroll
-        for (int v = 0; v < 4; ++v) buf_store(rs, ooff[v], (unsigned)(k - 1) * ostep, x[v]);
+        for (int v = 0; v < 4; ++v) buf_store(rs, skip ? BUF_OOB : ooff[v], (unsigned)(k - 1) * ostep, x[v]);
     };
 
     // -- start --------------------------------------------------------------------
@@ -995,8 +1028,8 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         const int sc = max(s, 1);
         M.load(S.f, H.blk(sc));
         load_y(s, S.y);
-        S.sh = a.ax.sh[H.half_line(max(s - 1, 0))];
     };
+    auto fetch_coef = [&](Slot& S, int s) { S.sh = uniform_load(a.ax.sh + H.half_line(max(s - 1, 0))); };
     cplx<T> x[4], u[4];
     // E x_{s+1} (sh: s1 between blocks s and s + 1) for step s
     auto coupled = [&](int s, cplx<T> shc) {
@@ -1008,7 +1041,10 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     };
     Slot sl[NS];
 #pragma unroll
-    for (int q = 0; q < NS; ++q) fetch(sl[q], smax - 1 - q);
+    for (int q = 0; q < NS - 1; ++q) {
+        fetch(sl[q], smax - 1 - q);
+        fetch_coef(sl[q], smax - 1 - q);
+    }
     if constexpr (TW) {
         if (a.twist_kind == 0) {
             load_y(smax, x);
@@ -1042,31 +1078,43 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
             if constexpr (NW > 1) tb[smax & 1][row[v]][li] = u[v];
         }
         if constexpr (NW > 1) __syncthreads();
-        const CTile<T> acc = M.product(f, u, tb[NW > 1 ? smax & 1 : 0]);
+        cplx<T> b[KS];
+        M.vectors(b, u, tb[NW > 1 ? smax & 1 : 0]);
+        const CTile<T> acc = M.product(f, b);
 #pragma unroll
         for (int v = 0; v < 4; ++v) x[v] = mk<T>(acc.re[v], acc.im[v]);
-        emit(smax, x);
     }
     if (smax > 1) coupled(smax - 1, ccast<T>(a.ax.sh[H.half_line(smax - 1)]));
     __builtin_amdgcn_s_waitcnt(0);
-    auto step = [&](int s, Slot& S, auto pre) {
+    // the order of the forward pass's step: the loads of step s - NS + 1 and the
+    // outputs of step s + 1 under the products (the maps' outputs, entries of one
+    // row, stay at the step's end)
+    auto step = [&](int s, Slot& S, Slot& F, auto pre) {
         if constexpr (NW > 1) __syncthreads();
-        const CTile<T> acc = M.product(S.f, u, tb[NW > 1 ? s & 1 : 0]);
+        cplx<T> b[KS];
+        M.vectors(b, u, tb[NW > 1 ? s & 1 : 0]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!TW) emit(s + 1, x);
+        if constexpr (decltype(pre)::value) fetch(F, s - NS + 1);
+        if constexpr (NW > 1) __builtin_amdgcn_sched_barrier(0);
+        const CTile<T> acc = M.product(S.f, b);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(pre)::value) fetch_coef(F, s - NS + 1);
         use_y(s, S.y);
 #pragma unroll
         for (int v = 0; v < 4; ++v) x[v] = S.y[v] - mk<T>(acc.re[v], acc.im[v]);
-        emit(s, x);
+        if constexpr (TW) emit(s, x);
         coupled(s - 1, ccast<T>(S.sh));
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(pre)::value) fetch(S, s - NS);
     };
     int s = smax - 1;
     for (; s - NS + 1 >= 1; s -= NS)
 #pragma unroll
-        for (int q = 0; q < NS; ++q) step(s - q, sl[q], std::true_type{});
+        for (int q = 0; q < NS; ++q) step(s - q, sl[q], sl[(q + NS - 1) % NS], std::true_type{});
 #pragma unroll
     for (int q = 0; q < NS - 1; ++q)
-        if (s - q >= 1) step(s - q, sl[q], std::false_type{});
+        if (s - q >= 1) step(s - q, sl[q], sl[q], std::false_type{});
+    if constexpr (!TW) emit(1, x);
 }
 
 // ----------------------------------------------------------------------------
