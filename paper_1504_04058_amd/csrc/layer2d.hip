@@ -689,6 +689,16 @@ struct SolveItem {
     }
 };
 
+// __syncthreads with the wait for this wavefront's LDS accesses spelled out: in a
+// loop entered after an explicit wait for everything the compiler takes the
+// barrier's own wait at the loop's head for redundant, also on the way round,
+// where LDS writes are outstanding (seen in the code of the step loops: another
+// wavefront could then read the vectors of two steps before).
+__device__ __forceinline__ void step_sync() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __syncthreads();
+}
+
 // Register slots of a step's loads: one fewer than that many steps are in flight.
 // A step of a 16-row problem in FP32 takes 0.4 us, less than half of a loaded
 // HBM read, and its slots are small: three steps ahead (R and L solves at n =
@@ -828,7 +838,7 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     // step vectors: they issue in the latency of those and under the products,
     // not between a step's result and the next barrier.
     auto step = [&](int s, Slot& S, Slot& F, auto pre) {
-        if constexpr (NW > 1) __syncthreads();
+        if constexpr (NW > 1) step_sync();
         cplx<T> b[KS];
         M.vectors(b, u, tb[NW > 1 ? s & 1 : 0]);
         __builtin_amdgcn_sched_barrier(0);
@@ -1077,7 +1087,7 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
             u[v] = (t - (cm * sinv2[v]) * ym[v]) - (cp * sinv2[v]) * yp[v];
             if constexpr (NW > 1) tb[smax & 1][row[v]][li] = u[v];
         }
-        if constexpr (NW > 1) __syncthreads();
+        if constexpr (NW > 1) step_sync();
         cplx<T> b[KS];
         M.vectors(b, u, tb[NW > 1 ? smax & 1 : 0]);
         const CTile<T> acc = M.product(f, b);
@@ -1090,7 +1100,7 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     // outputs of step s + 1 under the products (the maps' outputs, entries of one
     // row, stay at the step's end)
     auto step = [&](int s, Slot& S, Slot& F, auto pre) {
-        if constexpr (NW > 1) __syncthreads();
+        if constexpr (NW > 1) step_sync();
         cplx<T> b[KS];
         M.vectors(b, u, tb[NW > 1 ? s & 1 : 0]);
         __builtin_amdgcn_sched_barrier(0);
