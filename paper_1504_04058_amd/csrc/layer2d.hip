@@ -498,9 +498,9 @@ __global__ __launch_bounds__(FB) void rgf2d_kernel(const SubDesc* __restrict__ d
 }
 
 // ----------------------------------------------------------------------------
-// batched solves on the matrix cores: one workgroup of LR / 16 wavefronts per
-// (auxiliary problem, chunk of 16 right-hand sides, half), one 16-row tile of
-// the step vectors per wavefront.  The forward kernel runs both halves towards
+// batched solves on the matrix cores: one workgroup per (auxiliary problem,
+// chunk of 16 right-hand sides, half), one or two wavefronts per 16-row tile of
+// the step vectors.  The forward kernel runs both halves towards
 // the middle block and keeps its results in scratch; the backward kernel
 // solves the middle block (each half for itself) and runs outwards.  A block
 // step is the product of S_k^-1 with the chunk's step vectors.  The wavefront's
@@ -586,13 +586,19 @@ __device__ __forceinline__ zd uniform_load(const zd* p) {
     return mk(q[0], q[1]);
 }
 
-// one wavefront's 16-row tile of a block step
-template <typename T, int LR, bool SPL>
+// One wavefront's 16-row tile of a block step, or (KW = 2) its product over half
+// of the columns.  With KW = 1 a wavefront holds the rows of its result tile of
+// the step vectors and reads the others' from LDS; with KW = 2 it holds those of
+// its columns: every wavefront puts its product's share into LDS and forms its
+// entries of the next step vector from the sum of the shares, one barrier per
+// step either way.
+template <typename T, int LR, bool SPL, int KW>
 struct BlockTile {
     static constexpr int NW = LR / 16;
-    static constexpr int KS = (sizeof(T) == 8 && LR == 64) ? 12 : LR / 4;   // operand entries per lane
+    static constexpr int KS = ((sizeof(T) == 8 && LR == 64) ? 12 : LR / 4) / KW;   // operand entries per lane
+    static constexpr int NX = KW > 1 ? KS : 4;   // entries of the step vectors a lane holds
     static constexpr int TBS = RC + 1;   // padded row stride of the step vectors in LDS
-    int l, li, lk, rt, L;
+    int l, li, lk, rt, kq, L;
     unsigned aoff[KS];           // byte offsets of this lane's operand entries, past the range if unused
     __amdgpu_buffer_rsrc_t rf;
     unsigned fstep;
@@ -600,14 +606,50 @@ struct BlockTile {
     // the column of S^-1 that operand entry j of this lane holds
     __device__ __forceinline__ int col(int j) const {
         if constexpr (SPL) return NW == 1 ? 4 * lk + j : 32 * (j >> 3) + 8 * lk + (j & 7);
+        if constexpr (KW > 1) return xrow(j);
         if constexpr (NW == 1) return Mfma<T>::row(l, j);
         return 4 * j + lk;
+    }
+    // the row of entry e of the step vectors: of the wavefront's result tile, or
+    // of its share of the columns
+    __device__ __forceinline__ int xrow(int e) const {
+        if constexpr (KW > 1) {
+            const int j = kq * KS + e;
+            return 16 * (j >> 2) + Mfma<T>::row(l, j & 3);
+        }
+        return 16 * rt + Mfma<T>::row(l, e);
+    }
+    // KW > 1: a product's share of this wavefront into LDS, [share][tile][entry][lane]
+    // (lanes in order: no bank conflicts), and the sum over the shares of the
+    // entries it holds, in a fixed order
+    __device__ __forceinline__ void put(cplx<T>* part, const CTile<T>& acc) const {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[((kq * NW + rt) * 4 + v) * 64 + l] = mk<T>(acc.re[v], acc.im[v]);
+    }
+    __device__ __forceinline__ void gather(const cplx<T>* part, cplx<T> (&x)[NX]) const {
+#pragma unroll
+        for (int e = 0; e < NX; ++e) {
+            const int j = kq * KS + e;
+            x[e] = part[j * 64 + l];
+#pragma unroll
+            for (int q = 1; q < KW; ++q) x[e] = x[e] + part[(q * NW * 4 + j) * 64 + l];
+        }
+    }
+    // LDS so that gather() gives x (rows of the first tile's wavefronts in share 0)
+    __device__ __forceinline__ void put_sum(cplx<T>* part, const cplx<T> (&x)[NX]) const {
+        if (kq > 0)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[((kq * NW + rt) * 4 + v) * 64 + l] = mk<T>(T(0), T(0));
+        if (rt == 0)
+#pragma unroll
+            for (int e = 0; e < NX; ++e) part[(kq * KS + e) * 64 + l] = x[e];
     }
     __device__ __forceinline__ void init(const SubDesc& d, const cplx<T>* F) {
         l = threadIdx.x & 63;
         li = l & 15;
         lk = l >> 4;
-        rt = threadIdx.x >> 6;
+        rt = (threadIdx.x >> 6) % NW;
+        kq = (threadIdx.x >> 6) / NW;
         L = d.L;
         rf = __builtin_amdgcn_make_buffer_rsrc(const_cast<cplx<T>*>(F), 0, 0x7fffffff, BUF_DW3);
         fstep = (unsigned)(L * LR * sizeof(cplx<T>));
@@ -622,10 +664,10 @@ struct BlockTile {
         for (int j = 0; j < KS; ++j) a[j] = buf_load<T>(rf, aoff[j], (unsigned)(blk - 1) * fstep);
     }
     // the step vectors: the lane's own values u (one tile) or the LDS copy tb
-    __device__ __forceinline__ void vectors(cplx<T> (&b)[KS], const cplx<T> (&u)[4], const cplx<T> (*tb)[TBS]) const {
+    __device__ __forceinline__ void vectors(cplx<T> (&b)[KS], const cplx<T> (&u)[NX], const cplx<T> (*tb)[TBS]) const {
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
-            if constexpr (NW == 1)
+            if constexpr (NW == 1 || KW > 1)
                 b[j] = u[j];
             else
                 b[j] = tb[col(j)][li];
@@ -657,7 +699,7 @@ struct BlockTile {
             k3.zero();
 #pragma unroll
             for (int j = 0; j < KS; ++j)
-                if (NW == 1 || j <= KS / 2 || j < ksn) kmac3(k3, a[j], b[j]);
+                if (NW == 1 || KW > 1 || j <= KS / 2 || j < ksn) kmac3(k3, a[j], b[j]);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 acc.re[v] = k3.p1[v] - k3.p3[v];
@@ -667,7 +709,7 @@ struct BlockTile {
             acc.zero();
 #pragma unroll
             for (int j = 0; j < KS; ++j)
-                if (NW == 1 || j <= KS / 2 || j < ksn) cmac(acc, a[j], b[j]);
+                if (NW == 1 || KW > 1 || j <= KS / 2 || j < ksn) cmac(acc, a[j], b[j]);
         }
         return acc;
     }
@@ -693,7 +735,7 @@ struct SolveItem {
 // loop entered after an explicit wait for everything the compiler takes the
 // barrier's own wait at the loop's head for redundant, also on the way round,
 // where LDS writes are outstanding (seen in the code of the step loops: another
-// wavefront could then read the vectors of two steps before).
+// wavefront then read what the step before the last had left).
 __device__ __forceinline__ void step_sync() {
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
     __syncthreads();
@@ -705,8 +747,7 @@ __device__ __forceinline__ void step_sync() {
 // 511, ms per apply: two steps 0.353, three 0.274, five 0.276).  The other
 // steps are longer and a fourth slot would spill: two ahead; the maps' chains
 // have the chip full (three steps ahead: 5% slower).  Wavefronts per SIMD that
-// the registers are held to: at three the slots spill; FP64 in 32 rows spills a
-// little at two and is still 5% faster than at one.
+// the registers are held to: at three the slots spill.
 template <typename T, int LR, int INM>
 constexpr int nslot() { return LR == 16 && INM != IN_TWIST && sizeof(T) == 4 ? 4 : 3; }
 template <typename T, int LR>
@@ -717,12 +758,15 @@ constexpr int solve_waves() { return LR == 64 ? 1 : 2; }
 // address or one past the resource's range (no traffic), and the loop has no
 // branch around one: the wait for a load issued some steps ahead then counts
 // exactly the operations issued after it.
-template <typename T, int LR, int INM, bool SPL>
-__global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_fwd_kernel(SolveArgs a) {
+template <typename T, int LR, int INM, bool SPL, int KW>
+__global__ __launch_bounds__(4 * LR * KW) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_fwd_kernel(SolveArgs a) {
     static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
-    using Tile = BlockTile<T, LR, SPL>;
-    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T, LR, INM>();
-    __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
+    using Tile = BlockTile<T, LR, SPL, KW>;
+    constexpr int NW = Tile::NW, KS = Tile::KS, NX = Tile::NX, NS = nslot<T, LR, INM>();
+    constexpr bool TB_LDS = NW > 1 && KW == 1;
+    constexpr int GO = KW > 1 ? 0 : 1;   // a slot's data: of the step's block or of the next one
+    __shared__ cplx<T> tb[TB_LDS ? 2 : 1][TB_LDS ? LR : 1][Tile::TBS];
+    __shared__ cplx<T> part[2][KW > 1 ? KW * LR * 16 : 1];   // KW > 1: shares of the products
     const int nchunk = (a.nact + RC - 1) / RC;
     const SolveItem it(a.njobs, nchunk);
     if (!it.ok) return;
@@ -741,13 +785,13 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         reinterpret_cast<cplx<T>*>(a.y) + ((long long)it.jl * nchunk + it.ch) * n * LR * RC, 0, 0x7fffffff,
         BUF_DW3);
     constexpr unsigned ystep = LR * RC * sizeof(cplx<T>);
-    unsigned yoff[4];
-    cplx<T> sinv2[4];
+    unsigned yoff[NX];
+    cplx<T> sinv2[NX];
     // step data: the rows of X (IN_GRID), or the boundary data on the carrying
     // row (IN_BOUNDARY, one entry per lane at most); rows without data and lanes
     // past the right-hand sides lie past the resource's range and read zero
     const bool valid = it.ch * RC + li < a.nact;
-    constexpr int NG = INM == IN_GRID ? 4 : 1;
+    constexpr int NG = INM == IN_GRID ? NX : 1;
     using TG = std::conditional_t<INM == IN_GRID, T, double>;
     const long long line_len = (long long)n * a.nact;
     const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(
@@ -757,14 +801,14 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         0, 0x7fffffff, BUF_DW3);
     const unsigned gstep = (unsigned)(a.nact * sizeof(cplx<TG>));
     unsigned goff[NG];
-    bool use[4];
+    bool use[NX];
     if (INM != IN_GRID) goff[0] = BUF_OOB;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int row = 16 * M.rt + Mfma<T>::row(M.l, v);
+    for (int v = 0; v < NX; ++v) {
+        const int row = M.xrow(v);
         const int line = d.lo + row;
         const bool rowv = row < L;
-        yoff[v] = rowv ? (unsigned)((row * RC + li) * sizeof(cplx<T>)) : BUF_OOB;
+        yoff[v] = rowv && (KW == 1 || M.rt == 0) ? (unsigned)((row * RC + li) * sizeof(cplx<T>)) : BUF_OOB;
         sinv2[v] = rowv ? ccast<T>(tab[L + 1 + row]) : mk<T>(0, 0);
         if (INM == IN_GRID) {
             use[v] = rowv && line >= d.xs && line <= d.xe;
@@ -779,32 +823,32 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         cplx<TG> g[NG];  // data of step s + 1
         zd sh, ism;      // s1 between blocks s and s + 1; 1 / (s1 h^2) at block s + 1
     };
-    // data of block s + 1 (the middle block past the last step: unused)
+    // data of block s + GO (the middle block past the last step: unused)
     auto fetch = [&](Slot& S, int s) {
         const int sc = min(s, H.np);
         M.load(S.f, H.blk(sc));
-        const int k = H.blk(sc + 1);
+        const int k = H.blk(sc + GO);
 #pragma unroll
         for (int e = 0; e < NG; ++e) S.g[e] = buf_load<TG>(rg, goff[e], (unsigned)(k - 1) * gstep);
     };
     auto fetch_coef = [&](Slot& S, int s) {
         const int sc = min(s, H.np);
-        S.sh = uniform_load(a.ax.sh + H.half_line(sc));
-        if (INM != IN_GRID) S.ism = uniform_load(a.ax.inv_sh2 + H.blk(sc + 1) - 1);
+        S.sh = uniform_load(a.ax.sh + H.half_line(sc - 1 + GO));
+        if (INM != IN_GRID) S.ism = uniform_load(a.ax.inv_sh2 + H.blk(sc + GO) - 1);
     };
-    cplx<T> u[4];
-    auto input = [&](const cplx<TG> (&g)[NG], zd ism, cplx<T> shc, const cplx<T> (&y)[4], int buf) {
+    cplx<T> u[NX];
+    auto input = [&](const cplx<TG> (&g)[NG], zd ism, cplx<T> shc, const cplx<T> (&y)[NX], int buf) {
         cplx<T> gb;
         if constexpr (INM != IN_GRID) gb = ccast<T>(ccast<double>(g[0]) * -(coupl * ism));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < NX; ++v) {
             cplx<T> t;
             if constexpr (INM == IN_GRID)
                 t = ccast<T>(g[v % NG]);
             else
                 t = csel(use[v], gb, mk<T>(T(0), T(0)));
             u[v] = t - (shc * sinv2[v]) * y[v];
-            if constexpr (NW > 1) tb[buf][16 * M.rt + Mfma<T>::row(M.l, v)][li] = u[v];
+            if constexpr (TB_LDS) tb[buf][16 * M.rt + Mfma<T>::row(M.l, v)][li] = u[v];
         }
     };
     Slot sl[NS];
@@ -819,18 +863,21 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
             fetch(sl[q], 1 + q);
             fetch_coef(sl[q], 1 + q);
         }
-        const cplx<T> y0[4] = {mk<T>(0, 0), mk<T>(0, 0), mk<T>(0, 0), mk<T>(0, 0)};
-        input(g0, ism0, mk<T>(T(0), T(0)), y0, 1);
+        cplx<T> y0[NX];
+#pragma unroll
+        for (int e = 0; e < NX; ++e) y0[e] = mk<T>(T(0), T(0));
+        if constexpr (KW > 1) M.put_sum(part[1], y0);
+        else input(g0, ism0, mk<T>(T(0), T(0)), y0, 1);
     }
     // nothing outstanding on entry: the waits in the loop count its own operations
     __builtin_amdgcn_s_waitcnt(0);
-    cplx<T> y[4];
+    cplx<T> y[NX];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) y[v] = mk<T>(T(0), T(0));
+    for (int v = 0; v < NX; ++v) y[v] = mk<T>(T(0), T(0));
     auto store = [&](int s) {
         const unsigned ys = (unsigned)(H.blk(max(s, 1)) - 1) * ystep;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) buf_store(ry, yoff[v], ys, y[v]);
+        for (int v = 0; v < NX; ++v) buf_store(ry, yoff[v], ys, y[v]);
     };
     // F: the slot of step s - 1, free to take the loads of step s + NS - 1.  The
     // step's memory operations (those loads, the previous step's results; before
@@ -838,19 +885,27 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     // step vectors: they issue in the latency of those and under the products,
     // not between a step's result and the next barrier.
     auto step = [&](int s, Slot& S, Slot& F, auto pre) {
-        if constexpr (NW > 1) step_sync();
+        if constexpr (NW > 1 || KW > 1) step_sync();
         cplx<T> b[KS];
-        M.vectors(b, u, tb[NW > 1 ? s & 1 : 0]);
+        if constexpr (KW > 1) {
+            M.gather(part[s & 1], y);
+            input(S.g, S.ism, ccast<T>(S.sh), y, 0);
+        }
+        M.vectors(b, u, tb[TB_LDS ? s & 1 : 0]);
         __builtin_amdgcn_sched_barrier(0);
         store(s - 1);
         if constexpr (decltype(pre)::value) fetch(F, s + NS - 1);
-        if constexpr (NW > 1) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TB_LDS) __builtin_amdgcn_sched_barrier(0);
         const CTile<T> acc = M.product(S.f, b);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (decltype(pre)::value) fetch_coef(F, s + NS - 1);
+        if constexpr (KW > 1) {
+            M.put(part[(s + 1) & 1], acc);
+        } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) y[v] = mk<T>(acc.re[v], acc.im[v]);
-        input(S.g, S.ism, ccast<T>(S.sh), y, (s + 1) & 1);
+            for (int v = 0; v < 4; ++v) y[v] = mk<T>(acc.re[v], acc.im[v]);
+            input(S.g, S.ism, ccast<T>(S.sh), y, (s + 1) & 1);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     int s = 1;
@@ -860,6 +915,10 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
 #pragma unroll
     for (int q = 0; q < NS - 1; ++q)
         if (s + q <= H.np) step(s + q, sl[q], sl[q], std::false_type{});
+    if constexpr (KW > 1) {
+        step_sync();
+        M.gather(part[(H.np + 1) & 1], y);
+    }
     store(H.np);
 }
 
@@ -867,13 +926,16 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
 // outwards; outputs on the lines of X.  IN_TWIST (the boundary maps): chains
 // towards the end of the half that start from columns of the diagonal blocks
 // of H^-1 (kind 0) or from the unit vectors at the middle block (kind 2).
-template <typename T, int LR, int INM, bool SPL>
-__global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_bwd_kernel(SolveArgs a) {
+template <typename T, int LR, int INM, bool SPL, int KW>
+__global__ __launch_bounds__(4 * LR * KW) ASP_PLAIN_ACC(solve_waves<T, LR>()) void solve2d_bwd_kernel(SolveArgs a) {
     static_assert(!SPL || std::is_same<T, float>::value, "the split products take FP32 operands");
-    using Tile = BlockTile<T, LR, SPL>;
-    constexpr int NW = Tile::NW, KS = Tile::KS, NS = nslot<T, LR, INM>();
+    using Tile = BlockTile<T, LR, SPL, KW>;
+    constexpr int NW = Tile::NW, KS = Tile::KS, NX = Tile::NX, NS = nslot<T, LR, INM>();
+    constexpr bool TB_LDS = NW > 1 && KW == 1;
+    constexpr int YO = KW > 1 ? 1 : 0;   // a slot's y: of the step's block or of the one before
     constexpr bool TW = INM == IN_TWIST;
-    __shared__ cplx<T> tb[NW > 1 ? 2 : 1][NW > 1 ? LR : 1][Tile::TBS];
+    __shared__ cplx<T> tb[TB_LDS ? 2 : 1][TB_LDS ? LR : 1][Tile::TBS];
+    __shared__ cplx<T> part[2][KW > 1 ? KW * LR * 16 : 1];
     const int n = a.n, p = mid_block(n);
     int jl, ch, dir, nchunk;
     bool below = false;   // IN_TWIST kind 0: the triangle away from the diagonal's chains
@@ -917,12 +979,12 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     const int grow = (d.kind == ASP_SUB_R) ? 0 : L - 1;
     const int jout = (d.kind == ASP_SUB_R) ? (d.xe - d.lo) : (d.xs - d.lo);   // outgoing line
     const zd coupl = (d.kind == ASP_SUB_R) ? tab[0] : tab[L];
-    int row[4];
-    bool rowv[4];
-    cplx<T> sinv2[4];
+    int row[NX];
+    bool rowv[NX];
+    cplx<T> sinv2[NX];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        row[v] = 16 * M.rt + Mfma<T>::row(M.l, v);
+    for (int v = 0; v < NX; ++v) {
+        row[v] = M.xrow(v);
         rowv[v] = row[v] < L;
         sinv2[v] = rowv[v] ? ccast<T>(tab[L + 1 + row[v]]) : mk<T>(0, 0);
     }
@@ -939,9 +1001,9 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
                                 ((long long)jl * nchunk + ch) * n * LR * RC),
         0, 0x7fffffff, BUF_DW3);
     constexpr unsigned ystep = (TW ? 2 * LR : LR * RC) * sizeof(cplx<T>);
-    unsigned yoff[4];
+    unsigned yoff[NX];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int v = 0; v < NX; ++v)
         yoff[v] = !rowv[v] ? BUF_OOB
                   : TW     ? (unsigned)(((below ? LR : 0) + row[v]) * sizeof(cplx<T>))
                            : (unsigned)((row[v] * RC + li) * sizeof(cplx<T>));
@@ -950,16 +1012,16 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
     // coupling, or column jout (below); kind 2 adds nothing after the start
     const cplx<T> cin_s =
         TW && !below ? ccast<T>(-(coupl * a.ax.inv_sh2[H.blk(min(slot, n - 1) + 1) - 1])) : mk<T>(T(1), T(0));
-    auto load_y = [&](int s, cplx<T> (&y)[4]) {
+    auto load_y = [&](int s, cplx<T> (&y)[NX]) {
         const int k = H.blk(max(s, 1));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) y[v] = buf_load<T>(ry, yoff[v], (unsigned)(k - 1) * ystep);
+        for (int v = 0; v < NX; ++v) y[v] = buf_load<T>(ry, yoff[v], (unsigned)(k - 1) * ystep);
     };
-    auto use_y = [&](int s, cplx<T> (&y)[4]) {
+    auto use_y = [&](int s, cplx<T> (&y)[NX]) {
         if constexpr (TW) {
             const bool st = a.twist_kind == 0 && valid && slot == s - 1;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) y[v] = csel(st, cin_s * y[v], mk<T>(T(0), T(0)));
+            for (int v = 0; v < NX; ++v) y[v] = csel(st, cin_s * y[v], mk<T>(T(0), T(0)));
         }
     };
 
@@ -973,27 +1035,32 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
                                 (d.xs - 1) * line_len + ch * RC),
         0, 0x7fffffff, BUF_DW3);
     const unsigned ostep = (unsigned)(a.nact * sizeof(cplx<T>));
-    unsigned ooff[4];
+    unsigned ooff[NX];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < NX; ++v) {
         const int line = d.lo + row[v];
-        const bool inX = valid && rowv[v] && line >= d.xs && line <= d.xe;
+        const bool inX = valid && rowv[v] && (KW == 1 || M.rt == 0) && line >= d.xs && line <= d.xe;
         ooff[v] = inX ? (unsigned)(((line - d.xs) * line_len + li) * sizeof(cplx<T>)) : BUF_OOB;
     }
     // IN_TWIST: the wavefront and lanes holding the row a map entry is read from
     const int jrow = below ? grow : jout;
-    const bool jmine = TW && (jrow >> 4) == M.rt, gmine = TW && (grow >> 4) == M.rt, omine = TW && (jout >> 4) == M.rt;
-    auto pick = [&](const cplx<T> (&x)[4], int r, bool& hit) {
+    auto mine = [&](int r) {
+        if constexpr (KW > 1)
+            return M.rt == 0 && (4 * (r >> 4) + (sizeof(T) == 8 ? (r & 15) >> 2 : r & 3)) / KS == M.kq;
+        return (r >> 4) == M.rt;
+    };
+    const bool jmine = TW && mine(jrow), gmine = TW && mine(grow), omine = TW && mine(jout);
+    auto pick = [&](const cplx<T> (&x)[NX], int r, bool& hit) {
         cplx<T> y = x[0];
         hit = row[0] == r;
 #pragma unroll
-        for (int v = 1; v < 4; ++v) {
+        for (int v = 1; v < NX; ++v) {
             y = csel(row[v] == r, x[v], y);
             hit = hit || row[v] == r;
         }
         return y;
     };
-    auto emit = [&](int s, const cplx<T> (&x)[4]) {
+    auto emit = [&](int s, const cplx<T> (&x)[NX]) {
         const int k = H.blk(s);
         if constexpr (TW) {
             bool hit;
@@ -1026,27 +1093,27 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
         }
         const bool skip = dir && s > H.np;   // the middle block is half 0's
 #pragma unroll
-        for (int v = 0; v < 4; ++v) buf_store(rs, skip ? BUF_OOB : ooff[v], (unsigned)(k - 1) * ostep, x[v]);
+        for (int v = 0; v < NX; ++v) buf_store(rs, skip ? BUF_OOB : ooff[v], (unsigned)(k - 1) * ostep, x[v]);
     };
 
     // -- start --------------------------------------------------------------------
     struct Slot {
-        cplx<T> f[KS], y[4];   // operand and y of step s
+        cplx<T> f[KS], y[NX];   // operand and y of step s
         zd sh;                 // s1 between blocks s - 1 and s
     };
     auto fetch = [&](Slot& S, int s) {
         const int sc = max(s, 1);
         M.load(S.f, H.blk(sc));
-        load_y(s, S.y);
+        load_y(s + YO, S.y);
     };
-    auto fetch_coef = [&](Slot& S, int s) { S.sh = uniform_load(a.ax.sh + H.half_line(max(s - 1, 0))); };
-    cplx<T> x[4], u[4];
+    auto fetch_coef = [&](Slot& S, int s) { S.sh = uniform_load(a.ax.sh + H.half_line(max(s - 1 + YO, 0))); };
+    cplx<T> x[NX], u[NX], y1[NX];
     // E x_{s+1} (sh: s1 between blocks s and s + 1) for step s
     auto coupled = [&](int s, cplx<T> shc) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < NX; ++v) {
             u[v] = (shc * sinv2[v]) * x[v];
-            if constexpr (NW > 1) tb[s & 1][row[v]][li] = u[v];
+            if constexpr (TB_LDS) tb[s & 1][row[v]][li] = u[v];
         }
     };
     Slot sl[NS];
@@ -1061,22 +1128,22 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
             use_y(smax, x);
         } else {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) x[v] = mk<T>(row[v] == slot ? T(1) : T(0), T(0));
+            for (int v = 0; v < NX; ++v) x[v] = mk<T>(row[v] == slot ? T(1) : T(0), T(0));
         }
-        if (a.twist_kind == 0 || dir == 0) emit(smax, x);
+        if (KW == 1 && (a.twist_kind == 0 || dir == 0)) emit(smax, x);
     } else {
         // x_p = M_p^-1 (g_p - E_{p-1} y_{p-1} - E_p y_{p+1})
-        cplx<T> ym[4], yp[4], f[KS];
+        cplx<T> ym[NX], yp[NX], f[KS];
         M.load(f, p);
         const cplx<T> cm = p > 1 ? ccast<T>(a.ax.sh[p - 1]) : mk<T>(T(0), T(0));
         const cplx<T> cp = p < n ? ccast<T>(a.ax.sh[p]) : mk<T>(T(0), T(0));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < NX; ++v) {
             ym[v] = buf_load<T>(ry, p > 1 ? yoff[v] : BUF_OOB, (unsigned)(max(p - 1, 1) - 1) * ystep);
             yp[v] = buf_load<T>(ry, p < n ? yoff[v] : BUF_OOB, (unsigned)(min(p + 1, n) - 1) * ystep);
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < NX; ++v) {
             const int line = d.lo + row[v];
             cplx<T> t = mk<T>(T(0), T(0));
             if (INM == IN_GRID && valid && rowv[v] && line >= d.xs && line <= d.xe)
@@ -1085,36 +1152,68 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
                 t = ccast<T>(a.W[d.wrow * line_len + (long long)(p - 1) * a.nact + slot] *
                              -(coupl * a.ax.inv_sh2[p - 1]));
             u[v] = (t - (cm * sinv2[v]) * ym[v]) - (cp * sinv2[v]) * yp[v];
-            if constexpr (NW > 1) tb[smax & 1][row[v]][li] = u[v];
+            if constexpr (TB_LDS) tb[smax & 1][row[v]][li] = u[v];
         }
-        if constexpr (NW > 1) step_sync();
+        if constexpr (TB_LDS) step_sync();
         cplx<T> b[KS];
-        M.vectors(b, u, tb[NW > 1 ? smax & 1 : 0]);
+        M.vectors(b, u, tb[TB_LDS ? smax & 1 : 0]);
         const CTile<T> acc = M.product(f, b);
+        if constexpr (KW > 1) {
+            M.put(part[smax & 1], acc);
+            step_sync();
+            M.gather(part[smax & 1], x);
+        } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = mk<T>(acc.re[v], acc.im[v]);
+            for (int v = 0; v < 4; ++v) x[v] = mk<T>(acc.re[v], acc.im[v]);
+        }
     }
-    if (smax > 1) coupled(smax - 1, ccast<T>(a.ax.sh[H.half_line(smax - 1)]));
+    if constexpr (KW > 1) {
+        // the first step takes x_smax as y - (sum of the shares) with y = 0
+        load_y(1, y1);
+        cplx<T> nx[NX];
+#pragma unroll
+        for (int e = 0; e < NX; ++e) {
+            nx[e] = mk<T>(-x[e].x, -x[e].y);
+            sl[0].y[e] = mk<T>(T(0), T(0));
+            if (smax == 1) y1[e] = mk<T>(T(0), T(0));
+        }
+        M.put_sum(part[(smax - 1) & 1], nx);
+    } else {
+        if (smax > 1) coupled(smax - 1, ccast<T>(a.ax.sh[H.half_line(smax - 1)]));
+    }
     __builtin_amdgcn_s_waitcnt(0);
     // the order of the forward pass's step: the loads of step s - NS + 1 and the
     // outputs of step s + 1 under the products (the maps' outputs, entries of one
     // row, stay at the step's end)
     auto step = [&](int s, Slot& S, Slot& F, auto pre) {
-        if constexpr (NW > 1) step_sync();
+        if constexpr (NW > 1 || KW > 1) step_sync();
         cplx<T> b[KS];
-        M.vectors(b, u, tb[NW > 1 ? s & 1 : 0]);
+        if constexpr (KW > 1) {
+            M.gather(part[s & 1], x);
+            use_y(s + 1, S.y);
+#pragma unroll
+            for (int v = 0; v < NX; ++v) x[v] = S.y[v] - x[v];
+            coupled(s, ccast<T>(S.sh));
+        }
+        M.vectors(b, u, tb[TB_LDS ? s & 1 : 0]);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!TW) emit(s + 1, x);
         if constexpr (decltype(pre)::value) fetch(F, s - NS + 1);
-        if constexpr (NW > 1) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TB_LDS) __builtin_amdgcn_sched_barrier(0);
         const CTile<T> acc = M.product(S.f, b);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (decltype(pre)::value) fetch_coef(F, s - NS + 1);
-        use_y(s, S.y);
+        if constexpr (KW > 1) {
+            M.put(part[(s + 1) & 1], acc);
+            if constexpr (TW)
+                if (s + 1 < smax || a.twist_kind == 0 || dir == 0) emit(s + 1, x);
+        } else {
+            use_y(s, S.y);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = S.y[v] - mk<T>(acc.re[v], acc.im[v]);
-        if constexpr (TW) emit(s, x);
-        coupled(s - 1, ccast<T>(S.sh));
+            for (int v = 0; v < 4; ++v) x[v] = S.y[v] - mk<T>(acc.re[v], acc.im[v]);
+            if constexpr (TW) emit(s, x);
+            coupled(s - 1, ccast<T>(S.sh));
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     int s = smax - 1;
@@ -1124,7 +1223,17 @@ __global__ __launch_bounds__(4 * LR) ASP_PLAIN_ACC(solve_waves<T, LR>()) void so
 #pragma unroll
     for (int q = 0; q < NS - 1; ++q)
         if (s - q >= 1) step(s - q, sl[q], sl[q], std::false_type{});
-    if constexpr (!TW) emit(1, x);
+    if constexpr (KW > 1) {
+        step_sync();
+        M.gather(part[0], x);
+        use_y(1, y1);
+#pragma unroll
+        for (int v = 0; v < NX; ++v) x[v] = y1[v] - x[v];
+    }
+    if constexpr (!TW)
+        emit(1, x);
+    else if (KW > 1 && (smax > 1 || a.twist_kind == 0 || dir == 0))
+        emit(1, x);
 }
 
 // ----------------------------------------------------------------------------
@@ -1661,28 +1770,41 @@ hipError_t launch_rgf2d(const asp_plan* P, int job0, int job1, int njobs, hipStr
 
 // one kernel per (precision, row count, input mode): the M-solves, the R/L
 // solves and the map chains are separate kernels
-template <typename T, int LR, int INM, bool SPL>
+template <typename T, int LR, int INM, bool SPL, int KW>
 static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st) {
     if (INM == IN_TWIST) {
         const int half = (mid_block(a.n) + RC - 1) / RC;
         const unsigned blocks = a.twist_kind == 0 ? 4u * a.njobs * half : 2u * a.njobs * nchunk;
-        hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL>), dim3(blocks), dim3(4 * LR), 0, st, a);
+        hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL, KW>), dim3(blocks), dim3(4 * LR * KW), 0, st, a);
         return hipGetLastError();
     }
     constexpr int FWD = INM == IN_TWIST ? IN_GRID : INM;   // map chains have no forward pass
     const unsigned blocks = (2u * a.njobs * nchunk + 7) / 8 * 8;
-    hipLaunchKernelGGL((solve2d_fwd_kernel<T, LR, FWD, SPL>), dim3(blocks), dim3(4 * LR), 0, st, a);
+    hipLaunchKernelGGL((solve2d_fwd_kernel<T, LR, FWD, SPL, KW>), dim3(blocks), dim3(4 * LR * KW), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL>), dim3(blocks), dim3(4 * LR), 0, st, a);
+    hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL, KW>), dim3(blocks), dim3(4 * LR * KW), 0, st, a);
     return hipGetLastError();
 }
 
+// Wavefronts per 16-row tile.  Two halve the chain of products of a block step
+// (FP64: 64 cycles each): ms per solve with one / two at n = 255 (FP64) M 0.65 /
+// 0.54, R and L 0.38 / 0.30; n = 511 (FP32) M 3.79 / 3.19; sequential n = 150
+// (FP32) 12.5 / 10.0; n = 700 (FP64, 16-row and 32-row problems, every SIMD in
+// use) 22.1 / 22.0.  In FP32 only while the tiles of all layers, with one chunk
+// of right-hand sides, leave half of the SIMDs idle: n = 1023 (255 layers of 32
+// rows) M 53.2 / 59.2, bound by its memory instructions, of which the second
+// wavefront repeats the data's.  A rule on the plan alone, so that a result does
+// not depend on the batch.  The bf16-split products run over 32 columns at once.
+constexpr int SOLVE_SPLIT_WAVES = 512;
+
 template <int LR, int INM>
 static hipError_t launch_solve_lr(const asp_plan* P, const SolveArgs& a, int nchunk, hipStream_t st) {
-    if (P->prec == ASP_PREC_BF16X3) return launch_solve_t<float, LR, INM, true>(a, nchunk, st);
-    if (P->prec != ASP_PREC_FP64) return launch_solve_t<float, LR, INM, false>(a, nchunk, st);
-    return launch_solve_t<double, LR, INM, false>(a, nchunk, st);
+    if (P->prec == ASP_PREC_BF16X3) return launch_solve_t<float, LR, INM, true, 1>(a, nchunk, st);
+    if (P->prec == ASP_PREC_FP64) return launch_solve_t<double, LR, INM, false, 2>(a, nchunk, st);
+    if (2LL * P->m * (LR / 16) <= SOLVE_SPLIT_WAVES)
+        return launch_solve_t<float, LR, INM, false, 2>(a, nchunk, st);
+    return launch_solve_t<float, LR, INM, false, 1>(a, nchunk, st);
 }
 
 template <int LR>
