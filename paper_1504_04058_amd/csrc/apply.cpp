@@ -285,17 +285,15 @@ asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int n
     return ASP_OK;
 }
 
-// boundary-to-boundary maps: T^R_p = (G~^R_p e_c) on the last line of X_p and
-// T^L_p = (G~^L_p e_c) on the first line of X_p, c = 1..n, for 1 < p < m
 // The boundary maps T^R_p, T^L_p (1 < p < m): column c of a map is the outgoing
-// line of G~ applied to unit data at i1 = c + 1.  With the forward factors
-// S_k^-1 and the diagonal blocks G_k of H^-1 (launch_rgf2d), the solution for
-// unit data at block c + 1 is the coupling times column grow of G_{c+1} there
-// and, towards block 1, x_k = -S_k^-1 E_k x_{k+1}: the map entries on and
-// above the diagonal (IN_TWIST kind 0).  The entries below it come from the
-// solutions for unit data on the outgoing line (column jout of G_{r+1}), read
-// on the data line, since H is complex symmetric (kind 1).  No forward sweep
-// and no scratch: a chunk of columns is one chain of at most (ch + 1) SRB steps.
+// line of G~ (the last line of X_p for R, the first for L) for unit data at
+// i1 = c + 1.  With the diagonal blocks G_k of H^-1 (launch_rgf2d), the solution
+// at the data's block is the coupling times column grow of G_{c+1}, and from
+// there towards the end of its half x_k = -S_k^-1 E_k x_{k+1}: the entries on one
+// side of the diagonal; the other side comes from unit data on the outgoing line
+// (column jout of G), read on the data line, since H is complex symmetric
+// (IN_TWIST kind 0: both).  Entries between the halves are products of two rows
+// of the propagators from the middle block (kind 2, then launch_map_cross).
 static asp_status compute_transfer(asp_plan* P) {
     const int m = P->m;
     if (m < 3) return ASP_OK;

@@ -75,8 +75,8 @@ __host__ __device__ __forceinline__ cplx<To> ccast(cplx<Ti> a) { return {(To)a.x
 // ---------------------------------------------------------------------------
 // Block-tridiagonal layout of a 2D auxiliary problem on sweep lines lo..hi
 // (L lines): block k (k = i1 = 1..n) holds the L unknowns (i1 = k, lo..hi).
-// The factor stores, for every k, S_k^-1 (S_k the Schur complement of the
-// block recurrence) column-major with leading dimension LR >= L (rows past L
+// The factor stores, for every k, the inverse of block k's Schur complement in
+// the elimination from both ends towards mid_block(n), column-major with leading dimension LR >= L (rows past L
 // zero): entry (i, j) of block k at [(k-1) L LR + j LR + i], so that the LR
 // lanes holding the rows of one solve load each column coalesced.
 //

@@ -8,11 +8,11 @@
 // with L x L blocks:
 //   D_k      tridiagonal: the sweep-axis couplings s(lo+j+1/2)/(s1(k) h^2) and the diagonal,
 //   E_k      diagonal coupling of block k to k+1: s1(k+1/2) / (s(lo+j) h^2),
-// in the symmetric form.  The block recurrence S_1 = D_1,
-// S_k = D_k - E_{k-1} S_{k-1}^-1 E_{k-1} is the banded LU of the paper in block
-// form; the factor keeps S_k^-1 for every k.  A solve is the forward sweep
-// y_k = S_k^-1 (g_k - E_{k-1} y_{k-1}) and the backward sweep
-// v_k = y_k - S_k^-1 E_k v_{k+1}.
+// in the symmetric form.  The banded LU of the paper in block form, S_k = D_k -
+// E_{k-1} S_{k-1}^-1 E_{k-1}, runs from both ends towards the middle block; the
+// factor keeps the inverse of every block.  A solve is the forward sweep of both
+// halves, y_k = S_k^-1 (g_k - E_{k-1} y_{k-1}), the middle block, and the
+// backward sweep outwards, v_k = y_k - S_k^-1 E_k v_{k+1}.
 #include <algorithm>
 
 #include "asp_internal.h"
