@@ -499,8 +499,8 @@ __global__ __launch_bounds__(FB) void rgf2d_kernel(const SubDesc* __restrict__ d
 
 // ----------------------------------------------------------------------------
 // batched solves on the matrix cores: one workgroup per (auxiliary problem,
-// chunk of 16 right-hand sides, half), one or two wavefronts per 16-row tile of
-// the step vectors.  The forward kernel runs both halves towards
+// chunk of 16 right-hand sides, half), one, two or four wavefronts per 16-row
+// tile of the step vectors.  The forward kernel runs both halves towards
 // the middle block and keeps its results in scratch; the backward kernel
 // solves the middle block (each half for itself) and runs outwards.  A block
 // step is the product of S_k^-1 with the chunk's step vectors.  The wavefront's
@@ -586,9 +586,9 @@ __device__ __forceinline__ zd uniform_load(const zd* p) {
     return mk(q[0], q[1]);
 }
 
-// One wavefront's 16-row tile of a block step, or (KW = 2) its product over half
-// of the columns.  With KW = 1 a wavefront holds the rows of its result tile of
-// the step vectors and reads the others' from LDS; with KW = 2 it holds those of
+// One wavefront's 16-row tile of a block step, or (KW = 2, 4) its product over
+// a share of the columns.  With KW = 1 a wavefront holds the rows of its result tile of
+// the step vectors and reads the others' from LDS; with KW > 1 it holds those of
 // its columns: every wavefront puts its product's share into LDS and forms its
 // entries of the next step vector from the sum of the shares, one barrier per
 // step either way.
@@ -1787,23 +1787,27 @@ static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st)
     return hipGetLastError();
 }
 
-// Wavefronts per 16-row tile.  Two halve the chain of products of a block step
-// (FP64: 64 cycles each): ms per solve with one / two at n = 255 (FP64) M 0.65 /
-// 0.54, R and L 0.38 / 0.30; n = 511 (FP32) M 3.79 / 3.19; sequential n = 150
-// (FP32) 12.5 / 10.0; n = 700 (FP64, 16-row and 32-row problems, every SIMD in
-// use) 22.1 / 22.0.  In FP32 only while the tiles of all layers, with one chunk
-// of right-hand sides, leave half of the SIMDs idle: n = 1023 (255 layers of 32
-// rows) M 53.2 / 59.2, bound by its memory instructions, of which the second
-// wavefront repeats the data's.  A rule on the plan alone, so that a result does
-// not depend on the batch.  The bf16-split products run over 32 columns at once.
+// Wavefronts per 16-row tile.  Several shorten the chain of products of a block
+// step (FP64: 64 cycles each): ms per solve with one / two / four at n = 255
+// (FP64) M 0.65 / 0.54 / 0.50, R and L 0.38 / 0.30 / 0.25; n = 511 (FP32) M 3.79 /
+// 3.24 / 2.72; sequential n = 150 (FP32) 12.5 / 10.1 / 9.0; n = 700 (FP64, 16-row
+// and 32-row problems, every SIMD in use) 22.1 / 22.0 / 22.1.  Two for 64 rows
+// (four would be sixteen wavefronts and 128 KB of shares) and for the map chains,
+// which have the chip full (n = 511: 1.80 / 2.18 with two / four).  In FP32 only
+// while the tiles of all layers, with one chunk of right-hand sides, leave half of
+// the SIMDs idle: n = 1023 (32 rows) M 53.2 / 59.2 with one / two, bound by its
+// memory instructions, of which the other wavefronts repeat the data's.  A rule on
+// the plan alone, so that a result does not depend on the batch.  The bf16-split
+// products run over 32 columns at once.
 constexpr int SOLVE_SPLIT_WAVES = 512;
 
 template <int LR, int INM>
 static hipError_t launch_solve_lr(const asp_plan* P, const SolveArgs& a, int nchunk, hipStream_t st) {
     if (P->prec == ASP_PREC_BF16X3) return launch_solve_t<float, LR, INM, true, 1>(a, nchunk, st);
-    if (P->prec == ASP_PREC_FP64) return launch_solve_t<double, LR, INM, false, 2>(a, nchunk, st);
+    constexpr int KW = LR == 64 || INM == IN_TWIST ? 2 : 4;
+    if (P->prec == ASP_PREC_FP64) return launch_solve_t<double, LR, INM, false, KW>(a, nchunk, st);
     if (2LL * P->m * (LR / 16) <= SOLVE_SPLIT_WAVES)
-        return launch_solve_t<float, LR, INM, false, 2>(a, nchunk, st);
+        return launch_solve_t<float, LR, INM, false, KW>(a, nchunk, st);
     return launch_solve_t<float, LR, INM, false, 1>(a, nchunk, st);
 }
 

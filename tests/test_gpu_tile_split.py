@@ -1,5 +1,5 @@
-"""2D layer solves on both sides of the rule that gives a 16-row tile one or two
-wavefronts (FP32: two up to 256, 128 and 64 layers for problems of 16, 32 and
+"""2D layer solves on both sides of the rule that gives a 16-row tile one or more
+wavefronts (FP32: several up to 256, 128 and 64 layers for problems of 16, 32 and
 64 rows), with problems at the ends of the sweep that leave whole four-column
 steps of a tile unused.  Apply in FP32 against the CPU FP64 oracle (4e-5, the
 bound of the other parity tests on rough fields), one vector bitwise as in a
