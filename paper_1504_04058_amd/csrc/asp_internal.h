@@ -359,6 +359,8 @@ struct SolveLaunch {
     int twist_kind = 0;
 };
 hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t st);
+// wavefronts per 16-row tile of such a launch in input mode `in_mode` (on the plan alone)
+int solve_wavefronts(const asp_plan* P, int in_mode);
 // the map entries between blocks of different halves (after the kind-2 chains)
 hipError_t launch_map_cross(const asp_plan* P, const SolveLaunch& L, hipStream_t st);
 // columns grow and jout of the diagonal blocks of H^-1 of the map problems

@@ -1787,27 +1787,50 @@ static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st)
     return hipGetLastError();
 }
 
-// Wavefronts per 16-row tile.  Several shorten the chain of products of a block
-// step (FP64: 64 cycles each): ms per solve with one / two / four at n = 255
-// (FP64) M 0.65 / 0.54 / 0.50, R and L 0.38 / 0.30 / 0.25; n = 511 (FP32) M 3.79 /
-// 3.24 / 2.72; sequential n = 150 (FP32) 12.5 / 10.1 / 9.0; n = 700 (FP64, 16-row
-// and 32-row problems, every SIMD in use) 22.1 / 22.0 / 22.1.  Two for 64 rows
-// (four would be sixteen wavefronts and 128 KB of shares) and for the map chains,
-// which have the chip full (n = 511: 1.80 / 2.18 with two / four).  In FP32 only
-// while the tiles of all layers, with one chunk of right-hand sides, leave half of
-// the SIMDs idle: n = 1023 (32 rows) M 53.2 / 59.2 with one / two, bound by its
-// memory instructions, of which the other wavefronts repeat the data's.  A rule on
-// the plan alone, so that a result does not depend on the batch.  The bf16-split
-// products run over 32 columns at once.
+// Wavefronts per 16-row tile of a launch (mode: M problems, R and L problems, map
+// chains).  Several shorten the chain of products of a block step (FP64: 64 cycles
+// each): ms per solve with one / two / four at n = 255 (FP64) M 0.65 / 0.54 / 0.50,
+// R and L 0.38 / 0.30 / 0.25; n = 511 (FP32) M 3.79 / 3.24 / 2.72; sequential n = 150
+// (FP32) 12.5 / 10.1 / 9.0.  Two for 64 rows (four would be sixteen wavefronts and
+// 128 KB of shares) and for the map chains, which have the chip full (n = 511:
+// 1.80 / 2.18 with two / four).  In FP32 only while the tiles of the launch's
+// problems, two halves each and one chunk of right-hand sides, leave half of the
+// SIMDs idle; past that the step is bound by its memory instructions, of which the
+// other wavefronts repeat the data's.  ms per apply with one / two / four, 64 (8)
+// right-hand sides, layers of 4 lines:
+//   M, 32 rows      n = 511 (492 tiles)   0.99 / 1.19 / 1.13  (0.48 / 0.40 / 0.34)
+//                   n = 640 (620)         1.57 / 1.81 / 1.78  (0.78 / 0.72 / 0.69)
+//                   n = 1023 (1004)       3.89 / 4.51 / 4.51  (1.26 / 1.28 / 1.25)
+//   R and L, 16     n = 511 (488)         0.67 / 0.67 / 0.72  (0.27 / 0.27 / 0.24)
+//                   n = 640 (616)         1.05 / 1.05 / 1.12  (0.35 / 0.36 / 0.36)
+//                   n = 1023 (1000)       2.58 / 2.74 / 2.82  (0.87 / 0.83 / 0.86)
+// and a sequential sweep, whose launches have two problems at any size (n = 300,
+// layers of one line, 40 right-hand sides): 42.5 / 34.3 / 30.3.
+// In FP64 always: more wavefronts are faster with few right-hand sides and slower
+// with many at every size past 512 tiles (M, one / four: n = 700 1.51 / 1.30 with 4
+// right-hand sides, 1.79 / 1.87 with 24; n = 1023 2.25 / 2.01 with one, 3.64 / 3.74
+// with 24, 6.27 / 7.53 with 64; R and L within 4%), and the rule may look at the plan
+// alone, so that a result does not depend on the batch.  The bf16-split products
+// run over 32 columns at once: one wavefront.
 constexpr int SOLVE_SPLIT_WAVES = 512;
+
+int solve_wavefronts(const asp_plan* P, int in_mode) {
+    if (P->prec == ASP_PREC_BF16X3) return 1;
+    const int LR = in_mode == IN_GRID ? P->LR_M : P->LR_RL;
+    const int problems = in_mode == IN_GRID      ? P->m
+                         : in_mode == IN_TWIST   ? 2 * P->m - 4
+                         : P->sweep_seq          ? 2
+                                                 : 2 * P->m - 2;
+    if (P->prec != ASP_PREC_FP64 && 2LL * problems * (LR / 16) > SOLVE_SPLIT_WAVES) return 1;
+    return LR == 64 || in_mode == IN_TWIST ? 2 : 4;
+}
 
 template <int LR, int INM>
 static hipError_t launch_solve_lr(const asp_plan* P, const SolveArgs& a, int nchunk, hipStream_t st) {
     if (P->prec == ASP_PREC_BF16X3) return launch_solve_t<float, LR, INM, true, 1>(a, nchunk, st);
     constexpr int KW = LR == 64 || INM == IN_TWIST ? 2 : 4;
     if (P->prec == ASP_PREC_FP64) return launch_solve_t<double, LR, INM, false, KW>(a, nchunk, st);
-    if (2LL * P->m * (LR / 16) <= SOLVE_SPLIT_WAVES)
-        return launch_solve_t<float, LR, INM, false, KW>(a, nchunk, st);
+    if (solve_wavefronts(P, INM) > 1) return launch_solve_t<float, LR, INM, false, KW>(a, nchunk, st);
     return launch_solve_t<float, LR, INM, false, 1>(a, nchunk, st);
 }
 
