@@ -1791,9 +1791,13 @@ static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st)
 // chains).  Several shorten the chain of products of a block step (FP64: 64 cycles
 // each): ms per solve with one / two / four at n = 255 (FP64) M 0.65 / 0.54 / 0.50,
 // R and L 0.38 / 0.30 / 0.25; n = 511 (FP32) M 3.79 / 3.24 / 2.72; sequential n = 150
-// (FP32) 12.5 / 10.1 / 9.0.  Two for 64 rows (four would be sixteen wavefronts and
-// 128 KB of shares) and for the map chains, which have the chip full (n = 511:
-// 1.80 / 2.18 with two / four).  In FP32 only while the tiles of the launch's
+// (FP32) 12.5 / 10.1 / 9.0.  Two for the map chains, which have the chip full (n =
+// 511: 1.80 / 2.18 with two / four), and for 64 rows in FP64 (four would be sixteen
+// wavefronts and 128 KB of shares).  In FP32 one for 64 rows, whose four tiles
+// already share a step (ms per apply with one / two, 16 and 64 right-hand sides: M at
+// n = 180, gamma = 20, b = 4 0.32 / 0.40 and 0.56 / 0.82; n = 400, gamma = 24, b = 1
+// 2.19 / 2.93 and 7.65 / 11.0; FP64 n = 250, gamma = 20, b = 8 0.64 / 0.61 and 0.70 /
+// 0.68, n = 600 1.62 / 1.53 and 4.89 / 4.58), else several only while the tiles of the launch's
 // problems, two halves each and one chunk of right-hand sides, leave half of the
 // SIMDs idle; past that the step is bound by its memory instructions, of which the
 // other wavefronts repeat the data's.  ms per apply with one / two / four, 64 (8)
@@ -1821,7 +1825,7 @@ int solve_wavefronts(const asp_plan* P, int in_mode) {
                          : in_mode == IN_TWIST   ? 2 * P->m - 4
                          : P->sweep_seq          ? 2
                                                  : 2 * P->m - 2;
-    if (P->prec != ASP_PREC_FP64 && 2LL * problems * (LR / 16) > SOLVE_SPLIT_WAVES) return 1;
+    if (P->prec != ASP_PREC_FP64 && (LR == 64 || 2LL * problems * (LR / 16) > SOLVE_SPLIT_WAVES)) return 1;
     return LR == 64 || in_mode == IN_TWIST ? 2 : 4;
 }
 
@@ -1830,7 +1834,8 @@ static hipError_t launch_solve_lr(const asp_plan* P, const SolveArgs& a, int nch
     if (P->prec == ASP_PREC_BF16X3) return launch_solve_t<float, LR, INM, true, 1>(a, nchunk, st);
     constexpr int KW = LR == 64 || INM == IN_TWIST ? 2 : 4;
     if (P->prec == ASP_PREC_FP64) return launch_solve_t<double, LR, INM, false, KW>(a, nchunk, st);
-    if (solve_wavefronts(P, INM) > 1) return launch_solve_t<float, LR, INM, false, KW>(a, nchunk, st);
+    if constexpr (LR < 64)
+        if (solve_wavefronts(P, INM) > 1) return launch_solve_t<float, LR, INM, false, KW>(a, nchunk, st);
     return launch_solve_t<float, LR, INM, false, 1>(a, nchunk, st);
 }
 

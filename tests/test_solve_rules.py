@@ -1,7 +1,7 @@
 """The rule that gives a 16-row tile of a 2D layer solve one or more wavefronts
 counts the problems of its own launch (CPU, host-only plans): m for the M
 problems, 2 m - 2 for the R and L problems, two for those of a sequential
-sweep.  tests/solve_rules.cpp asks the built library."""
+sweep; problems of 64 rows take one in FP32.  tests/solve_rules.cpp asks the built library."""
 import os
 import shutil
 import subprocess
@@ -47,6 +47,9 @@ def rules(tmp_path_factory):
     (300, 1, 12, FP32, 1, 1, 4),       # sequential, 278 layers: two R/L problems at a time
     (150, 4, 12, FP32, 1, 4, 4),
     (1023, 4, 12, FP64, 0, 4, 4),
+    (180, 4, 20, FP32, 0, 1, 4),       # M problems of 64 rows: one in FP32,
+    (180, 4, 20, FP64, 0, 2, 4),       # two in FP64
+    (120, 10, 24, FP32, 0, 1, 1),      # R and L problems of 64 rows too
     (1023, 4, 12, SPLIT, 0, 1, 1),
 ])
 def test_wavefronts_of_layer_solves(rules, n, b, gamma, prec, seq, m, rl):
