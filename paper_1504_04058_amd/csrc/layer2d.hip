@@ -1768,13 +1768,14 @@ hipError_t launch_rgf2d(const asp_plan* P, int job0, int job1, int njobs, hipStr
     return launch_rgf_t<double>(P, j0, j1, nl, njobs, st);
 }
 
+static int map_chunks(int n) { return (mid_block(n) + RC - 1) / RC; }   // of a half's columns
+
 // one kernel per (precision, row count, input mode): the M-solves, the R/L
 // solves and the map chains are separate kernels
 template <typename T, int LR, int INM, bool SPL, int KW>
 static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st) {
     if (INM == IN_TWIST) {
-        const int half = (mid_block(a.n) + RC - 1) / RC;
-        const unsigned blocks = a.twist_kind == 0 ? 4u * a.njobs * half : 2u * a.njobs * nchunk;
+        const unsigned blocks = a.twist_kind == 0 ? 4u * a.njobs * map_chunks(a.n) : 2u * a.njobs * nchunk;
         hipLaunchKernelGGL((solve2d_bwd_kernel<T, LR, INM, SPL, KW>), dim3(blocks), dim3(4 * LR * KW), 0, st, a);
         return hipGetLastError();
     }
@@ -1787,56 +1788,79 @@ static hipError_t launch_solve_t(const SolveArgs& a, int nchunk, hipStream_t st)
     return hipGetLastError();
 }
 
-// Wavefronts per 16-row tile of a launch (mode: M problems, R and L problems, map
-// chains).  Several shorten the chain of products of a block step (FP64: 64 cycles
-// each): ms per solve with one / two / four at n = 255 (FP64) M 0.65 / 0.54 / 0.50,
-// R and L 0.38 / 0.30 / 0.25; n = 511 (FP32) M 3.79 / 3.24 / 2.72; sequential n = 150
-// (FP32) 12.5 / 10.1 / 9.0.  Two for the map chains, which have the chip full (n =
-// 511: 1.80 / 2.18 with two / four), and for 64 rows in FP64 (four would be sixteen
-// wavefronts and 128 KB of shares).  In FP32 one for 64 rows, whose four tiles
-// already share a step (ms per apply with one / two, 16 and 64 right-hand sides: M at
-// n = 180, gamma = 20, b = 4 0.32 / 0.40 and 0.56 / 0.82; n = 400, gamma = 24, b = 1
-// 2.19 / 2.93 and 7.65 / 11.0; FP64 n = 250, gamma = 20, b = 8 0.64 / 0.61 and 0.70 /
-// 0.68, n = 600 1.62 / 1.53 and 4.89 / 4.58), else several only while the tiles of the launch's
-// problems, two halves each and one chunk of right-hand sides, leave half of the
-// SIMDs idle; past that the step is bound by its memory instructions, of which the
-// other wavefronts repeat the data's.  ms per apply with one / two / four, 64 (8)
-// right-hand sides, layers of 4 lines:
+// Wavefronts per 16-row tile of a launch: several shorten the chain of products of
+// a block step (FP64: 64 cycles each) but repeat the loads of its data.  A rule on
+// the plan alone, so that a result does not depend on the batch.  (ms per apply with
+// one / two / four wavefronts; layers of 4 lines and gamma = 12 unless stated.)
+//
+// M, R and L, FP32, 16 and 32 rows: four while the tiles of the launch's problems,
+// two halves each and one chunk of right-hand sides, leave half of the SIMDs idle;
+// past that one, the step being bound by its memory instructions.  64 (8)
+// right-hand sides:
 //   M, 32 rows      n = 511 (492 tiles)   0.99 / 1.19 / 1.13  (0.48 / 0.40 / 0.34)
 //                   n = 640 (620)         1.57 / 1.81 / 1.78  (0.78 / 0.72 / 0.69)
 //                   n = 1023 (1004)       3.89 / 4.51 / 4.51  (1.26 / 1.28 / 1.25)
 //   R and L, 16     n = 511 (488)         0.67 / 0.67 / 0.72  (0.27 / 0.27 / 0.24)
 //                   n = 640 (616)         1.05 / 1.05 / 1.12  (0.35 / 0.36 / 0.36)
 //                   n = 1023 (1000)       2.58 / 2.74 / 2.82  (0.87 / 0.83 / 0.86)
-// and a sequential sweep, whose launches have two problems at any size (n = 300,
-// layers of one line, 40 right-hand sides): 42.5 / 34.3 / 30.3.
-// In FP64 always: more wavefronts are faster with few right-hand sides and slower
-// with many at every size past 512 tiles (M, one / four: n = 700 1.51 / 1.30 with 4
-// right-hand sides, 1.79 / 1.87 with 24; n = 1023 2.25 / 2.01 with one, 3.64 / 3.74
-// with 24, 6.27 / 7.53 with 64; R and L within 4%), and the rule may look at the plan
-// alone, so that a result does not depend on the batch.  The bf16-split products
-// run over 32 columns at once: one wavefront.
+//   sequential sweep (two problems per launch at any size), n = 300, layers of one
+//   line, 40 right-hand sides: 42.5 / 34.3 / 30.3
+// FP32, 64 rows: one, the four tiles already sharing a step (M, 16 and 64 right-hand
+// sides: n = 180, gamma = 20 0.32 / 0.40 and 0.56 / 0.82; n = 400, gamma = 24, b = 1
+// 2.19 / 2.93 and 7.65 / 11.0).
+// FP64: four (64 rows: two; four would be sixteen wavefronts and 128 KB of shares).
+// More are faster with few right-hand sides and slower with many at every size past
+// 512 tiles (M, one / four: n = 255 0.35 / 0.26 with 16 right-hand sides; n = 700
+// 1.51 / 1.30 with 4, 1.79 / 1.87 with 24; n = 1023 2.25 / 2.01 with one, 3.64 / 3.74
+// with 24, 6.27 / 7.53 with 64; R and L within 4%; 64 rows, n = 600, gamma = 20, b = 8,
+// one / two: 1.62 / 1.53 with 16, 4.89 / 4.58 with 64).
+//
+// Map chains, which come four per problem and 16 columns of a half: two while their
+// products of 16 x 16 tiles per step are few, else one; one for 64 rows.  ms per
+// factorization with one / two:
+//   FP32  n = 255 (3648) 0.48 / 0.44, 300 (5440) 0.67 / 0.67, 511 with b = 8 and
+//         gamma = 9 (7680) 1.10 / 1.06, 383 (8544) 0.98 / 0.98, 511 (15488) 1.67 / 1.74,
+//         1023 11.2 / 11.7; 32 rows: n = 250, gamma = 20, b = 8 (6400) 1.51 / 1.48,
+//         n = 300, gamma = 17, b = 3 (28160) 2.32 / 2.55
+//   FP64  n = 120 (736) 0.25 / 0.23, 255 (3648) 0.62 / 0.61, 300 (5440) 0.90 / 0.94,
+//         1023 19.3 / 20.5; 32 rows: n = 200, gamma = 20, b = 8 (4256) 1.36 / 1.34,
+//         n = 300, gamma = 5, b = 14 (6080) 1.51 / 1.64
+//   64 rows, n = 300, gamma = 13, b = 24: FP32 8.8 / 9.1, FP64 9.1 / 9.2
+//
+// The bf16-split products run over 32 columns at once: one wavefront.
 constexpr int SOLVE_SPLIT_WAVES = 512;
+constexpr int MAP_SPLIT_PRODUCTS = 8192;   // FP64: half, its products taking twice as long
 
 int solve_wavefronts(const asp_plan* P, int in_mode) {
     if (P->prec == ASP_PREC_BF16X3) return 1;
-    const int LR = in_mode == IN_GRID ? P->LR_M : P->LR_RL;
-    const int problems = in_mode == IN_GRID      ? P->m
-                         : in_mode == IN_TWIST   ? 2 * P->m - 4
-                         : P->sweep_seq          ? 2
-                                                 : 2 * P->m - 2;
-    if (P->prec != ASP_PREC_FP64 && (LR == 64 || 2LL * problems * (LR / 16) > SOLVE_SPLIT_WAVES)) return 1;
-    return LR == 64 || in_mode == IN_TWIST ? 2 : 4;
+    const bool f64 = P->prec == ASP_PREC_FP64;
+    const int LR = in_mode == IN_GRID ? P->LR_M : P->LR_RL, tiles = LR / 16;
+    if (in_mode == IN_TWIST) {
+        const long long products = 4LL * (2 * P->m - 4) * map_chunks(P->n) * tiles * tiles;
+        return LR < 64 && products <= (f64 ? MAP_SPLIT_PRODUCTS / 2 : MAP_SPLIT_PRODUCTS) ? 2 : 1;
+    }
+    if (f64) return LR == 64 ? 2 : 4;
+    const long long problems = in_mode == IN_GRID ? P->m : P->sweep_seq ? 2 : 2 * P->m - 2;
+    return LR < 64 && 2 * problems * tiles <= SOLVE_SPLIT_WAVES ? 4 : 1;
 }
 
 template <int LR, int INM>
 static hipError_t launch_solve_lr(const asp_plan* P, const SolveArgs& a, int nchunk, hipStream_t st) {
     if (P->prec == ASP_PREC_BF16X3) return launch_solve_t<float, LR, INM, true, 1>(a, nchunk, st);
-    constexpr int KW = LR == 64 || INM == IN_TWIST ? 2 : 4;
-    if (P->prec == ASP_PREC_FP64) return launch_solve_t<double, LR, INM, false, KW>(a, nchunk, st);
-    if constexpr (LR < 64)
-        if (solve_wavefronts(P, INM) > 1) return launch_solve_t<float, LR, INM, false, KW>(a, nchunk, st);
-    return launch_solve_t<float, LR, INM, false, 1>(a, nchunk, st);
+    const bool f64 = P->prec == ASP_PREC_FP64, one = solve_wavefronts(P, INM) == 1;
+    if constexpr (INM == IN_TWIST) {
+        if constexpr (LR < 64)
+            if (!one)
+                return f64 ? launch_solve_t<double, LR, INM, false, 2>(a, nchunk, st)
+                           : launch_solve_t<float, LR, INM, false, 2>(a, nchunk, st);
+        return f64 ? launch_solve_t<double, LR, INM, false, 1>(a, nchunk, st)
+                   : launch_solve_t<float, LR, INM, false, 1>(a, nchunk, st);
+    } else {
+        if (f64) return launch_solve_t<double, LR, INM, false, LR == 64 ? 2 : 4>(a, nchunk, st);
+        if constexpr (LR < 64)
+            if (!one) return launch_solve_t<float, LR, INM, false, 4>(a, nchunk, st);
+        return launch_solve_t<float, LR, INM, false, 1>(a, nchunk, st);
+    }
 }
 
 template <int LR>

@@ -37,3 +37,22 @@ def test_tile_split_classes(n, gamma, seq):
     e = float(np.linalg.norm(z[16] - ref) / np.linalg.norm(ref))
     print(f"tile split classes n={n} gamma={gamma} seq={seq}: rel err {e:.2e}", flush=True)
     assert e < 4e-5
+
+
+# (n, b, gamma): sizes around the lines of the map chains' rule (products of 16 x 16
+# tiles: 3584, 5680, 8736; 32 rows 8192 and 8448; 64 rows), FP64 1e-11
+@pytest.mark.parametrize("prec,tol", [(asp.ASP_PREC_FP64, 1e-11), (asp.ASP_PREC_FP32, 4e-5)])
+@pytest.mark.parametrize("n,b,gamma", [(120, 1, 4), (150, 1, 4), (190, 1, 4), (100, 1, 18), (102, 1, 18), (99, 24, 13)])
+def test_map_split(n, b, gamma, prec, tol):
+    print(f"map split n={n} b={b} gamma={gamma} prec={prec}", flush=True)
+    c = workloads.velocity_random(n, 2, seed=9, width=4.0)
+    P = Problem(2, n, 2 * math.pi * (n + 1) / 8, gamma, 25.0, b, c)
+    rng = np.random.default_rng(n)
+    r = rng.standard_normal((1, P.N)) + 1j * rng.standard_normal((1, P.N))
+    with asp.Plan(2, c, P.omega, n, b, gamma, C=P.C, prec=prec) as plan:
+        plan.factor()
+        z = plan.apply(torch.from_numpy(r).cuda()).cpu().numpy()[0]
+    ref = Preconditioner(P).apply(r[0])
+    e = float(np.linalg.norm(z - ref) / np.linalg.norm(ref))
+    print(f"map split n={n} b={b} gamma={gamma} prec={prec}: rel err {e:.2e}", flush=True)
+    assert e < tol

@@ -54,3 +54,22 @@ def rules(tmp_path_factory):
 ])
 def test_wavefronts_of_layer_solves(rules, n, b, gamma, prec, seq, m, rl):
     assert rules(n, b, gamma, prec, seq)[:2] == (m, rl)
+
+
+# map chains (4 x (2 m - 4) problems x chunks of 16 columns of a half x (rows / 16)^2): two
+# wavefronts up to 8192 products of 16 x 16 tiles in FP32, 4096 in FP64; one for 64 rows
+@pytest.mark.parametrize("n,b,gamma,prec,maps", [
+    (255, 4, 12, FP64, 2),      # 59 layers: 3648
+    (300, 4, 12, FP64, 1),      # 70 layers: 5440
+    (300, 4, 12, FP32, 2),
+    (511, 8, 9, FP32, 2),       # 62 layers: 7680
+    (383, 4, 12, FP32, 1),      # 91 layers: 8544
+    (1023, 4, 12, FP64, 1),
+    (200, 8, 20, FP32, 2),      # 32 rows
+    (300, 3, 17, FP32, 1),
+    (120, 10, 24, FP32, 1),     # 64 rows
+    (150, 24, 13, FP64, 1),
+    (383, 4, 12, SPLIT, 1),
+])
+def test_wavefronts_of_map_chains(rules, n, b, gamma, prec, maps):
+    assert rules(n, b, gamma, prec)[2] == maps
