@@ -42,17 +42,22 @@ Apply2 apply2_of(const asp_plan* P, int nact) {
 }
 
 // algorithmic bytes and flops of a batch of layer solves: each factor entry
-// read once per launch, each grid value read and written once per right-hand side
-void solve_cost(const asp_plan* P, int sub0, int nsub, int nact, double io_vectors, double* bytes,
-                double* flops) {
+// read once per launch, each right-hand side's data and results (io bytes) once
+void solve_cost(const asp_plan* P, int sub0, int nsub, int nact, double io, double* bytes, double* flops) {
     double fb = 0, fl = 0;
     for (int s = sub0; s < sub0 + nsub; ++s) {
         fb += factor_bytes_of(P, P->subs[s]);
         const double L = P->subs[s].L;
         fl += 2.0 * P->n * L * L * 8.0;   // forward + backward, L^2 complex MACs per block
     }
-    *bytes = fb + io_vectors * nact * (double)P->N * sizeof(zd);
+    *bytes = fb + io * nact;
     *flops = fl * nact;
+}
+
+// bytes of an R or L problem's boundary row (double) and of its results on X_p
+double rl_io(const asp_plan* P, int sub) {
+    const SubDesc& d = P->subs[sub];
+    return (double)P->n * sizeof(zd) + (double)P->n * (d.xe - d.xs + 1) * elem_bytes(P);
 }
 
 }  // namespace
@@ -182,6 +187,8 @@ static asp_status apply_pass2d(asp_plan* P, const zd* r, zd* z, const int* act, 
     hipStream_t st = P->stream;
     const int m = P->m;
     const Apply2 v = apply2_of(P, nact);
+    const double esz = elem_bytes(P);
+    const double row = (double)nact * P->n;   // entries of one grid line
     double by, fl;
     // u~_{q,q} = G~^M_q f_q for q = 1..m, all at once
     {
@@ -192,8 +199,9 @@ static asp_status apply_pass2d(asp_plan* P, const zd* r, zd* z, const int* act, 
         L.in_mode = IN_GRID;
         L.r = v.R;
         L.out = v.U;
-        solve_cost(P, 0, m, nact, 2.0, &by, &fl);
-        KTimer t(P, ASP_K_SOLVE_M, by, fl);
+        // the caller's vectors into the packed ones, those read, u~ written
+        solve_cost(P, 0, m, nact, (double)P->N * (sizeof(zd) + 3 * esz), &by, &fl);
+        KTimer t(P, ASP_K_SOLVE_M, by, fl, 1 + solve_launches(P, L));
         ASP_HIP(P, launch_pack2d(P, v, r, P->N, 1, P->n, 0, act, id0, st));
         ASP_HIP(P, launch_solve2d(P, L, st));
         t.end();
@@ -202,17 +210,19 @@ static asp_status apply_pass2d(asp_plan* P, const zd* r, zd* z, const int* act, 
         // Algorithm 2 as stated: R_{t+1} and L_{m-t} solved in step t (one launch),
         // each handing its outgoing boundary line (plus u~) to the next problem of
         // its sweep; R outputs a_p in A, L outputs c_p in C
-        double sb = 0, sf = 0;
+        const double line = row * esz, wline = row * sizeof(zd);
+        double sb = 2 * (line + wline) + 2.0 * sweep_wt_line(P, nact) * esz;   // the seed
+        double sf = 0;
         for (int t = 1; t <= m - 1; ++t) {
-            double b1, f1;
-            solve_cost(P, P->idx_R(t + 1), 1, nact, 2.0, &b1, &f1);
-            sb += b1;
-            sf += f1;
-            solve_cost(P, P->idx_L(m - t), 1, nact, 2.0, &b1, &f1);
-            sb += b1;
-            sf += f1;
+            const int pair[2] = {P->idx_R(t + 1), P->idx_L(m - t)};
+            for (int s : pair) {
+                solve_cost(P, s, 1, nact, rl_io(P, s), &by, &fl);
+                sb += by;
+                sf += fl;
+            }
+            if (t < m - 1) sb += 2 * (2 * line + wline);   // the handed lines
         }
-        KTimer t(P, ASP_K_SWEEP, sb, sf, 1 + (m - 1) + (m - 2));
+        KTimer t(P, ASP_K_SWEEP, sb, sf, 1 + 2 * (m - 1) + (m - 2));
         ASP_HIP(P, launch_sweep_seed(P, v, P->wrow(P->idx_R(2)), P->wrow(P->idx_L(m - 1)), st));
         const int nsub = (int)P->subs.size();
         for (int s = 1; s <= m - 1; ++s) {
@@ -236,11 +246,13 @@ static asp_status apply_pass2d(asp_plan* P, const zd* r, zd* z, const int* act, 
         // accumulated layer by layer (W rows hold the data entering R_p / L_p); the
         // seed and the m-2 steps are timed as one span of m-1 launches
         {
-            const double esz = elem_bytes(P);
+            const double line = row * esz, wline = row * sizeof(zd);
             const double nn = (double)P->n * P->n;
             const double steps = m - 2;
+            // the seed; a step and side: the map, W in, u~, W out in both precisions
             KTimer t(P, ASP_K_SWEEP,
-                     4.0 * nact * P->n * sizeof(zd) + steps * (2.0 * nn * esz + 6.0 * nact * P->n * sizeof(zd)),
+                     2 * (line + wline) + 2.0 * sweep_wt_line(P, nact) * esz +
+                         steps * 2 * (nn * esz + 3 * line + wline),
                      steps * 2.0 * nn * nact * 8.0, m - 1);
             ASP_HIP(P, launch_sweep_seed(P, v, P->wrow(P->idx_R(2)), P->wrow(P->idx_L(m - 1)), st));
             for (int s = 1; s <= m - 2; ++s) ASP_HIP(P, launch_sweep_step(P, v, s, st));
@@ -256,16 +268,20 @@ static asp_status apply_pass2d(asp_plan* P, const zd* r, zd* z, const int* act, 
         L.out = v.A;
         L.out_L = v.C;
         L.W = v.W;
-        solve_cost(P, L.job0, 2 * m - 2, nact, 2.0, &by, &fl);
-        KTimer t(P, ASP_K_SOLVE_RL, by, fl);
+        double io = 0;
+        for (int s = L.job0; s < L.job0 + L.njobs; ++s) io += rl_io(P, s);
+        solve_cost(P, L.job0, L.njobs, nact, io, &by, &fl);
+        KTimer t(P, ASP_K_SOLVE_RL, by, fl, solve_launches(P, L));
         ASP_HIP(P, launch_solve2d(P, L, st));
         t.end();
     }
     // u~_p = u~_{p,1:p-1} + u~_{p,p} + u~_{p,p+1:m}
     {
-        KTimer t(P, ASP_K_COMBINE, 5.0 * nact * (double)P->N * sizeof(zd), 0.0);
-        ASP_HIP(P, launch_unpack2d(P, v, v.U, m > 1 ? v.A : nullptr, m > 1 ? v.C : nullptr, P->X[0][1] + 1,
-                                   m > 1 ? P->X[m - 2][1] : 0, z, P->N, 1, P->n, 0, act, id0, st));
+        // u~ on every line, a from line a0, c up to line c1, the caller's vectors
+        const int a0 = P->X[0][1] + 1, c1 = m > 1 ? P->X[m - 2][1] : 0;
+        KTimer t(P, ASP_K_COMBINE, row * ((P->n + (P->n - a0 + 1) + c1) * esz + P->n * (double)sizeof(zd)), 0.0);
+        ASP_HIP(P, launch_unpack2d(P, v, v.U, m > 1 ? v.A : nullptr, m > 1 ? v.C : nullptr, a0, c1, z, P->N, 1,
+                                   P->n, 0, act, id0, st));
         t.end();
     }
     return ASP_OK;

@@ -359,6 +359,8 @@ struct SolveLaunch {
     int twist_kind = 0;
 };
 hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t st);
+// kernel launches of launch_solve2d (IN_GRID, IN_BOUNDARY)
+int solve_launches(const asp_plan* P, const SolveLaunch& L);
 // wavefronts per 16-row tile of such a launch in input mode `in_mode` (on the plan alone)
 int solve_wavefronts(const asp_plan* P, int in_mode);
 // the map entries between blocks of different halves (after the kind-2 chains)
@@ -407,6 +409,7 @@ hipError_t launch_sweep_hand(const asp_plan* P, const Apply2& v, int rowR, int l
                              hipStream_t st);
 // sweep step t = 1..m-2 (both directions); workspace size for nrhs right-hand sides
 int sweep_wt_len(const asp_plan* P, int nrhs);
+long long sweep_wt_line(const asp_plan* P, int nact);   // entries of one transposed line
 hipError_t launch_sweep_step(const asp_plan* P, const Apply2& v, int t, hipStream_t st);
 
 // ---------------------------------------------------------------------------

@@ -1920,15 +1920,25 @@ int apply_max_rhs(const asp_plan* P) {
     return (int)std::min<long long>(std::max<long long>(s, 1), 4096);
 }
 
+// problems per launch for which the forward-result scratch has room (all of
+// them, but for a workspace of a fixed size that is nearly too small)
+static long long solve_room(const asp_plan* P, const SolveLaunch& L) {
+    const long long nchunk = (L.nact + RC - 1) / RC;
+    return P->y_elems / (nchunk * P->n * (L.rl ? P->LR_RL : P->LR_M) * RC);
+}
+
+int solve_launches(const asp_plan* P, const SolveLaunch& L) {
+    const long long room = std::max(solve_room(P, L), 1LL);
+    return 2 * (int)((L.njobs + room - 1) / room);
+}
+
 hipError_t launch_solve2d(const asp_plan* P, const SolveLaunch& L, hipStream_t st) {
     if (L.njobs <= 0 || L.nact <= 0) return hipSuccess;
     const int LR = L.rl ? P->LR_RL : P->LR_M;   // every job of one launch shares its row count
     const int nchunk = (L.nact + RC - 1) / RC;
     SolveLaunch part = L;
     if (L.in_mode != IN_TWIST) {
-        // as many problems per launch as the forward-result scratch holds (all
-        // of them, but for a workspace of a fixed size that is nearly too small)
-        const long long room = P->y_elems / ((long long)nchunk * P->n * LR * RC);
+        const long long room = solve_room(P, L);
         if (room < 1 || L.nact > apply_max_rhs(P)) return hipErrorInvalidValue;
         part.njobs = (int)std::min<long long>(L.njobs, room);
     }
@@ -1952,6 +1962,8 @@ hipError_t launch_map_cross(const asp_plan* P, const SolveLaunch& L, hipStream_t
 }
 
 static int sweep_slots(int nact) { return (nact + SW_RT - 1) / SW_RT * SW_RT; }
+
+long long sweep_wt_line(const asp_plan* P, int nact) { return (long long)P->n * sweep_slots(nact); }
 
 int sweep_wt_len(const asp_plan* P, int nrhs) { return 4 * P->n * sweep_slots(nrhs); }
 
