@@ -179,6 +179,19 @@ asp_status ensure_apply_ws(asp_plan* P, int nrhs) {
     return ASP_OK;
 }
 
+// whether the apply's third vector over nrhs right-hand sides holds a Krylov vector
+static bool shares_vector(const asp_plan* P, int nrhs) {
+    return P->dim == 2 && P->prec == ASP_PREC_FP64 && nrhs <= apply_max_rhs(P);
+}
+
+zd* shared_vector(const asp_plan* P, int nrhs) {
+    return shares_vector(P, nrhs) ? static_cast<zd*>(apply2_of(P, nrhs).C) : nullptr;
+}
+
+int krylov_vectors(const asp_plan* P, int nrhs, int restart) {
+    return 2 * restart + (shares_vector(P, nrhs) ? 1 : 2);
+}
+
 // ---------------------------------------------------------------------------
 // apply (Algorithm 2)
 // ---------------------------------------------------------------------------
@@ -506,7 +519,7 @@ extern "C" asp_status asp_workspace_estimate(const asp_plan* P, int nrhs, int re
     const double wrows = (double)std::max(2 * P->m - 2, 1) * pass * P->n * sizeof(zd);
     const double wt = (double)sweep_wt_len(P, pass) * esz;
     const double y = (double)solve_scratch_elems(P, pass) * esz;
-    const double krylov = vec * (2.0 * restart + 2.0) + krylov_small_bytes(P->N, nrhs);
+    const double krylov = vec * krylov_vectors(P, nrhs, restart) + krylov_small_bytes(P->N, nrhs);
     *bytes = (size_t)(vec2 + wrows + wt + y + krylov);
     return ASP_OK;
 }

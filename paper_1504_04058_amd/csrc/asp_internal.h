@@ -518,6 +518,13 @@ hipError_t launch_scale_vec(const zd* w, zd* v, const zd* scal, long long N, con
 
 // host-side pieces shared by the entry points
 asp_status ensure_apply_ws(asp_plan* P, int nrhs);
+// complex128 grid vectors per right-hand side in the GMRES workspace: the restart + 1
+// basis vectors, the preconditioned ones and b.  In 2D with FP64 factors the last
+// basis vector, which only the last step of a cycle writes, after its apply, and
+// nothing keeps, lies in the apply's third vector (shared_vector; NULL: it has its
+// own): an apply holds three vectors there
+int krylov_vectors(const asp_plan* P, int nrhs, int restart);
+zd* shared_vector(const asp_plan* P, int nrhs);
 asp_status apply_internal(asp_plan* P, const zd* r, zd* z, const int* act, int nact);
 // right-hand sides per chunk of the 3D nested-dissection solves
 constexpr int ND_CHUNK = 16;

@@ -54,7 +54,8 @@ asp_status ensure_krylov_ws(asp_plan* P, int nrhs, int restart) {
     P->kr_rhs = P->kr_restart = 0;
     P->kr_bytes = 0;
     const size_t vec = (size_t)nrhs * P->N;
-    if (dev_alloc(P, &P->d_V, vec * (restart + 1)) != ASP_OK) return ASP_ERR_OOM;
+    const int nv = krylov_vectors(P, nrhs, restart);   // basis, preconditioned vectors, b
+    if (dev_alloc(P, &P->d_V, vec * (nv - restart - 1)) != ASP_OK) return ASP_ERR_OOM;
     if (dev_alloc(P, &P->d_Z, vec * restart) != ASP_OK) return ASP_ERR_OOM;
     if (dev_alloc(P, &P->d_b, vec) != ASP_OK) return ASP_ERR_OOM;
     const size_t red = krylov_red_elems(P->N);
@@ -65,7 +66,7 @@ asp_status ensure_krylov_ws(asp_plan* P, int nrhs, int restart) {
     if (dev_alloc(P, &P->d_act, (size_t)nrhs) != ASP_OK) return ASP_ERR_OOM;
     P->kr_rhs = nrhs;
     P->kr_restart = restart;
-    P->kr_bytes = vec * (2 * restart + 2) * sizeof(zd) + (size_t)nrhs * red * sizeof(zd) +
+    P->kr_bytes = vec * nv * sizeof(zd) + (size_t)nrhs * red * sizeof(zd) +
                   (size_t)nrhs * (SMALL + 1 + CGS_MAXV * CGS_MAXV) * sizeof(zd);
     return ASP_OK;
 }
@@ -102,6 +103,7 @@ extern "C" asp_status asp_gmres(asp_plan* P, const void* f_, void* u_, int nrhs,
     const long long vs = (long long)nrhs * N;   // stride between Krylov vectors
     zd* V = P->d_V;
     zd* Z = P->d_Z;
+    zd* last = shared_vector(P, nrhs);   // of the basis, NULL: in V
     zd* b = P->d_b;
     zd* small = P->d_small;
     zd* scal = P->d_small + (size_t)nrhs * SMALL;
@@ -201,7 +203,7 @@ extern "C" asp_status asp_gmres(asp_plan* P, const void* f_, void* u_, int nrhs,
             if ((s = upload_act(inner)) != ASP_OK) return s;
             zd* vj = V + (long long)j * vs;
             zd* zj = Z + (long long)j * vs;
-            zd* w = V + (long long)(j + 1) * vs;
+            zd* w = last && j + 1 == restart ? last : V + (long long)(j + 1) * vs;
             // z_j = M^-1 v_j ; w = A z_j
             if ((s = apply_internal(P, vj, zj, P->d_act, ni)) != ASP_OK) return s;
             ASP_TIMED(P, ASP_K_STENCIL, 32.0 * ni * N + 8.0 * N, 40.0 * ni * N,
