@@ -13,9 +13,11 @@ server
   go into the next GMRES call on that key's plan, so requests that arrive while
   the key is busy join the following batch; different keys run concurrently on
   their own HIP streams from a pool of worker threads.  While other keys
-  occupy the device, a request for an idle key waits up to ``JOIN_S`` seconds
+  occupy the device, a request for an idle key waits up to ``join_s`` seconds
   from its arrival for others of the same key (a solve costs little more with
-  more right-hand sides, and would share the device with the running ones);
+  more right-hand sides, and would share the device with the running ones).
+  A key whose request waited in vain does not wait again until two of its
+  requests have arrived that close together;
 * records arrival, start and completion times, from which p50/p99 latency and
   solves/s follow.
 
@@ -33,7 +35,7 @@ from typing import Dict, List, Optional
 import numpy as np
 
 
-JOIN_S = 0.0015   # about the time of a small solve
+JOIN_S = 0.0015   # default join_s of a server: about the time of a small solve
 
 
 @dataclasses.dataclass
@@ -207,20 +209,26 @@ class _Entry:
     fbytes: int = 0
     busy: bool = False
     creating: bool = False
+    held: bool = False          # its queued requests wait for company
     last_used: float = 0.0
 
 
 class Server:
     """Continuous-batching request loop.  `run` replays a request stream
-    (sorted by arrival) and returns the results and summary statistics."""
+    (sorted by arrival) and returns the results and summary statistics.
+    join_s: longest wait of a request for others of its key while other keys
+    occupy the device (0: none; default JOIN_S)."""
 
     def __init__(self, backend: Backend, budget_bytes: int, max_rhs: int = 64, workers: int = 4,
-                 realtime: bool = True, progress_every: int = 0):
+                 realtime: bool = True, progress_every: int = 0, join_s: Optional[float] = None):
         self.backend = backend
         self.budget = int(budget_bytes)
         self.max_rhs = max_rhs
         self.workers = workers
         self.realtime = realtime
+        self.join_s = JOIN_S if join_s is None else join_s
+        self._last_arrival: Dict[tuple, float] = {}
+        self._alone = set()         # keys whose last wait for company was in vain
         self._lock = threading.Condition()
         self._queue: Dict[tuple, collections.deque] = collections.OrderedDict()
         self._cache: Dict[tuple, _Entry] = collections.OrderedDict()
@@ -268,11 +276,13 @@ class Server:
     def _hold(self, e, q):
         """Seconds for which the queued requests of an idle key still wait for
         company, 0 if they run now."""
-        if not self.realtime or self._arrivals_done or sum(r.nrhs for r in q) >= self.max_rhs:
+        if not self.realtime or self._arrivals_done or e.key in self._alone:
+            return 0.0
+        if sum(r.nrhs for r in q) >= self.max_rhs:
             return 0.0
         if not any(o.busy or o.creating for o in self._cache.values() if o is not e):
             return 0.0
-        return q[0].arrival + JOIN_S - (time.perf_counter() - self._t0)
+        return q[0].arrival + self.join_s - (time.perf_counter() - self._t0)
 
     def _pick(self):
         """Next unit of work under the lock: ('create', req) or ('solve', entry, reqs)."""
@@ -300,8 +310,12 @@ class Server:
                 continue
             hold = self._hold(e, q)
             if hold > 0.0:
+                e.held = True
                 self._wake = min(self._wake, hold)
                 continue
+            if e.held and len(q) == 1:
+                self._alone.add(key)
+            e.held = False
             batch, total = [], 0
             while q and (not batch or total + q[0].nrhs <= self.max_rhs):
                 total += q[0].nrhs
@@ -414,6 +428,9 @@ class Server:
                 res = self._results[r.rid]
                 res.cache_hit = r.key in seen
                 seen.add(r.key)
+                if r.arrival - self._last_arrival.get(r.key, -np.inf) <= self.join_s:
+                    self._alone.discard(r.key)
+                self._last_arrival[r.key] = r.arrival
                 self._queue.setdefault(r.key, collections.deque()).append(r)
                 self._lock.notify_all()
         with self._lock:
