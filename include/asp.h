@@ -195,16 +195,20 @@ asp_status asp_apply(asp_plan* plan, const void* r, void* z, int nrhs);
  * timing events: asp_timing_read does not see it).
  *   r, z, nrhs as for asp_apply.  The plan must be factored (asp_factor
  *   allocates the factors; this call only reads them).  2D plans and 3D plans
- *   factored by nested dissection.  The work buffers grow with n, the layer
- *   count and nrhs: 2D n = 127 fits with up to 16 right-hand sides in either
- *   precision, 3D n = 31 with 16.
+ *   factored by nested dissection.  What a request counts as grows with n, the
+ *   layer count and nrhs: 2D n = 127 fits with up to 16 right-hand sides in
+ *   either precision, 3D n = 31 with 16.  In 2D it is the bytes of two complex128
+ *   vectors of nrhs right-hand sides, their boundary rows and sweep lines, and
+ *   forward results in chunks of 1024 / LR right-hand sides (LR = 16, 32 or 64,
+ *   the rows of the widest problem); an accepted request whose buffers take more
+ *   than the array runs in passes or over the problems in parts.
  * Every call on one device uses that device's array and leaves the last
  * call's contents in it (nothing in it has to start at zero): calls that
  * overlap on one device (other streams, other plans, other host threads) race
  * and give wrong results.
  * Errors: ASP_ERR_ARG (bad arguments; a 3D plan factored by the block
- * recurrence; work buffers for nrhs right-hand sides larger than
- * ASP_NOALLOC_SCRATCH_BYTES, the message giving both sizes), ASP_ERR_STATE
+ * recurrence; a request that counts as more than ASP_NOALLOC_SCRATCH_BYTES, the
+ * message giving both sizes), ASP_ERR_STATE
  * (not factored), ASP_ERR_DEVICE. */
 asp_status asp_apply_noalloc(asp_plan* plan, const void* r, void* z, int nrhs);
 

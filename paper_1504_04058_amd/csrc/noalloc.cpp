@@ -105,9 +105,12 @@ size_t lay_out(asp_plan* P, int nrhs, unsigned char* base) {
     return c.used;
 }
 
-// what a request counts as against the limit: in 2D the vectors of nrhs
-// right-hand sides and forward results in chunks of 1024 / LR of them; where
-// the buffers of the whole batch take more than that, it runs in passes
+// what a request counts as against the limit: in 2D two complex128 vectors of
+// nrhs right-hand sides, their boundary rows and sweep lines, and forward results
+// in chunks of 1024 / LR of them.  A fixed measure, not the layout: where the
+// buffers of the whole batch would take more than the scratch, an accepted request
+// runs in passes (FP64 with one or two layers) or over the problems in parts, and
+// one that counts as too large is refused also where passes could serve it
 size_t request_bytes(asp_plan* P, int nrhs) {
     if (P->dim == 3) return lay_out(P, nrhs, nullptr);
     Carve c{nullptr};
@@ -144,8 +147,8 @@ extern "C" asp_status asp_apply_noalloc(asp_plan* P, const void* r, void* z, int
     keep.restore(P);
     if (std::max(need, used) > ASP_NOALLOC_SCRATCH_BYTES)
         return plan_fail(P, ASP_ERR_ARG,
-                         "asp_apply_noalloc: " + std::to_string(std::max(need, used)) + " bytes of work buffers for " +
-                             std::to_string(nrhs) + " right-hand sides exceed the fixed " +
+                         "asp_apply_noalloc: " + std::to_string(nrhs) + " right-hand sides count as " +
+                             std::to_string(std::max(need, used)) + " bytes of work, more than the fixed " +
                              std::to_string((size_t)ASP_NOALLOC_SCRATCH_BYTES) + "-byte scratch");
     unsigned char* base = nullptr;
     ASP_HIP(P, scratch_ptr(&base));
