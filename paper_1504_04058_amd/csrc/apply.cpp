@@ -549,7 +549,7 @@ extern "C" asp_status asp_release_workspace(asp_plan* P) {
     P->wt_elems = 0;
     P->kr_rhs = P->kr_restart = 0;
     P->kr_bytes = 0;
-    // the layer solves' scratch (shared by asp_factor and the applies)
+    // the layer solves' forward results
     dev_free(P->d_y);
     P->d_y = nullptr;
     P->y_elems = 0;

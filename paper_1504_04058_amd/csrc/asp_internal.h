@@ -76,9 +76,10 @@ __host__ __device__ __forceinline__ cplx<To> ccast(cplx<Ti> a) { return {(To)a.x
 // Block-tridiagonal layout of a 2D auxiliary problem on sweep lines lo..hi
 // (L lines): block k (k = i1 = 1..n) holds the L unknowns (i1 = k, lo..hi).
 // The factor stores, for every k, the inverse of block k's Schur complement in
-// the elimination from both ends towards mid_block(n), column-major with leading dimension LR >= L (rows past L
-// zero): entry (i, j) of block k at [(k-1) L LR + j LR + i], so that the LR
-// lanes holding the rows of one solve load each column coalesced.
+// the elimination from both ends towards mid_block(n), column-major with leading
+// dimension LR >= L (rows past L zero): entry (i, j) of block k at
+// [(k-1) L LR + j LR + i], so that 16 lanes of a wavefront load the 16 rows of a
+// tile in one run.
 //
 // 3D: block k (k = i1 = 1..n) holds the n L unknowns (i1 = k, i2, i3 = lo..hi)
 // at in-block index j = (i3 - lo) + L (i2 - 1); blocks are padded to B (a
@@ -88,7 +89,7 @@ struct SubDesc {
     int kind;            // ASP_SUB_M / R / L
     int p;               // layer index (1-based)
     int lo, hi, L;       // sweep lines of the extended grid
-    int LR;              // 2D: rows per solve wavefront (16 or 32, >= L)
+    int LR;              // 2D: rows of a stored block (16, 32 or 64, >= L)
     int B;               // 3D: padded block size (multiple of 64); 2D: 0
     int xs, xe;          // lines of X_p (output lines)
     int src_line;        // R: last line of X_{p-1};  L: first line of X_{p+1};  M: 0
@@ -144,7 +145,7 @@ struct RecDesc {
 
 // solve launch modes
 enum { IN_GRID = 0, IN_BOUNDARY = 1, IN_TWIST = 2 };
-enum { OUT_GRID_STORE = 0, OUT_GRID_ADD_U = 1, OUT_GRID_ACC = 2, OUT_LINE = 3 };
+enum { OUT_GRID_STORE = 0, OUT_GRID_ADD_U = 1 };   // 3D outputs: store, store plus u~
 
 // Per-problem sweep-axis tables, complex double, at tab_off:
 //   [0 .. L]        s at the half lines lo-1/2 .. hi+1/2
@@ -152,14 +153,14 @@ enum { OUT_GRID_STORE = 0, OUT_GRID_ADD_U = 1, OUT_GRID_ACC = 2, OUT_LINE = 3 };
 //   [2L+1 .. 3L]    1 / s at the lines lo .. hi
 inline long long sub_table_len(int L) { return 3LL * L + 1; }
 
-// Global axis tables (the boundary PML, the same on every axis), complex double:
-//   sh[k]      s at t = k + 1/2, k = 0..n
-//   inv_sh2[i] 1 / (s(i+1) h^2), i = 0..n-1
-//   inv_s[i]   1 / s(i+1)
 // the middle block of the twisted 2D factorization (1-based): the recurrence
 // runs from block 1 up and from block n down to it
 __host__ __device__ constexpr int mid_block(int n) { return (n + 1) / 2; }
 
+// Global axis tables (the boundary PML, the same on every axis), complex double:
+//   sh[k]      s at t = k + 1/2, k = 0..n
+//   inv_sh2[i] 1 / (s(i+1) h^2), i = 0..n-1
+//   inv_s[i]   1 / s(i+1)
 struct AxisTables {
     const zd* sh;
     const zd* inv_sh2;
@@ -397,8 +398,8 @@ hipError_t launch_unpack2d(const asp_plan* P, const Apply2& v, const void* U, co
                            int a_from, int c_to, zd* z, long long stride, int line0, int line1, int line_off,
                            const int* act, int id0, hipStream_t st);
 // the most sweep lines a 2D auxiliary problem may have with blocks of LR rows
-// (LR = 16, 32, 64) in element type T: the solve kernels keep two blocks in
-// LDS, which at LR = 64 holds 64 lines of FP32 and 48 of FP64
+// (LR = 16, 32, 64) in element type T: a lane of a solve holds 12 operand entries
+// (48 columns) of a 64-row block in FP64, 16 in FP32
 template <typename T>
 constexpr int max_lines_2d(int LR) { return LR <= 32 ? 32 : (sizeof(T) == 4 ? 64 : 48); }
 // the W rows (row indices) that start the two sweeps (from u~_{1,1} and u~_{m,m} in U)

@@ -1337,6 +1337,9 @@ constexpr int SW_ROWS = 16;    // output rows (i1) per block: one matrix-core ti
 // second tile is pure latency: per step at n = 150, 3 right-hand sides, FP64
 // 8.7 -> 5.4 us (5.8 with eight wavefronts), n = 511, 8, FP32 8.3 -> 7.1 (8.6
 // with four), n = 700, 24, FP64 18.4 -> 12.5; n = 1023, 64 (two tiles) 14.3.
+// Four / eight wavefronts, ms of sweep per apply with one right-hand side: FP64
+// n = 160 0.172 / 0.191, 192 0.242 / 0.265, 224 0.335 / 0.321, 256 0.391 / 0.376; FP32
+// 192 0.183 / 0.196, 224 0.246 / 0.235, 256 0.322 / 0.295 (16 and 64: the same order).
 // The number of wavefronts depends on n alone: a right-hand side's sums are the
 // same in any batch.
 constexpr int SW_ONE_TILE = 256, SW_FEW_COLUMNS = 192;

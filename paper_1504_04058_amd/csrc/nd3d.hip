@@ -537,7 +537,12 @@ hipError_t launch_nd_copyout(const asp_plan* P, const NdFront* fr, int nfr, cons
 // problems per sweep step, backward: 16 fronts of 1152 columns 24 -> 12 us
 // (64 rows and four waves against 16 and sixteen), 128 fronts of 640 columns 32
 // -> 21 us (four waves), 3328 leaf fronts (the M problems) 593 against 505 us
-// with the wide shape.  The counts leave out the chunks of right-hand sides, so
+// with the wide shape.  R and L solves, ms per apply of 16 right-hand sides with
+// the lines here / ND_WIDE 512 / 4096 / ND_FEW 256 / 1024 / never sixteen waves: n = 31 FP32
+// 0.618 / 0.610 / 0.618 / 0.617 / 0.619 / 0.670, n = 47 FP32 2.31 / 2.29 / 2.37 / 2.30 /
+// 2.38 / 2.47, n = 63 FP32 4.70 / 4.78 / 4.85 / 5.00 / 4.75 / 5.18, n = 63 FP64 7.34 /
+// 7.52 / 7.12 / 7.72 / 7.33 / 7.84; ND_DEEP 256 and 1024 within 2%, but for 0.671 with
+// 1024 at n = 31.  The counts leave out the chunks of right-hand sides, so
 // that a right-hand side's result does not depend on the batch.
 constexpr long long ND_WIDE = 1024, ND_FEW = 512;
 constexpr int ND_DEEP = 512;
