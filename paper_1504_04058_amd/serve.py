@@ -16,8 +16,8 @@ server
   occupy the device, a request for an idle key waits up to ``join_s`` seconds
   from its arrival for others of the same key (a solve costs little more with
   more right-hand sides, and would share the device with the running ones).
-  A key whose request waited in vain does not wait again until two of its
-  requests have arrived that close together;
+  A key three of whose waits in a row were in vain does not wait again until two
+  of its requests have arrived that close together;
 * records arrival, start and completion times, from which p50/p99 latency and
   solves/s follow.
 
@@ -36,6 +36,7 @@ import numpy as np
 
 
 JOIN_S = 0.0015   # default join_s of a server: about the time of a small solve
+JOIN_VAIN = 3     # waits in a row without company after which a key stops waiting
 
 
 @dataclasses.dataclass
@@ -228,7 +229,7 @@ class Server:
         self.realtime = realtime
         self.join_s = JOIN_S if join_s is None else join_s
         self._last_arrival: Dict[tuple, float] = {}
-        self._alone = set()         # keys whose last wait for company was in vain
+        self._vain: Dict[tuple, int] = {}   # waits in a row without company
         self._lock = threading.Condition()
         self._queue: Dict[tuple, collections.deque] = collections.OrderedDict()
         self._cache: Dict[tuple, _Entry] = collections.OrderedDict()
@@ -276,7 +277,7 @@ class Server:
     def _hold(self, e, q):
         """Seconds for which the queued requests of an idle key still wait for
         company, 0 if they run now."""
-        if not self.realtime or self._arrivals_done or e.key in self._alone:
+        if not self.realtime or self._arrivals_done or self._vain.get(e.key, 0) >= JOIN_VAIN:
             return 0.0
         if sum(r.nrhs for r in q) >= self.max_rhs:
             return 0.0
@@ -314,7 +315,7 @@ class Server:
                 self._wake = min(self._wake, hold)
                 continue
             if e.held and len(q) == 1:
-                self._alone.add(key)
+                self._vain[key] = self._vain.get(key, 0) + 1
             e.held = False
             batch, total = [], 0
             while q and (not batch or total + q[0].nrhs <= self.max_rhs):
@@ -429,7 +430,7 @@ class Server:
                 res.cache_hit = r.key in seen
                 seen.add(r.key)
                 if r.arrival - self._last_arrival.get(r.key, -np.inf) <= self.join_s:
-                    self._alone.discard(r.key)
+                    self._vain.pop(r.key, None)
                 self._last_arrival[r.key] = r.arrival
                 self._queue.setdefault(r.key, collections.deque()).append(r)
                 self._lock.notify_all()

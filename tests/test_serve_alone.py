@@ -1,6 +1,6 @@
-"""Serving: a request that waited in vain for company is the last of its key to
-wait, until requests of the key arrive close together again; a server option sets
-the wait or switches it off (a fake backend; the scheduler's decisions only)."""
+"""Serving: after three waits in vain the requests of a key no longer wait for
+company, until two of them arrive close together again; a server option sets the
+wait or switches it off (a fake backend; the scheduler's decisions only)."""
 import time
 
 import numpy as np
@@ -11,7 +11,7 @@ from paper_1504_04058_amd.serve import Backend, Request, Server
 
 
 class FakeBackend(Backend):
-    """Key 1 solves for 1.6 s, the others for 1 ms."""
+    """Key 1 solves for 2.6 s, the others for 1 ms."""
 
     def factor_bytes(self, req):
         return 1000
@@ -23,7 +23,7 @@ class FakeBackend(Backend):
         return req.key
 
     def solve(self, handle, f):
-        time.sleep(1.6 if handle[2] == 1 else 0.001)
+        time.sleep(2.6 if handle[2] == 1 else 0.001)
         k = f.shape[0]
         return 2 * f, np.full(k, 3, np.int32), np.full(k, 1e-7), "ASP_OK"
 
@@ -35,26 +35,27 @@ def req(rid, arrival, tag):
     return Request(rid, (2, 4, tag), arrival, 2, 4, 1.0, 1, np.ones((4, 4)), np.ones((1, 16), complex))
 
 
-# key 0 is factored first; key 1 keeps the device busy from 0.1 s to 1.7 s; a last
+# key 0 is factored first; key 1 keeps the device busy from 0.1 s to 2.7 s; a last
 # request keeps the stream open until after that
 def stream(times):
     return [req(0, 0.0, 0), req(1, 0.1, 1)] + [req(2 + i, t, 0) for i, t in enumerate(times)] + \
-        [req(2 + len(times), 1.9, 2)]
+        [req(2 + len(times), 2.9, 2)]
 
 
 def waits(res):
     return [r.start - r.arrival for r in res]
 
 
-def test_lone_requests_wait_once(monkeypatch):
+def test_lone_requests_stop_waiting(monkeypatch):
     monkeypatch.setattr(serve, "JOIN_S", 0.15)
-    res, summ = Server(FakeBackend(), budget_bytes=10 ** 6, workers=3).run(stream([0.4, 0.8, 1.2]))
-    assert summ["completed"] == 6
-    w = waits(res)[2:5]
-    assert w[0] > 0.1 and w[1] < 0.08 and w[2] < 0.08, w
+    res, summ = Server(FakeBackend(), budget_bytes=10 ** 6, workers=3).run(stream([0.3, 0.7, 1.1, 1.5, 1.9]))
+    assert summ["completed"] == 8
+    w = waits(res)[2:7]
+    assert min(w[:3]) > 0.1 and max(w[3:]) < 0.08, w
 
 
-def test_close_arrivals_wait_again():
+def test_close_arrivals_wait_again(monkeypatch):
+    monkeypatch.setattr(serve, "JOIN_VAIN", 1)
     srv = Server(FakeBackend(), budget_bytes=10 ** 6, workers=3, join_s=0.15)
     res, summ = srv.run(stream([0.3, 0.7, 0.75, 0.8, 1.3, 1.35]))
     assert summ["completed"] == 9
