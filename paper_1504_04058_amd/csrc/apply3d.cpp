@@ -117,7 +117,7 @@ asp_status factor3d(asp_plan* P) {
     for (const auto& d : P->subs) {
         const double B = (double)P->n * d.L;
         fb += factor_bytes_of(P, d);
-        fl += (double)P->n * B * B * B * 8.0;
+        fl += (double)P->n * B * B * B * 4.0;   // the inverse of a symmetric block
     }
     {
         KTimer t(P, ASP_K_FACTOR, fb, fl);

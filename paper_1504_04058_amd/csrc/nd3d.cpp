@@ -356,15 +356,15 @@ asp_status nd_factor(asp_plan* P) {
     double fb = 0, fl = 0;
     int launches = 0;
     // the method's work, from the unpadded separator (s) and boundary (t)
-    // unknowns of each front: LU elimination of the separator, 8 (s^3/3 +
+    // unknowns of each front: symmetric elimination of the separator, 4 (s^3/3 +
     // s^2 t + s t^2) real flops, and [F_II^-1 | F_II^-1 F_IB] written once.
-    // The Gauss-Jordan kernels execute more (the whole padded front, the
-    // explicit inverse), which counts as overhead, not as work.
+    // The Gauss-Jordan kernels execute more (padded fronts, the explicit
+    // inverse), which counts as overhead, not as work.
     for (const auto& F : P->nd_fronts) {
         const NdNode& nd = P->nd_nodes[F.node];
         const double sI = (double)nd.nI * F.L, tB = (double)nd.nB * F.L;
         fb += sI * (sI + tB) * e;
-        fl += 8.0 * (sI * sI * sI / 3.0 + sI * sI * tB + sI * tB * tB);
+        fl += 4.0 * (sI * sI * sI / 3.0 + sI * sI * tB + sI * tB * tB);
     }
     for (const auto& gr : P->nd_groups)
         for (int d = 0; d < P->nd_levels; ++d) {

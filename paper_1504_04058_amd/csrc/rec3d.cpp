@@ -248,7 +248,7 @@ asp_status rec_factor(asp_plan* P) {
     for (const RecDesc& d : P->rec_desc) {
         const double BB = (double)P->subs[d.outer].L * P->subs[d.inner].L;
         fb += (double)P->n * BB * BB * esz(P);
-        fl += (double)P->n * BB * BB * BB * 8.0;   // one inverse per block (the stored factor)
+        fl += (double)P->n * BB * BB * BB * 4.0;   // the inverse of a symmetric block
     }
     const int np = P->rec_Bmax / TB;
     asp_status s = ASP_OK;

@@ -1,8 +1,9 @@
-"""The bytes and launches that asp_timing_read reports for a 2D apply are those of
-its kernels: vectors with the right-hand sides fastest in the factor precision
-between the caller's complex128 ones, boundary rows in complex128, every factor
-and map entry once.  Written out here from the layers; m = 1, 2 and more, both
-sweeps, FP64 and FP32."""
+"""What asp_timing_read reports.  3D factorizations: the work of an elimination
+that keeps the symmetry.  2D applies: the bytes and launches of their kernels,
+vectors with the right-hand sides fastest in the factor precision between the
+caller's complex128 ones, boundary rows in complex128, every factor and map
+entry once.  Written out here from the layers; m = 1, 2 and more, both sweeps,
+FP64 and FP32."""
 import math
 
 import pytest
@@ -16,7 +17,7 @@ asp = pytest.importorskip("paper_1504_04058_amd.asp")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-SOLVE_M, SOLVE_RL, SWEEP, COMBINE = 2, 3, 4, 5
+FACTOR, SOLVE_M, SOLVE_RL, SWEEP, COMBINE = 0, 2, 3, 4, 5
 
 
 def expected(n, nrhs, e, layers, subs, seq):
@@ -59,3 +60,38 @@ def test_counts(n, gamma, b, nrhs, seq, prec, e):
     subs = [("MRL"[s[0]], width[s[1]], int(s[3] - s[2] + 1)) for s in subs]
     want = expected(n, nrhs, e, layers, subs, seq)
     assert {k: (v[0], v[2]) for k, v in got.items() if v[0]} == want
+
+
+def fronts(n, x0, x1, y0, y1):
+    """(separator, boundary) columns of every node of the dissection of n x n columns
+    (regions of at most 4 x 4 are leaves, others are cut at the middle of the longer side)."""
+    w, h = x1 - x0 + 1, y1 - y0 + 1
+    t = h * ((x0 > 0) + (x1 < n - 1)) + w * ((y0 > 0) + (y1 < n - 1))
+    if w <= 4 and h <= 4:
+        return [(w * h, t)]
+    if w >= h:
+        c = x0 + (w - 1) // 2
+        parts, s = [(x0, c - 1, y0, y1), (c + 1, x1, y0, y1)], h
+    else:
+        c = y0 + (h - 1) // 2
+        parts, s = [(x0, x1, y0, c - 1), (x0, x1, c + 1, y1)], w
+    return [(s, t)] + [f for p in parts if p[0] <= p[1] and p[2] <= p[3] for f in fronts(n, *p)]
+
+
+@pytest.mark.parametrize("n,gamma,b", [(9, 2, 2), (16, 4, 2)])
+@pytest.mark.parametrize("nd", [True, False])
+def test_factor_work_3d(n, gamma, b, nd):
+    print(f"factor work n={n} gamma={gamma} b={b} nd={nd}", flush=True)
+    c = workloads.velocity_random(n, 3, seed=3, width=2.0)
+    with asp.Plan(3, c, 2 * math.pi * (n + 1) / 8, n, b, gamma, prec=asp.ASP_PREC_FP32, nd3d=nd) as plan:
+        lines = [int(s[3] - s[2] + 1) for s in plan.layers()[1]]
+        asp.asp_timing_enable(plan.handle, 1)
+        plan.factor()
+        flops = asp.asp_timing_read(plan.handle, FACTOR)[3]
+        asp.asp_timing_enable(plan.handle, 0)
+    if nd:
+        want = sum(4 * ((s * L) ** 3 / 3 + (s * L) ** 2 * t * L + s * L * (t * L) ** 2)
+                   for L in lines for s, t in fronts(n, 0, n - 1, 0, n - 1))
+    else:
+        want = sum(4 * n * (n * L) ** 3 for L in lines)
+    assert abs(flops - want) <= 1e-9 * want
