@@ -245,17 +245,22 @@ class Server:
         self._completed = 0
 
     # -- memory ------------------------------------------------------------------------
-    def _reserve(self, nbytes):
-        """Reserve nbytes, evicting idle cached plans (least recently used first)."""
+    def _reserve(self, nbytes, solving=None):
+        """Reserve nbytes, evicting idle cached plans (least recently used first):
+        those without queued requests, and, for the workspace of `solving` while
+        nothing else runs (so that nothing would ever be given back), any other."""
         if nbytes > self.budget:
             return False
+        last = solving is not None and \
+            not any(e.busy or e.creating for e in self._cache.values() if e is not solving)
         while self._used + nbytes > self.budget:
             victim = None
             for e in self._cache.values():
-                if not e.busy and not e.creating and e.handle is not None \
-                        and not self._queue.get(e.key):
-                    if victim is None or e.last_used < victim.last_used:
-                        victim = e
+                if e.busy or e.creating or e.handle is None or (self._queue.get(e.key) and not last):
+                    continue
+                if victim is None or (bool(self._queue.get(e.key)), e.last_used) < \
+                        (bool(self._queue.get(victim.key)), victim.last_used):
+                    victim = e
             if victim is None:
                 return False
             self.backend.destroy(victim.handle)
@@ -328,6 +333,8 @@ class Server:
                 q.appendleft(batch.pop())            # a smaller batch may fit
                 ws = self.backend.workspace_bytes(batch[0], sum(r.nrhs for r in batch))
                 reserved = self._reserve(ws)
+            if not reserved and ws <= self.budget - e.fbytes:
+                reserved = self._reserve(ws, e)
             if not reserved:
                 e.busy = False
                 if ws > self.budget - e.fbytes:      # can never fit next to its factors
