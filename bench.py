@@ -290,7 +290,9 @@ def run_workload(name, prec_name, steps, warmup, restart=None, tol=None, nd3d=Tr
     else:
         achieved = ks["flops"] / (ks["ms"] / 1e3) / 1e12
     roof = {"bound": bound, "achieved": achieved, "peak": peak, "unit": unit,
-            "frac": achieved / peak, "traffic": recorded_traffic(name, prec_name, dom),
+            "frac": achieved / peak,
+            # the record was taken with the default factorization
+            "traffic": recorded_traffic(name, prec_name, dom) if nd3d and not fact3d else None,
             "traffic_unit": "bytes per launch", "kernel_class": dom,
             "avg_launch_ms": ks["ms"] / ks["launches"], "launches": ks["launches"],
             "per_launch_bytes": ks["bytes"] / ks["launches"],
