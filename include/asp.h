@@ -291,11 +291,17 @@ asp_status asp_timing_read(asp_plan* plan, int cls, int* launches, double* ms, d
 /* asp_workspace_estimate -- device bytes of the workspaces asp_gmres allocates
  * for nrhs right-hand sides and the given restart length (apply scratch,
  * sweep data, Krylov basis); host only.
+ * asp_device_bytes -- the device memory that the factors, the work buffers of
+ * asp_factor and those workspaces take: every buffer is a block of its own, above
+ * 1 MiB in steps of 2 MiB (the driver's), so this is what a memory budget has to
+ * count; host only.  Any of the three pointers may be NULL.
  * asp_release_workspace -- free those workspaces (and the factorization's
  * kept work buffers) now, keeping the factors (a factor cache keeps idle plans
  * this way); the next call allocates again.
  * Synchronizes the plan's stream. */
 asp_status asp_workspace_estimate(const asp_plan* plan, int nrhs, int restart, size_t* bytes);
+asp_status asp_device_bytes(const asp_plan* plan, int nrhs, int restart, size_t* factors,
+                            size_t* factor_work, size_t* workspace);
 asp_status asp_release_workspace(asp_plan* plan);
 
 /* asp_set_cache_limit -- device memory the library may keep for reuse, per

@@ -85,6 +85,7 @@ def lib():
                                     ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double),
                                     ctypes.POINTER(ctypes.c_double)]),
             "asp_workspace_estimate": (I, [P, I, I, ctypes.POINTER(ctypes.c_size_t)]),
+            "asp_device_bytes": (I, [P, I, I] + 3 * [ctypes.POINTER(ctypes.c_size_t)]),
             "asp_release_workspace": (I, [P]),
             "asp_set_cache_limit": (ctypes.c_size_t, [ctypes.c_size_t]),
             "asp_cached_bytes": (ctypes.c_size_t, []),
@@ -213,6 +214,14 @@ def asp_workspace_estimate(plan, nrhs, restart):
     b = ctypes.c_size_t()
     _check(plan, lib().asp_workspace_estimate(plan, nrhs, restart, ctypes.byref(b)))
     return b.value
+
+
+def asp_device_bytes(plan, nrhs, restart):
+    """Device memory of the factors, the factorization's work buffers and the
+    workspaces of a solve, as blocks of the allocator."""
+    b = [ctypes.c_size_t() for _ in range(3)]
+    _check(plan, lib().asp_device_bytes(plan, nrhs, restart, *(ctypes.byref(q) for q in b)))
+    return tuple(q.value for q in b)
 
 
 def asp_release_workspace(plan):

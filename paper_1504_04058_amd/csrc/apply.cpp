@@ -66,11 +66,10 @@ size_t solve_scratch_bytes(const asp_plan* P) {
     return P->dim == 2 ? (size_t)P->y_elems * elem_bytes(P) : 0;
 }
 
-size_t factor_work_estimate(const asp_plan* P) {
+BufSizes factor_work_sizes(const asp_plan* P) {
     if (P->dim == 3)
-        return P->rec ? rec_factor_work_estimate(P)
-                      : P->nd ? nd_factor_work_estimate(P) : factor3d_work_estimate(P);
-    return 0;   // 2D: the factorization and the boundary maps use no work buffers
+        return P->rec ? rec_factor_work_sizes(P) : P->nd ? nd_factor_work_sizes(P) : factor3d_work_sizes(P);
+    return BufSizes{};   // 2D: the factorization and the boundary maps use no work buffers
 }
 
 double factor_bytes_of(const asp_plan* P, const SubDesc& d) {
@@ -502,25 +501,46 @@ extern "C" asp_status asp_subsolve(asp_plan* P, int kind, int p, const void* in,
 // ---------------------------------------------------------------------------
 // workspace accounting
 // ---------------------------------------------------------------------------
+static BufSizes workspace_sizes2(const asp_plan* P, int nrhs) {
+    const size_t esz = elem_bytes(P);
+    const int pass = std::min(nrhs, apply_max_rhs(P));
+    BufSizes b;
+    b.add(3 * vec2_elems(P, pass) * esz);
+    b.add((size_t)std::max(2 * P->m - 2, 1) * pass * P->n * sizeof(zd));
+    b.add((size_t)sweep_wt_len(P, pass) * esz);
+    b.add((size_t)solve_scratch_elems(P, pass) * esz);
+    return b;
+}
+
+static BufSizes workspace_sizes(const asp_plan* P, int nrhs, int restart) {
+    BufSizes b = P->dim == 2 ? workspace_sizes2(P, nrhs)
+                 : P->rec    ? rec_workspace_sizes(P, nrhs)
+                 : P->nd     ? nd_workspace_sizes(P, nrhs)
+                             : workspace_sizes3(P, nrhs);
+    const size_t vec = (size_t)nrhs * P->N * sizeof(zd);
+    b.add(vec * (krylov_vectors(P, nrhs, restart) - restart - 1));
+    b.add(vec * restart);
+    b.add(vec);
+    const size_t red = krylov_red_bytes(P->N, nrhs);
+    b.add(red);
+    b.add((size_t)krylov_small_bytes(P->N, nrhs) - red);
+    b.blocks += devmem_block_bytes(nrhs * sizeof(int));   // the list of running right-hand sides
+    return b;
+}
+
 extern "C" asp_status asp_workspace_estimate(const asp_plan* P, int nrhs, int restart,
                                              size_t* bytes) {
     if (!P || !bytes || nrhs < 1 || restart < 1) return ASP_ERR_ARG;
-    const double esz = elem_bytes(P);
-    if (P->dim == 3) {
-        const double vec3 = (double)nrhs * P->N * sizeof(zd);
-        const double kr3 = vec3 * (2.0 * restart + 2.0) + krylov_small_bytes(P->N, nrhs);
-        *bytes = (P->rec ? rec_workspace_estimate(P, nrhs)
-                  : P->nd ? nd_workspace_estimate(P, nrhs) : workspace_estimate3(P, nrhs)) + (size_t)kr3;
-        return ASP_OK;
-    }
-    const double vec = (double)nrhs * P->N * sizeof(zd);
-    const int pass = std::min(nrhs, apply_max_rhs(P));
-    const double vec2 = 3.0 * vec2_elems(P, pass) * esz;
-    const double wrows = (double)std::max(2 * P->m - 2, 1) * pass * P->n * sizeof(zd);
-    const double wt = (double)sweep_wt_len(P, pass) * esz;
-    const double y = (double)solve_scratch_elems(P, pass) * esz;
-    const double krylov = vec * krylov_vectors(P, nrhs, restart) + krylov_small_bytes(P->N, nrhs);
-    *bytes = (size_t)(vec2 + wrows + wt + y + krylov);
+    *bytes = workspace_sizes(P, nrhs, restart).bytes;
+    return ASP_OK;
+}
+
+extern "C" asp_status asp_device_bytes(const asp_plan* P, int nrhs, int restart, size_t* factors,
+                                       size_t* factor_work, size_t* workspace) {
+    if (!P || nrhs < 1 || restart < 1) return ASP_ERR_ARG;
+    if (factors) *factors = devmem_block_bytes(P->fac_bytes) + (P->t_bytes ? devmem_block_bytes(P->t_bytes) : 0);
+    if (factor_work) *factor_work = factor_work_sizes(P).blocks;
+    if (workspace) *workspace = workspace_sizes(P, nrhs, restart).blocks;
     return ASP_OK;
 }
 

@@ -88,16 +88,22 @@ asp_status ensure_apply_ws3(asp_plan* P, int nrhs) {
     return ASP_OK;
 }
 
-size_t workspace_estimate3(const asp_plan* P, int nrhs) {
-    const double vec = (double)nrhs * P->N * sizeof(zd);
-    const double ye = (double)y3_len(P, nrhs) * esz(P);
-    const double we = 4.0 * P->S * chunks_of(nrhs) * RW3 * sizeof(zd);
-    return (size_t)(2.0 * vec + 2.0 * ye + we);
+BufSizes workspace_sizes3(const asp_plan* P, int nrhs) {
+    BufSizes b;
+    for (int i = 0; i < 2; ++i) {
+        b.add((size_t)nrhs * P->N * sizeof(zd));
+        b.add((size_t)y3_len(P, nrhs) * esz(P));
+    }
+    b.add((size_t)4 * P->S * chunks_of(nrhs) * RW3 * sizeof(zd));
+    return b;
 }
 
-size_t factor3d_work_estimate(const asp_plan* P) {
+BufSizes factor3d_work_sizes(const asp_plan* P) {
     const size_t nsub = P->subs.size();
-    return nsub * ((size_t)P->Bmax * TB3 + (size_t)TB3 * TB3) * esz(P);
+    BufSizes b;
+    b.add(nsub * P->Bmax * TB3 * esz(P));
+    b.add(nsub * TB3 * TB3 * esz(P));
+    return b;
 }
 
 // Algorithm 3: every auxiliary problem at once, block k after block k-1; each

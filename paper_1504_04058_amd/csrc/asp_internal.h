@@ -374,6 +374,16 @@ hipError_t launch_rgf2d(const asp_plan* P, int job0, int job1, int njobs, hipStr
 // to another plan, so a block is freed only once no work is pending on it
 // (after a synchronization of the owning plan's stream)
 hipError_t devmem_alloc(void** p, size_t bytes);
+size_t devmem_block_bytes(size_t bytes);   // of the block that an allocation takes
+
+// Sizes of some buffers: their sum, and what their blocks take
+struct BufSizes {
+    size_t bytes = 0, blocks = 0;
+    void add(size_t b) {
+        bytes += b;
+        blocks += devmem_block_bytes(b);
+    }
+};
 void devmem_free(void* p);
 
 // The vectors of a 2D apply over nact right-hand sides hold them (slots)
@@ -495,6 +505,7 @@ hipError_t launch_gram(zd* small, int small_stride, int off_h1, int off_h2, int 
                        const zd* scal, zd* E, int j, const int* act, int nact, hipStream_t st);
 // device bytes of the GMRES partial sums, small arrays and Gram columns
 double krylov_small_bytes(long long N, int nrhs);
+size_t krylov_red_bytes(long long N, int nrhs);   // ... of which the partial sums
 // partial sums of |v|^2 per right-hand side, reduced by launch_reduce (one value)
 hipError_t launch_norms(const zd* v, long long N, const int* act, int nact, zd* partial,
                         hipStream_t st);
@@ -532,15 +543,15 @@ constexpr int ND_CHUNK = 16;
 // device bytes of the 2D layer solves' forward-substitution scratch now allocated
 size_t solve_scratch_bytes(const asp_plan* P);
 // device bytes of the work buffers asp_factor allocates besides the factors
-size_t factor_work_estimate(const asp_plan* P);
-size_t nd_factor_work_estimate(const asp_plan* P);
-size_t factor3d_work_estimate(const asp_plan* P);
+BufSizes factor_work_sizes(const asp_plan* P);
+BufSizes nd_factor_work_sizes(const asp_plan* P);
+BufSizes factor3d_work_sizes(const asp_plan* P);
 // algorithmic bytes of one auxiliary problem's factor (n dense L x L blocks in
 // 2D, n dense nL x nL blocks in 3D)
 double factor_bytes_of(const asp_plan* P, const SubDesc& d);
 // 3D counterparts (apply3d.cpp)
 asp_status ensure_apply_ws3(asp_plan* P, int nrhs);
-size_t workspace_estimate3(const asp_plan* P, int nrhs);
+BufSizes workspace_sizes3(const asp_plan* P, int nrhs);
 asp_status factor3d(asp_plan* P);
 asp_status apply3d_internal(asp_plan* P, const zd* r, zd* z, const int* act, int nact);
 asp_status subsolve3d(asp_plan* P, int idx, const void* in, void* out, int nrhs);
@@ -552,7 +563,7 @@ asp_status nd_factor(asp_plan* P);
 asp_status nd_apply(asp_plan* P, const zd* r, zd* z, const int* act, int nact);
 asp_status nd_subsolve(asp_plan* P, int idx, const void* in, void* out, int nrhs);
 asp_status nd_ensure_ws(asp_plan* P, int nrhs);
-size_t nd_workspace_estimate(const asp_plan* P, int nrhs);
+BufSizes nd_workspace_sizes(const asp_plan* P, int nrhs);
 
 // recursive sweep (rec3d.cpp): inner problems and job lists at setup, factor,
 // apply, one auxiliary solve, workspaces
@@ -562,8 +573,8 @@ asp_status rec_factor(asp_plan* P);
 asp_status rec_apply(asp_plan* P, const zd* r, zd* z, const int* act, int nact);
 asp_status rec_subsolve(asp_plan* P, int idx, const void* in, void* out, int nrhs);
 asp_status rec_ensure_ws(asp_plan* P, int nrhs);
-size_t rec_workspace_estimate(const asp_plan* P, int nrhs);
-size_t rec_factor_work_estimate(const asp_plan* P);
+BufSizes rec_workspace_sizes(const asp_plan* P, int nrhs);
+BufSizes rec_factor_work_sizes(const asp_plan* P);
 void rec_free_ws(asp_plan* P);
 
 // recursive-sweep kernels (rec3d.hip).  A launch covers nslot slabs (outer

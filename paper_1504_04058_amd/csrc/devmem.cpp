@@ -70,6 +70,8 @@ void trim_device(int dev, size_t keep) {
 
 }  // namespace
 
+size_t devmem_block_bytes(size_t bytes) { return rounded(bytes); }
+
 hipError_t devmem_alloc(void** p, size_t bytes) {
     *p = nullptr;
     int dev = 0;

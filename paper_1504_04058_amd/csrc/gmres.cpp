@@ -340,3 +340,5 @@ extern "C" asp_status asp_gmres(asp_plan* P, const void* f_, void* u_, int nrhs,
 double krylov_small_bytes(long long N, int nrhs) {
     return (double)nrhs * (double)(krylov_red_elems(N) + SMALL + 1 + CGS_MAXV * CGS_MAXV) * sizeof(zd);
 }
+
+size_t krylov_red_bytes(long long N, int nrhs) { return (size_t)nrhs * krylov_red_elems(N) * sizeof(zd); }

@@ -348,7 +348,7 @@ asp_status nd_factor(asp_plan* P) {
         P->d_nd_lb[1] = lb1;
         P->d_nd_rb = rb0;
         P->d_nd_db = db0;
-        P->nd_work_bytes = nd_factor_work_estimate(P);
+        P->nd_work_bytes = nd_factor_work_sizes(P).bytes;
     }
     char* lb[2] = {static_cast<char*>(P->d_nd_lb[0]), static_cast<char*>(P->d_nd_lb[1])};
     char* rb = static_cast<char*>(P->d_nd_rb);
@@ -407,15 +407,22 @@ asp_status nd_factor(asp_plan* P) {
     return s;
 }
 
-size_t nd_factor_work_estimate(const asp_plan* P) {
-    return (2 * (size_t)P->nd_lvlbuf + (size_t)P->nd_rbuf + (size_t)P->nd_dbuf * NDT * NDT) * esz(P);
+BufSizes nd_factor_work_sizes(const asp_plan* P) {
+    BufSizes b;
+    for (int i = 0; i < 2; ++i) b.add((size_t)P->nd_lvlbuf * esz(P));
+    b.add((size_t)P->nd_rbuf * esz(P));
+    b.add((size_t)P->nd_dbuf * NDT * NDT * esz(P));
+    return b;
 }
 
-size_t nd_workspace_estimate(const asp_plan* P, int nrhs) {
-    const double ch = (nrhs + RW - 1) / RW;
-    const double vec = (double)nrhs * P->N * sizeof(zd);
-    const double we = 4.0 * P->S * ch * RW * sizeof(zd);
-    return (size_t)(2.0 * vec + we + ch * (double)(P->nd_vtot + P->nd_xtot) * esz(P));
+BufSizes nd_workspace_sizes(const asp_plan* P, int nrhs) {
+    const size_t ch = (nrhs + RW - 1) / RW;
+    BufSizes b;
+    for (int i = 0; i < 2; ++i) b.add((size_t)nrhs * P->N * sizeof(zd));
+    b.add(4 * P->S * ch * RW * sizeof(zd));
+    b.add(ch * P->nd_vtot * esz(P));
+    b.add(ch * P->nd_xtot * esz(P));
+    return b;
 }
 
 asp_status nd_ensure_ws(asp_plan* P, int nrhs) {
@@ -443,7 +450,7 @@ asp_status nd_ensure_ws(asp_plan* P, int nrhs) {
     P->d_nd_x = x;
     P->w3_elems = we;
     P->ws_rhs = nrhs;
-    P->ws_bytes = nd_workspace_estimate(P, nrhs);
+    P->ws_bytes = nd_workspace_sizes(P, nrhs).bytes;
     return ASP_OK;
 }
 

@@ -418,7 +418,7 @@ extern "C" asp_status asp_info(const asp_plan* P, asp_plan_info* info) {
     info->factor_bytes = P->fac_bytes + P->t_bytes;
     info->workspace_bytes = P->ws_bytes + P->kr_bytes + P->nd_work_bytes + solve_scratch_bytes(P);
     info->factored = P->factored ? 1 : 0;
-    info->factor_work_bytes = factor_work_estimate(P);
+    info->factor_work_bytes = factor_work_sizes(P).bytes;
     return ASP_OK;
 }
 

@@ -227,9 +227,12 @@ asp_status rec_upload(asp_plan* P) {
     return ASP_OK;
 }
 
-size_t rec_factor_work_estimate(const asp_plan* P) {
+BufSizes rec_factor_work_sizes(const asp_plan* P) {
     const size_t nall = P->rec_desc.size();
-    return nall * ((size_t)P->rec_Bmax * TB + (size_t)TB * TB) * esz(P);
+    BufSizes b;
+    b.add(nall * P->rec_Bmax * TB * esz(P));
+    b.add(nall * TB * TB * esz(P));
+    return b;
 }
 
 // Algorithm 1 for every inner problem of every outer problem at once: block k
@@ -270,12 +273,15 @@ asp_status rec_factor(asp_plan* P) {
     return s;
 }
 
-size_t rec_workspace_estimate(const asp_plan* P, int nrhs) {
+BufSizes rec_workspace_sizes(const asp_plan* P, int nrhs) {
     const int chunks = (nrhs + RW - 1) / RW;
-    const double vec = (double)nrhs * P->N * sizeof(zd);
-    const double we = 4.0 * P->S * chunks * RW * sizeof(zd);
-    return (size_t)(2.0 * vec + we +
-                    (4.0 * sv_len(P, chunks) + w2_len(P, chunks) + 2.0 * blk_len(P, chunks)) * esz(P));
+    BufSizes b;
+    for (int i = 0; i < 2; ++i) b.add((size_t)nrhs * P->N * sizeof(zd));
+    b.add((size_t)4 * P->S * chunks * RW * sizeof(zd));
+    b.add(4 * sv_len(P, chunks) * esz(P));
+    b.add(w2_len(P, chunks) * esz(P));
+    for (int i = 0; i < 2; ++i) b.add(blk_len(P, chunks) * esz(P));
+    return b;
 }
 
 void rec_free_ws(asp_plan* P) {
@@ -319,7 +325,7 @@ asp_status rec_ensure_ws(asp_plan* P, int nrhs) {
     P->rec_chunks = chunks;
     P->w3_elems = we;
     P->ws_rhs = nrhs;
-    P->ws_bytes = rec_workspace_estimate(P, nrhs);
+    P->ws_bytes = rec_workspace_sizes(P, nrhs).bytes;
     return ASP_OK;
 }
 

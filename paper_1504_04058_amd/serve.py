@@ -106,6 +106,12 @@ class Backend:
     def workspace_bytes(self, req: Request, nrhs: int) -> int:
         raise NotImplementedError
 
+    def device_bytes(self, req: Request, nrhs: int):
+        """The device memory that the factors, the factorization's work buffers
+        and the workspace of a solve really take (a device hands memory out in
+        steps): what the server counts against its budget."""
+        return self.factor_bytes(req), self.factor_work_bytes(req), self.workspace_bytes(req, nrhs)
+
     def create(self, req: Request):
         raise NotImplementedError
 
@@ -135,7 +141,7 @@ class AspBackend(Backend):
         # the library's setting); given back by close()
         self._cache_prev = None if cache_bytes is None else asp.asp_set_cache_limit(cache_bytes)
         self._hosts = {}      # shape -> host-only plan (sizes only, no device state)
-        self._ws = {}         # (shape, nrhs) -> workspace bytes
+        self._ws = {}         # (shape, nrhs[, "device"]) -> workspace bytes, device memory
         self._lock = threading.Lock()
 
     def _host_plan(self, req):
@@ -162,6 +168,13 @@ class AspBackend(Backend):
             if (k, nrhs) not in self._ws:
                 self._ws[(k, nrhs)] = self.asp.asp_workspace_estimate(h, nrhs, self.restart)
             return self._ws[(k, nrhs)]
+
+    def device_bytes(self, req, nrhs):
+        k, (h, _) = self._host_plan(req)
+        with self._lock:
+            if (k, nrhs, "device") not in self._ws:
+                self._ws[(k, nrhs, "device")] = self.asp.asp_device_bytes(h, nrhs, self.restart)
+            return self._ws[(k, nrhs, "device")]
 
     def create(self, req):
         torch = self.torch
@@ -207,7 +220,8 @@ class AspBackend(Backend):
 class _Entry:
     key: tuple
     handle: object = None
-    fbytes: int = 0
+    fbytes: int = 0             # reserved for the factors
+    fsize: int = 0              # their size
     busy: bool = False
     creating: bool = False
     held: bool = False          # its queued requests wait for company
@@ -306,12 +320,16 @@ class Server:
                     self._fail(list(q), "exceeds the device memory budget")
                     q.clear()
                     continue
-                # the factors, and the factorization's work buffers while it runs
-                if not self._reserve(fb + fw):
+                # the factors, and the factorization's work buffers while it runs;
+                # the whole budget where the sizes fit it but not their blocks
+                fac, work, _ = self.backend.device_bytes(req, 1)
+                fac = min(fac, self.budget)
+                work = min(work, self.budget - fac)
+                if not self._reserve(fac + work):
                     continue
-                e = _Entry(key, fbytes=fb, creating=True)
+                e = _Entry(key, fbytes=fac, fsize=fb, creating=True)
                 self._cache[key] = e
-                return ("create", e, req, fw)
+                return ("create", e, req, work)
             if e.busy or e.creating:
                 continue
             hold = self._hold(e, q)
@@ -327,17 +345,20 @@ class Server:
                 total += q[0].nrhs
                 batch.append(q.popleft())
             e.busy = True                            # its own factors are not evictable
-            ws = self.backend.workspace_bytes(batch[0], total)
+            ws = self.backend.device_bytes(batch[0], total)[2]
             reserved = self._reserve(ws)
             while not reserved and len(batch) > 1:
                 q.appendleft(batch.pop())            # a smaller batch may fit
-                ws = self.backend.workspace_bytes(batch[0], sum(r.nrhs for r in batch))
+                ws = self.backend.device_bytes(batch[0], sum(r.nrhs for r in batch))[2]
                 reserved = self._reserve(ws)
-            if not reserved and ws <= self.budget - e.fbytes:
+            size = self.backend.workspace_bytes(batch[0], sum(r.nrhs for r in batch))
+            if not reserved and size <= self.budget - e.fsize:
+                # all that is left, where the sizes fit the budget but not their blocks
+                ws = min(ws, self.budget - e.fbytes)
                 reserved = self._reserve(ws, e)
             if not reserved:
                 e.busy = False
-                if ws > self.budget - e.fbytes:      # can never fit next to its factors
+                if size > self.budget - e.fsize:     # can never fit next to its factors
                     self._fail(batch, "exceeds the device memory budget")
                 else:
                     for r in reversed(batch):
